@@ -11,6 +11,7 @@
 #include <cstring>
 #include <new>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -201,6 +202,27 @@ struct octgrav_tree : DevAlloc {
     }
   }
 
+  // Scratch of a direct sum over nt targets (at most about 33 MB, see
+  // direct_scratch_bytes), kept for the next call; NULL where none is needed
+  // or the device has no memory for it (the sum then runs in one range).
+  void* d_direct = nullptr;
+  int64_t direct_cap = 0;
+  std::mutex direct_mu;
+  void* direct_scratch(int64_t nt) {
+    const int64_t need = direct_scratch_bytes(h.n, nt);
+    if (need <= direct_cap) return need ? d_direct : nullptr;
+    if (d_direct) dfree(d_direct);
+    direct_cap = 0;
+    d_direct = nullptr;
+    if (dalloc(&d_direct, (size_t)need) != OCTGRAV_OK) {
+      d_direct = nullptr;
+      g_err.clear();
+      return nullptr;
+    }
+    direct_cap = need;
+    return d_direct;
+  }
+
   template <typename T>
   int upload(const std::vector<T>& v, const T** out) {
     void* p = nullptr;
@@ -286,6 +308,8 @@ struct octgrav_tree : DevAlloc {
     learned = false;
     d_wrec_com = nullptr;
     com_theta = -1.0f;
+    d_direct = nullptr;
+    direct_cap = 0;
     dev = false;
     std::string err;
     if (build_device_tree(pos, mass, true, n, n_leaf, n_group, h, dt, darr, *this, stream, err,
@@ -994,11 +1018,17 @@ int octgrav_direct(octgrav_tree* t, float eps, const int32_t* targets, int64_t n
     for (int32_t v : tg)
       if (v < 0 || v >= t->h.n) return fail(OCTGRAV_EINVAL, "target index out of range");
   }
-  if (launch_direct(t->dt, targets, nt, eps, acc, pot, t->stream))
-    return fail(OCTGRAV_EHIP, "direct-sum launch failed");
-  if (hipStreamSynchronize(t->stream) != hipSuccess)
-    return fail(OCTGRAV_EHIP, std::string("device error: ") + hipGetErrorString(hipGetLastError()));
-  return OCTGRAV_OK;
+  try {
+    // The scratch is the handle's: calls from several threads take turns.
+    std::lock_guard<std::mutex> lock(t->direct_mu);
+    if (launch_direct(t->dt, targets, nt, eps, acc, pot, t->direct_scratch(nt), t->stream))
+      return fail(OCTGRAV_EHIP, "direct-sum launch failed");
+    if (hipStreamSynchronize(t->stream) != hipSuccess)
+      return fail(OCTGRAV_EHIP, std::string("device error: ") + hipGetErrorString(hipGetLastError()));
+    return OCTGRAV_OK;
+  } catch (const std::exception& e) {
+    return fail(OCTGRAV_EHIP, e.what());
+  }
 }
 
 int octgrav_mac_collect(octgrav_tree* t, float theta_lo, float theta_hi, float eps,

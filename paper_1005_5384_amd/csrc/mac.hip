@@ -4,6 +4,8 @@
 // walk records of the centre-of-mass offset opening test.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device_common.h"
 #include "octgrav_internal.h"
 
@@ -13,41 +15,126 @@ namespace {
 using namespace dev;
 
 constexpr int kThreads = 256;
-constexpr int kDTile = 1024;
+constexpr int kDTile = 256;
 
-// Direct sum: one thread per target, all particles streamed through LDS in
-// tiles; plain FP32 per tile folded into Neumaier pairs.  The target itself
-// contributes -m_i/eps to the potential and nothing to the acceleration;
-// that same FP32 value is removed at the end.
-__global__ __launch_bounds__(kThreads) void direct_kernel(DevTree T, const int32_t* targets,
-                                                          int64_t nt, float eps2, float* acc,
-                                                          float* pot) {
+// Direct sum.  One wave per block takes 64 * kDTpl targets, kDTpl per lane, and
+// one of `splits` contiguous ranges of the particles, streamed through LDS in
+// tiles of kDTile; plain FP32 per tile folded into compensated pairs.  The
+// target itself contributes -m_i/eps to the potential and nothing to the
+// acceleration; that same FP32 value is removed at the end.
+//
+// Bound: VALU issue, 13 FP32 instructions and one v_rsq_f32 per pair.  Measured
+// issue costs (cycles per wave instruction and SIMD): 2.4 for FP32 arithmetic on
+// vector registers or constants, 4.2 as soon as one operand is a scalar
+// register, 8.3 for v_rsq_f32.  So eps^2 sits in a vector register, one LDS
+// read serves two targets, and the tile loop is unrolled with the reads at
+// constant offsets.  The ranges fill the chip for any number of targets: 4096
+// targets of 2^20 particles made 16 blocks of four waves before (39.6 ms).
+constexpr int kDTpl = 2;
+constexpr int kDTargets = kDTpl * 64;
+
+// Forces a wave-uniform value into a vector register.
+__device__ __forceinline__ float in_vgpr(float v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+__global__ __launch_bounds__(64) void direct_kernel(DevTree T, const int32_t* __restrict__ targets,
+                                                    int64_t nt, float eps2, int64_t range,
+                                                    float4* __restrict__ part_out,
+                                                    float* __restrict__ acc,
+                                                    float* __restrict__ pot) {
   __shared__ float4 src[kDTile];
   const float4* part = reinterpret_cast<const float4*>(T.part);
-  const int64_t u = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const bool act = u < nt;
-  const int64_t i = act ? T.iperm[targets ? targets[u] : u] : 0;
-  const float4 xi = part[i];
-  Sum4 s;
-  s.zero();
-  for (int64_t base = 0; base < T.n; base += kDTile) {
-    const int cnt = (int)min((int64_t)kDTile, T.n - base);
-    for (int k = threadIdx.x; k < cnt; k += kThreads) src[k] = part[base + k];
-    __syncthreads();
-    if (act) {
-      float ax = 0.f, ay = 0.f, az = 0.f, ph = 0.f;
-      for (int j = 0; j < cnt; ++j) pp_term(xi, src[j], eps2, ax, ay, az, ph);
-      s.fold<false>(ax, ay, az, ph);
+  const int lane = threadIdx.x;
+  const int64_t u0 = (int64_t)blockIdx.x * kDTargets + lane;
+  const int64_t beg = (int64_t)blockIdx.y * range, end = min(T.n, beg + range);
+  float4 xi[kDTpl];
+  Sum4 s[kDTpl];
+#pragma unroll
+  for (int q = 0; q < kDTpl; ++q) {
+    const int64_t u = min(u0 + 64 * q, nt - 1);  // lanes past the end repeat the last target
+    xi[q] = part[T.iperm[targets ? targets[u] : u]];
+    s[q].zero();
+  }
+  const float e2 = in_vgpr(eps2);
+  for (int64_t base = beg; base < end; base += kDTile) {
+#pragma unroll
+    for (int k = 0; k < kDTile / 64; ++k) {
+      const int64_t j = base + 64 * k + lane;
+      // entries past the range carry no mass
+      src[64 * k + lane] = j < end ? part[j] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
+    const int cnt = ((int)min((int64_t)kDTile, end - base) + 3) & ~3;
+    float a[kDTpl][4];
+#pragma unroll
+    for (int q = 0; q < kDTpl; ++q) a[q][0] = a[q][1] = a[q][2] = a[q][3] = 0.f;
+    for (int j = 0; j < cnt; j += 4) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4 sj = src[j + k];
+#pragma unroll
+        for (int q = 0; q < kDTpl; ++q) pp_term(xi[q], sj, e2, a[q][0], a[q][1], a[q][2], a[q][3]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kDTpl; ++q) s[q].fold<false>(a[q][0], a[q][1], a[q][2], a[q][3]);
+    __syncthreads();
   }
-  if (act) {
-    neu_add(s.s[3], s.c[3], self_term(xi.w, eps2));
-    acc[3 * u + 0] = s.s[0] + s.c[0];
-    acc[3 * u + 1] = s.s[1] + s.c[1];
-    acc[3 * u + 2] = s.s[2] + s.c[2];
-    if (pot) pot[u] = s.s[3] + s.c[3];
+#pragma unroll
+  for (int q = 0; q < kDTpl; ++q) {
+    const int64_t u = u0 + 64 * q;
+    if (u >= nt) continue;
+    if (part_out) {
+      float4* o = part_out + 2 * ((int64_t)blockIdx.y * nt + u);
+      o[0] = make_float4(s[q].s[0], s[q].s[1], s[q].s[2], s[q].s[3]);
+      o[1] = make_float4(s[q].c[0], s[q].c[1], s[q].c[2], s[q].c[3]);
+      continue;
+    }
+    neu_add(s[q].s[3], s[q].c[3], self_term(xi[q].w, eps2));
+    acc[3 * u + 0] = s[q].s[0] + s[q].c[0];
+    acc[3 * u + 1] = s[q].s[1] + s[q].c[1];
+    acc[3 * u + 2] = s[q].s[2] + s[q].c[2];
+    if (pot) pot[u] = s[q].s[3] + s[q].c[3];
   }
+}
+
+// Adds the ranges' compensated sums of each target, sixteen lanes per target:
+// every lane a contiguous run of ranges, then the lanes in order.
+constexpr int kDLanes = 16;
+__global__ __launch_bounds__(kThreads) void direct_combine_kernel(
+    DevTree T, const int32_t* __restrict__ targets, int64_t nt, float eps2, int splits,
+    const float4* __restrict__ part_in, float* __restrict__ acc, float* __restrict__ pot) {
+  constexpr int kPer = kThreads / kDLanes;  // targets per block
+  __shared__ float4 sh[2][kDLanes][kPer];
+  const int t = threadIdx.x % kPer, l = threadIdx.x / kPer;
+  const int64_t u = (int64_t)blockIdx.x * kPer + t;
+  Sum4 s;
+  s.zero();
+  const int per = (splits + kDLanes - 1) / kDLanes;
+  const int k1 = min(splits, (l + 1) * per);
+  if (u < nt)
+    for (int k = l * per; k < k1; ++k) {
+      const float4 a = part_in[2 * ((int64_t)k * nt + u)], b = part_in[2 * ((int64_t)k * nt + u) + 1];
+      s.fold<false>(a.x, a.y, a.z, a.w);
+      s.fold<false>(b.x, b.y, b.z, b.w);
+    }
+  sh[0][l][t] = make_float4(s.s[0], s.s[1], s.s[2], s.s[3]);
+  sh[1][l][t] = make_float4(s.c[0], s.c[1], s.c[2], s.c[3]);
+  __syncthreads();
+  if (l != 0 || u >= nt) return;
+  for (int k = 1; k < kDLanes; ++k) {
+    const float4 a = sh[0][k][t], b = sh[1][k][t];
+    s.fold<false>(a.x, a.y, a.z, a.w);
+    s.fold<false>(b.x, b.y, b.z, b.w);
+  }
+  const float m = reinterpret_cast<const float4*>(T.part)[T.iperm[targets ? targets[u] : u]].w;
+  neu_add(s.s[3], s.c[3], self_term(m, eps2));
+  acc[3 * u + 0] = s.s[0] + s.c[0];
+  acc[3 * u + 1] = s.s[1] + s.c[1];
+  acc[3 * u + 2] = s.s[2] + s.c[2];
+  if (pot) pot[u] = s.s[3] + s.c[3];
 }
 
 // One block per band pair (group g, cell c): for every target i of g, the
@@ -166,11 +253,33 @@ int launch_com_records(const DevTree& T, float theta, float* out, void* stream) 
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// Source ranges of a direct sum: enough waves for eight per SIMD (256 CUs x 4
+// SIMDs; below about four the issue rate falls), each over at least two tiles.
+// The cost of a range is 32 bytes per target written and read again.
+int direct_splits(int64_t n, int64_t nt) {
+  const int64_t tb = (nt + kDTargets - 1) / kDTargets;
+  const int64_t want = (8 * 1024 + tb - 1) / tb, most = (n + 2 * kDTile - 1) / (2 * kDTile);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({want, most, 1024}));
+}
+
+int64_t direct_scratch_bytes(int64_t n, int64_t nt) {
+  const int splits = direct_splits(n, nt);
+  return splits > 1 ? 32 * (int64_t)splits * nt : 0;
+}
+
 int launch_direct(const DevTree& T, const int32_t* targets, int64_t nt, float eps, float* acc,
-                  float* pot, void* stream) {
+                  float* pot, void* scratch, void* stream) {
   if (nt <= 0) return 0;
-  const int64_t grid = (nt + kThreads - 1) / kThreads;
-  direct_kernel<<<grid, kThreads, 0, (hipStream_t)stream>>>(T, targets, nt, eps * eps, acc, pot);
+  hipStream_t s = (hipStream_t)stream;
+  int splits = scratch ? direct_splits(T.n, nt) : 1;
+  const int64_t tiles = (T.n + kDTile - 1) / kDTile, per = (tiles + splits - 1) / splits;
+  splits = (int)((tiles + per - 1) / per);  // no empty range
+  const dim3 grid((nt + kDTargets - 1) / kDTargets, splits);
+  float4* p = splits > 1 ? (float4*)scratch : nullptr;
+  direct_kernel<<<grid, 64, 0, s>>>(T, targets, nt, eps * eps, per * kDTile, p, acc, pot);
+  if (p)
+    direct_combine_kernel<<<(nt + kThreads / kDLanes - 1) / (kThreads / kDLanes), kThreads, 0, s>>>(
+        T, targets, nt, eps * eps, splits, p, acc, pot);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -143,9 +143,12 @@ int launch_walk_eval_block(const DevTree& T, const WalkBufs& B, float theta, flo
 // offset opening test at theta: boundary (com, l + theta |com - cb|), topology.
 int launch_com_records(const DevTree& T, float theta, float* out, void* stream);
 // FP32 compensated direct sum for targets (caller indices, device array, or
-// NULL = all); outputs in target order.
+// NULL = all); outputs in target order.  scratch: direct_scratch_bytes of
+// device memory for the partial sums of several particle ranges per target,
+// or NULL (one range).
 int launch_direct(const DevTree& T, const int32_t* targets, int64_t nt, float eps, float* acc,
-                  float* pot, void* stream);
+                  float* pot, void* scratch, void* stream);
+int64_t direct_scratch_bytes(int64_t n, int64_t nt);
 // Features (12, FP32) and labels of the band pairs of the listed groups
 // (pair p of listed group s sits at out_off[s] + k); also each pair's ids.
 int launch_mac_labels(const DevTree& T, const WalkBufs& B, const int32_t* groups, int64_t ngs,
