@@ -354,15 +354,14 @@ struct octgrav_tree : DevAlloc {
     if ((rc = dalloc(&p, 9 * 64 * 4))) return rc;
     wb.wctr = (int32_t*)p;
     // Fallback frontier queues: a breadth-first FIFO never holds more than
-    // two consecutive levels, hence at most twice the widest level; entries
-    // of two words (the fused wave walk's child ranges).
+    // two consecutive levels, hence at most twice the widest level.
     int64_t cap = 64;
     while (cap < 2 * h.max_level_cells + 64) cap <<= 1;
     wb.gq_cap = cap;
     wb.gq_waves = fallback_waves();
     // At most 4 GiB of queues.
-    while (wb.gq_waves > 64 && (int64_t)wb.gq_waves * cap * 8 > (int64_t(1) << 32)) wb.gq_waves >>= 1;
-    if ((rc = dalloc(&p, (size_t)wb.gq_waves * cap * 8))) return rc;
+    while (wb.gq_waves > 64 && (int64_t)wb.gq_waves * cap * 4 > (int64_t(1) << 32)) wb.gq_waves >>= 1;
+    if ((rc = dalloc(&p, (size_t)wb.gq_waves * cap * 4))) return rc;
     wb.gq = (int32_t*)p;
     wb.lds_qcap = lds_queue_entries();
     wb.export_lists = 0;
@@ -806,7 +805,7 @@ int octgrav_forces_noalloc(octgrav_tree* t, float theta, float eps, float* acc, 
     b.ovf_list = (int32_t*)take((size_t)std::max(ng, nw) * 4);
     b.ovf_list2 = (int32_t*)take((size_t)std::max(ng, nw) * 4);
     double* part = (double*)take((size_t)diag_scratch_entries(t->h.n) * 8);
-    const size_t limit = noalloc_limit(), qbytes = (size_t)t->wb.gq_cap * 8;
+    const size_t limit = noalloc_limit(), qbytes = (size_t)t->wb.gq_cap * 4;
     if (off + qbytes > limit)
       return fail(OCTGRAV_EINVAL, "tree needs " + std::to_string(off + qbytes) +
                                       " bytes of scratch; octgrav_forces_noalloc has " +

@@ -33,12 +33,6 @@ constexpr int kDTile = 256;
 constexpr int kDTpl = 2;
 constexpr int kDTargets = kDTpl * 64;
 
-// Forces a wave-uniform value into a vector register.
-__device__ __forceinline__ float in_vgpr(float v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 __global__ __launch_bounds__(64) void direct_kernel(DevTree T, const int32_t* __restrict__ targets,
                                                     int64_t nt, float eps2, int64_t range,
                                                     float4* __restrict__ part_out,

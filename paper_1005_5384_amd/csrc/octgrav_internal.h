@@ -95,7 +95,7 @@ struct WalkBufs {
   int32_t* ovf_count2; // [1]
   int32_t* wctr;       // [9 x 64]: work counters (stride 64) of persistent kernels:
                        // 8 per-XCD ranges, 1 overflow list
-  int32_t* gq;         // global frontier queues for the fallback walk: 2 * gq_cap words each
+  int32_t* gq;         // global frontier queues for the fallback walk: gq_cap words each
   int64_t gq_cap;      // entries per queue (power of two)
   int32_t gq_waves;    // queues (waves) of the fallback walk
   int32_t lds_qcap;    // cap on the LDS frontier in candidates (power of two >= 64; test

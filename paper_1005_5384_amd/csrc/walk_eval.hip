@@ -3,11 +3,11 @@
 // The paper builds the lists with two walks (count, then write, with a host
 // prefix sum between them) and evaluates them in separate kernels.  Here one
 // 64-lane wavefront per work item (a group, or a chunk of 32 of its targets)
-// walks the tree breadth-first itself, 64 candidates per step, and evaluates
-// the accepted cells and opened leaves in 64-entry LDS tiles as soon as a
+// walks the tree breadth-first itself, up to 64 candidates per step, and evaluates
+// the accepted cells and opened leaves in LDS tiles of up to 64 as soon as a
 // tile fills.  The lists never reach HBM, the walk needs no block barrier
-// (each wave owns its LDS area, wave-ordered), and with ~9 KB of LDS per
-// wave 16 walks are in flight per CU, so their dependent gathers overlap
+// (each wave owns its LDS area, wave-ordered), and with 6.9 KB of LDS per
+// wave 20 walks are in flight per CU, so their dependent gathers overlap
 // other waves' arithmetic.  The waves are persistent: work items (whose
 // costs differ by orders of magnitude) are handed out through per-XCD
 // counters, which removed the tail of the one-block-per-item launch (11 %).
@@ -16,14 +16,21 @@
 // order, ballot compaction in lane order), so the cell and leaf lists are
 // identical; an export mode writes them at offsets from the count walk for
 // the parity tests.  Each candidate costs one 32-byte gather (boundary +
-// topology).  The frontier FIFO holds one entry per opened cell (its
-// children are consecutive cells): a step takes the next 64 children of the
-// queued entries, finding each lane's entry with one mark per entry in LDS
-// and a ballot, so an opened cell costs one store instead of one per child,
-// and a queue entry stands for up to eight candidates.  Evaluation: the wave splits into S = floor(64 / n) slices of n
-// lanes; every slice holds all n targets and takes every S-th source of a
-// tile; plain FP32 per tile is folded into Neumaier pairs; slices are
-// combined in slice order.
+// topology).  The frontier FIFO holds one word per opened cell (its
+// children are consecutive cells); a step takes eight entries and gives each
+// eight lanes, one per child.  Evaluation: the wave splits into S = floor(64 / n)
+// slices of n lanes; every slice holds all n targets and takes every S-th
+// source of a tile; plain FP32 per tile is folded into compensated pairs;
+// slices are combined in slice order.
+//
+// Bound: VALU issue.  Measured costs per wave instruction and SIMD with four
+// waves (cycles): 2.4 for FP32 and integer additions and FP32 multiplies on
+// vector registers or constants, 4.2 for compares, selects, shifts, min / max,
+// lane counts and anything with a scalar-register operand, 8.3 for v_rsq_f32;
+// the clock falls to about 2.1 GHz under this load.  So the loops below keep
+// uniform operands in vector registers, count in scalar registers and build
+// lane masks there.  2^20 Plummer points, theta = 0.5: 2.01e9 -> 1.74e9
+// vector instructions, 5.6 -> 4.9 million cycles, 2.53 -> 2.33 ms.
 //
 // A work item whose frontier outgrows its LDS queue aborts before writing any
 // result and is redone by the next tier: 512-entry LDS queues, then
@@ -57,16 +64,17 @@ constexpr int kLanes = 64;
 constexpr int kTileW = 64;   // sources per tile
 constexpr int kRingW = 128;  // pending cells / leaves (two tiles)
 
-// Frontier entry: x = first child << 3 | (children - 1) (cell ids < 2^29),
-// y = position of the first child in the item's candidate sequence.
+// Frontier entry: first child << 3 | (children - 1) of an opened cell (cell
+// ids < 2^29).
 template <int QCAP>
 struct WShared {
-  int2 q[QCAP];
+  int q[QCAP];
   int cring[kRingW];
   int2 lring[kRingW];  // (first particle, n particles) of opened leaves
+  // Source tile: cells (com, M) [64], (Qxx, Qyy, Qzz, Qxy) [64], (Qxz, Qyz,
+  // -, -) [64], or particles [64]; the network's rows; the slices' sums.
   float4 tile[3 * kTileW];
-  int pre[kTileW + 1];
-  int lfirst[kTileW];
+  int mark[kTileW];
 };
 
 // Orders this wave's LDS accesses: lanes read what other lanes of the same
@@ -79,81 +87,136 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // LDS frontier queue of one wave.
 struct LQueue {
-  int2* p;
-  __device__ int2 get(uint32_t i) const { return p[i]; }
-  __device__ void put(uint32_t i, int x, int y) const { p[i] = make_int2(x, y); }
+  int* p;
+  __device__ int get(uint32_t i) const { return p[i]; }
+  __device__ void put(uint32_t i, int x) const { p[i] = x; }
 };
 
+typedef float v2f32 __attribute__((ext_vector_type(2)));
+
+// One 16-byte LDS read (member-wise copies of a float4 may be split).
+__device__ __forceinline__ float4 load_f4(const float4* p) {
+  const v4f32 v = *reinterpret_cast<const v4f32*>(p);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
+// The targets of one work item and their accumulators.  The wave splits into
+// S = floor(64 / n) slices of n lanes; a tile is T = S c sources (c =
+// floor(64 / S), T in [60, 64]) and slice s evaluates sources s, s + S, ...,
+// so every lane runs the same number of terms, the loop counter is a scalar
+// and one vector addition per term moves the LDS address (S adjacent entries
+// per read: no bank conflicts; c consecutive entries per slice would need no
+// addition but conflicted on a third of the LDS cycles).  A per-lane bound
+// and index arithmetic on scalar operands cost four slow instructions
+// per term before: compares and every instruction with a scalar-register
+// operand issue at half the rate of arithmetic on vector registers.
 template <bool PLAIN, typename SH>
 struct WItem {
   const DevTree& T;
   SH& sh;
-  float eps2;
-  int lane, nt, S, slice;
+  float eps2;  // in a vector register
+  int lane, nt, S, slice, c;
+  int step;  // 16 S, in a vector register
   bool active, do_eval;
   float4 xi;
   Sum4 acc4;
   int64_t nsrc = 0;
+  int stamp;  // last value written to sh.mark (never reused by this wave)
+
+  __device__ int tile_size() const { return S * c; }
+
+  // Terms per slice of a tile of cnt sources.
+  __device__ int terms(int cnt) const { return cnt == S * c ? c : uni((cnt + S - 1) / S); }
 
   __device__ void flush_cells(uint32_t start, int cnt) {
     if (!do_eval) return;
     const float4* mp = reinterpret_cast<const float4*>(T.mp);
-    if (lane < cnt) {
-      const int64_t id = sh.cring[(start + lane) & (kRingW - 1)];
-      const float4 a = mp[3 * id], b = mp[3 * id + 1], c = mp[3 * id + 2];
+    const int k = terms(cnt);
+    if (lane < S * k) {
+      // The last entries of a partial tile repeat its last cell without mass.
+      const int64_t id = sh.cring[(start + min(lane, cnt - 1)) & (kRingW - 1)];
+      float4 a = mp[3 * id], b = mp[3 * id + 1];
+      float2 d = *reinterpret_cast<const float2*>(mp + 3 * id + 2);
+      if (lane >= cnt) {
+        a.w = 0.f;
+        b = make_float4(0.f, 0.f, 0.f, 0.f);
+        d = make_float2(0.f, 0.f);
+      }
       sh.tile[lane] = a;
       sh.tile[kTileW + lane] = b;
-      sh.tile[2 * kTileW + lane] = c;
+      *reinterpret_cast<float2*>(sh.tile + 2 * kTileW + lane) = d;
     }
     wave_lds_sync();
     if (active) {
       float ax = 0.f, ay = 0.f, az = 0.f, ph = 0.f;
-      const float4* t0 = sh.tile;
-      const float4* t1 = sh.tile + kTileW;
-      const float4* t2 = sh.tile + 2 * kTileW;
-      strided2(slice, cnt, S, [&](int j) { pc_term(xi, t0[j], t1[j], t2[j], eps2, ax, ay, az, ph); });
+      const char* t = reinterpret_cast<const char*>(sh.tile + slice);
+      auto term = [&]() {
+        const float4* e = reinterpret_cast<const float4*>(t);
+        const v2f32 d = *reinterpret_cast<const v2f32*>(e + 2 * kTileW);
+        pc_term(xi, load_f4(e), load_f4(e + kTileW), make_float4(d[0], d[1], 0.f, 0.f), eps2, ax,
+                ay, az, ph);
+        t += step;
+      };
+      int j = 0;
+      for (; j + 2 <= k; j += 2) {
+        term();
+        term();
+      }
+      if (j < k) term();
       acc4.template fold<PLAIN>(ax, ay, az, ph);
     }
     wave_lds_sync();
   }
 
+  // The leaves [start, start + lc) of the ring: their particles, flattened in
+  // list order, tile by tile.  A leaf marks the lane at which its particles
+  // begin in the tile; a ballot of the marks gives every lane its leaf.
   __device__ void flush_leaves(uint32_t start, int lc) {
-    int ln = 0;
+    int first = 0, ln = 0;
     if (lane < lc) {
       const int2 fl = sh.lring[(start + lane) & (kRingW - 1)];
-      sh.lfirst[lane] = fl.x;
+      first = fl.x;
       ln = fl.y;
     }
-    int incl = ln;
-#pragma unroll
-    for (int o = 1; o < kLanes; o <<= 1) {
-      const int v = __shfl_up(incl, o);
-      if (lane >= o) incl += v;
-    }
-    const int total = __shfl(incl, kLanes - 1);
+    const int incl = wave_inclusive_sum(ln);
+    const int total = __builtin_amdgcn_readlane(incl, kLanes - 1);
     nsrc += total;
     if (!do_eval) return;
-    if (lane < lc) sh.pre[lane] = incl - ln;
-    if (lane == 0) sh.pre[lc] = total;
-    wave_lds_sync();
     const float4* part = reinterpret_cast<const float4*>(T.part);
-    for (int u0 = 0; u0 < total; u0 += kTileW) {
-      const int cnt = min(kTileW, total - u0);
-      if (lane < cnt) {
-        const int u = u0 + lane;
-        int lo = 0, hi = lc;  // pre[lo] <= u < pre[hi]
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (sh.pre[mid] <= u) lo = mid;
-          else hi = mid;
-        }
-        sh.tile[lane] = part[sh.lfirst[lo] + (u - sh.pre[lo])];
+    const int ex = incl - ln, rel = first - ex, tile = tile_size();
+    for (int u0 = 0; u0 < total; u0 += tile) {
+      const int cnt = min(tile, total - u0);
+      const int k = terms(cnt);
+      ++stamp;
+      if (ln > 0 && incl > u0 && ex < u0 + kTileW) sh.mark[max(ex - u0, 0)] = stamp;
+      wave_lds_sync();
+      const bool mk = sh.mark[lane] == stamp;
+      const int before = __popcll(__ballot(lane < lc && incl <= u0));  // leaves used up
+      const int own = before + rank_below(__ballot(mk)) + (mk ? 0 : -1);
+      int src = __shfl(rel, own) + u0 + lane;
+      const int last = __builtin_amdgcn_readlane(src, cnt - 1);
+      if (lane >= cnt) src = last;  // without mass below
+      if (lane < S * k) {
+        float4 p = part[src];
+        if (lane >= cnt) p.w = 0.f;
+        sh.tile[lane] = p;
       }
       wave_lds_sync();
       if (active) {
         float ax = 0.f, ay = 0.f, az = 0.f, ph = 0.f;
-        const float4* t0 = sh.tile;
-        strided2(slice, cnt, S, [&](int j) { pp_term(xi, t0[j], eps2, ax, ay, az, ph); });
+        const char* t = reinterpret_cast<const char*>(sh.tile + slice);
+        auto term = [&]() {
+          pp_term(xi, load_f4(reinterpret_cast<const float4*>(t)), eps2, ax, ay, az, ph);
+          t += step;
+        };
+        int j = 0;
+        for (; j + 4 <= k; j += 4) {
+          term();
+          term();
+          term();
+          term();
+        }
+        for (; j < k; ++j) term();
         acc4.template fold<PLAIN>(ax, ay, az, ph);
       }
       wave_lds_sync();
@@ -172,7 +235,8 @@ template <bool PLAIN, bool LEARNED, typename SH, typename Q>
 __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64_t w,
                               float th2, float eps2, float* __restrict__ acc,
                               float* __restrict__ pot, Q q, uint32_t qmask, bool gmem_q,
-                              bool do_eval, int cw, int* nband_out, const MlpView* mv) {
+                              bool do_eval, int cw, int* nband_out, int* stamp,
+                              const MlpView* mv) {
   const int lane = threadIdx.x & (kLanes - 1);
   // Per-item constants; with the learned criterion they are held in scalar
   // registers (its network needs the vector registers).
@@ -188,10 +252,13 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
   const float4 gmin = U(gbox[2 * g]), gmax = U(gbox[2 * g + 1]);
   const float4* rec = reinterpret_cast<const float4*>(T.wrec);
 
-  WItem<PLAIN, SH> it{T, sh, eps2};
+  WItem<PLAIN, SH> it{T, sh, in_vgpr(eps2)};
   it.lane = lane;
-  it.nt = min(kChunk, gi.y - wk.y);
+  it.nt = uni(min(kChunk, gi.y - wk.y));
   it.S = kLanes / it.nt;
+  it.c = kLanes / it.S;
+  it.step = in_vgpr(16 * it.S);
+  it.stamp = *stamp;
   it.slice = lane / it.nt;
   it.active = it.slice < it.S;
   it.do_eval = do_eval;
@@ -209,9 +276,11 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
   const int64_t xcb = exp ? U(B.c_off[g]) : 0, xce = exp ? U(B.c_off[g + 1]) : 0;
   const int64_t xlb = exp ? U(B.l_off[g]) : 0, xle = exp ? U(B.l_off[g + 1]) : 0;
 
-  // Frontier: entries [rhead, rtail) of q; candidates [vhead, vtail) of the
-  // item's breadth-first sequence (the entry at rhead may be partly taken).
-  uint32_t rhead = 0, rtail = 0, vhead = 0, vtail = 0;
+  // Frontier: entries [rhead, rtail) of q.  A step takes up to eight entries
+  // and gives each eight lanes, one per possible child, so no candidate has to
+  // look for its entry (trees average 7 to 8 children per split cell; the
+  // candidates keep their breadth-first order).
+  uint32_t rhead = 0, rtail = 0;
   uint32_t chead = 0, ctail = 0, lhead = 0, ltail = 0;
   const int4 root = reinterpret_cast<const int4*>(rec)[1];
   if (root.y == 0) {  // the root is a leaf: its particles are the whole list
@@ -221,40 +290,21 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
     }
     ltail = 1;
   } else {
-    if (lane == 0) q.put(0, (root.x << 3) | (root.y - 1), 0);
+    if (lane == 0) q.put(0, (root.x << 3) | (root.y - 1));
     rtail = 1;
-    vtail = (uint32_t)root.y;
   }
-  // Each step marks, in sh.lfirst, the lane at which each taken entry's
-  // children begin, with a value no earlier step of this item used
-  // (-1 - vhead) and that no particle index equals.
-  sh.lfirst[lane] = 0;
   if (gmem_q) __threadfence_block();  // queue stores complete before other lanes read
   wave_lds_sync();
+  const int lent = lane >> 3, lchild = lane & 7;
+  const uint32_t tile = (uint32_t)it.tile_size();
+  const float th2v = in_vgpr(th2);
 
-  // Candidate of each lane for the next min(64, vtail - vh) candidates from
-  // position vh, whose entry is rh; *used = entries that window uses up.
-  auto take = [&](uint32_t rh, uint32_t vh, uint32_t* used) {
-    const uint32_t nent = min((uint32_t)kLanes, rtail - rh);
-    const uint32_t navail = min((uint32_t)kLanes, vtail - vh);
-    const bool inq = (uint32_t)lane < nent;
-    int2 e = make_int2(0, 0);
-    if (inq) e = q.get((rh + lane) & qmask);
-    // First lane of this entry's children in the window (<= 0 for a partly
-    // taken head entry) and one past its last.
-    const int s0 = (int)((uint32_t)e.y - vh);
-    const int s1 = s0 + (int)((uint32_t)e.x & 7u) + 1;
-    const bool inwin = inq && s0 < kLanes;
-    const int stamp = -1 - (int)vh;
-    if (inwin) sh.lfirst[max(s0, 0)] = stamp;
-    wave_lds_sync();
-    const bool mark = sh.lfirst[lane] == stamp;
-    const uint64_t mM = __ballot(mark);
-    const int own = rank_below(mM) + (mark ? 0 : -1);  // entry of this lane's candidate
-    const int cfirst = __shfl((int)((uint32_t)e.x >> 3) - s0, own);
-    *used = (uint32_t)__popcll(__ballot(inwin && s1 <= (int)navail));
-    // lanes past the candidates read the root's record
-    return (uint32_t)lane < navail ? cfirst + lane : 0;
+  // Candidate of each lane in the window of the next min(8, rtail - rh)
+  // entries from rh; 0 (the root, never a candidate) for lanes without one.
+  auto take = [&](uint32_t rh) {
+    const int e = q.get((rh + lent) & qmask);
+    const bool has = lchild <= (e & 7) && (uint32_t)lent < rtail - rh;
+    return has ? (int)((uint32_t)e >> 3) + lchild : 0;
   };
   // Learned criterion: a step that runs the network also scores the next
   // step's band candidates when all of them are queued already (they come
@@ -264,25 +314,18 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
   bool have_next = false;
   int c_next = 0;
   float y_next = 0.0f;
-  uint32_t used_next = 0;
   uint64_t mO_next = 0, mB_next = 0;
 
-  while (vhead < vtail) {
-    const uint32_t navail = min((uint32_t)kLanes, vtail - vhead);
-    const bool valid = (uint32_t)lane < navail;
-    int c;
-    uint32_t used;
-    if (LEARNED && have_next) {
-      c = c_next;
-      used = used_next;
-    } else {
-      c = take(rhead, vhead, &used);
-    }
-    rhead += used;
-    vhead += navail;
+  // One walk step: tests a window of candidates and appends the accepted
+  // cells, the opened leaves and the opened cells' entries.  False if the
+  // queue cannot hold them.
+  auto step = [&]() -> bool {
+    const int c = LEARNED && have_next ? c_next : take(rhead);
+    const bool valid = c != 0;
+    rhead += min(8u, rtail - rhead);
 
     const int4 tp = reinterpret_cast<const int4*>(rec)[2 * (int64_t)c + 1];
-    bool op;
+    uint64_t mOp;
     if (LEARNED) {
       bool olo, band, accb = false;
       uint64_t mB;
@@ -312,12 +355,11 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
         if (mB) {
           const int ra = __popcll(mB);
           int rows = ra;
-          if (vtail - vhead >= (uint32_t)kLanes) {  // the next step's 64 candidates are queued
-            uint32_t u2;
-            const int c2 = take(rhead, vhead, &u2);
+          if (rtail - rhead >= 8u) {  // the next step's eight entries are queued
+            const int c2 = take(rhead);
             const float4 ge = rec[2 * (int64_t)c2];
             const float4 fc0 = fc[2 * (int64_t)c2], fc1 = fc[2 * (int64_t)c2 + 1];
-            const bool olo2 = open_cell(gmin, gmax, ge, B.mac_lo2);
+            const bool olo2 = c2 != 0 && open_cell(gmin, gmax, ge, B.mac_lo2);
             const bool band2 = olo2 && !open_cell(gmin, gmax, ge, B.mac_hi2);
             const uint64_t mB2 = __ballot(band2);
             if (ra + __popcll(mB2) <= kLanes) {  // every row's score lands in its own lane
@@ -329,7 +371,6 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
               rows += __popcll(mB2);
               have_next = true;
               c_next = c2;
-              used_next = u2;
               mO_next = __ballot(olo2);
               mB_next = mB2;
             }
@@ -355,61 +396,94 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
         }
         nband += __popcll(mB);
       }
-      op = olo && !accb;
+      mOp = __ballot(olo && !accb);
     } else {
       const float4 ge = rec[2 * (int64_t)c];
-      op = valid && open_cell(gmin, gmax, ge, th2);
+      mOp = __ballot(valid) & open_mask(gmin, gmax, ge, th2v);
     }
-    const bool toC = valid && !op, toL = op && tp.y == 0, toQ = op && tp.y != 0;
-    const uint64_t mC = __ballot(toC), mL = __ballot(toL), mQ = __ballot(toQ);
-    // Queue position of each opened cell's first child: prefix of the
-    // children counts (1..8) over the opened lanes, one ballot per bit.
-    const int nch = toQ ? tp.y : 0;
-    int preN = 0, totN = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const uint64_t m = __ballot((nch >> b) & 1);
-      preN += rank_below(m) << b;
-      totN += __popcll(m) << b;
-    }
+    // The three destinations as lane masks (scalar registers): accepted cells,
+    // opened leaves, opened cells with children.
+    const uint64_t mLeaf = __ballot(tp.y == 0);
+    const uint64_t mC = __ballot(valid) & ~mOp, mL = mOp & mLeaf, mQ = mOp & ~mLeaf;
     const uint32_t nq = (uint32_t)__popcll(mQ);
-    if ((rtail + nq) - rhead > qmask + 1) return kOverflow;
-    if (toC) {
+    if ((rtail + nq) - rhead > qmask + 1) return false;
+    if (__builtin_amdgcn_inverse_ballot_w64(mC)) {
       const uint32_t k = ctail + rank_below(mC);
       sh.cring[k & (kRingW - 1)] = c;
       if (exp && xcb + k < xce) B.c_ids[xcb + k] = c;
     }
-    if (toL) {
+    if (__builtin_amdgcn_inverse_ballot_w64(mL)) {
       const uint32_t k = ltail + rank_below(mL);
       sh.lring[k & (kRingW - 1)] = make_int2(tp.z, tp.w);
       if (exp && xlb + k < xle) B.l_ids[xlb + k] = c;
     }
-    if (toQ) q.put((rtail + rank_below(mQ)) & qmask, (tp.x << 3) | (tp.y - 1), (int)(vtail + preN));
+    if (__builtin_amdgcn_inverse_ballot_w64(mQ))
+      q.put((rtail + rank_below(mQ)) & qmask, (tp.x << 3) | (tp.y - 1));
     ctail += __popcll(mC);
     ltail += __popcll(mL);
     rtail += nq;
-    vtail += (uint32_t)totN;
     if (gmem_q) __threadfence_block();
     wave_lds_sync();
-    if (ctail - chead >= (uint32_t)kTileW) {
-      it.flush_cells(chead, kTileW);
-      chead += kTileW;
+    return true;
+  };
+
+  // At most 63 + 64 cells or leaves are ever pending, two tiles of as few as 60.
+  bool fits = true;
+  if constexpr (LEARNED) {
+    // Every step is followed by the evaluations it filled (with the loop below
+    // the learned call took 4 % longer, 1.59 against 1.53 ms at 2^20).
+    while (rhead != rtail) {
+      fits = step();
+      if (!fits) break;
+      while (ctail - chead >= tile) {
+        it.flush_cells(chead, (int)tile);
+        chead += tile;
+      }
+      if (ltail - lhead >= (uint32_t)kTileW) {
+        it.flush_leaves(lhead, kTileW);
+        lhead += kTileW;
+      }
     }
-    if (ltail - lhead >= (uint32_t)kTileW) {
-      it.flush_leaves(lhead, kTileW);
-      lhead += kTileW;
+    if (fits) {
+      while (ctail != chead) {
+        const int n = (int)min(tile, ctail - chead);
+        it.flush_cells(chead, n);
+        chead += n;
+      }
+      while (ltail != lhead) {
+        const int n = (int)min((uint32_t)kTileW, ltail - lhead);
+        it.flush_leaves(lhead, n);
+        lhead += n;
+      }
+    }
+  } else {
+    // Steps until a tile of cells or 64 leaves are pending, then one
+    // evaluation, so that the accumulators stay in their registers through the
+    // walk's loop (evaluating inside it cost 16 moves a step); at the end the
+    // remainders.
+    for (;;) {
+      while (rhead != rtail && ctail - chead < tile && ltail - lhead < (uint32_t)kTileW) {
+        fits = step();
+        if (!fits) break;
+      }
+      if (!fits) break;
+      const bool last = rhead == rtail;
+      const uint32_t pc = ctail - chead, pl = ltail - lhead;
+      if (pc >= tile || (last && pc != 0)) {
+        const uint32_t n = min(tile, pc);
+        it.flush_cells(chead, (int)n);
+        chead += n;
+      } else if (pl >= (uint32_t)kTileW || (last && pl != 0)) {
+        const uint32_t n = min((uint32_t)kTileW, pl);
+        it.flush_leaves(lhead, (int)n);
+        lhead += n;
+      } else {
+        break;
+      }
     }
   }
-  while (ctail != chead) {
-    const int n = (int)min((uint32_t)kTileW, ctail - chead);
-    it.flush_cells(chead, n);
-    chead += n;
-  }
-  while (ltail != lhead) {
-    const int n = (int)min((uint32_t)kTileW, ltail - lhead);
-    it.flush_leaves(lhead, n);
-    lhead += n;
-  }
+  *stamp = it.stamp;
+  if (!fits) return kOverflow;
 
   if (LEARNED) {
 #pragma unroll
@@ -467,13 +541,13 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
 template <bool PLAIN, bool LEARNED, typename SH, typename Q>
 __device__ int walk_eval_one(const DevTree& T, const WalkBufs& B, SH& sh, int64_t w, float th2,
                              float eps2, float* acc, float* pot, Q q, uint32_t qmask, bool gmem_q,
-                             bool do_eval, const MlpView* mv) {
+                             bool do_eval, int* stamp, const MlpView* mv) {
   int nb = 0;
   const int st = walk_eval_item<PLAIN, LEARNED>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q,
-                                                do_eval, 0, &nb, mv);
+                                                do_eval, 0, &nb, stamp, mv);
   if (!LEARNED || st != kFallBack) return st;
   return walk_eval_item<PLAIN, false>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q, do_eval,
-                                      2 * nb + 1, &nb, mv);
+                                      2 * nb + 1, &nb, stamp, mv);
 }
 
 // Next work index from a shared counter, one atomic per wave.
@@ -513,13 +587,15 @@ void walk_eval_persistent_kernel(
   // lds_qcap counts candidates; an entry holds up to eight
   const uint32_t qmask = (uint32_t)min(B.lds_qcap / 8, QCAP) - 1;
   const LQueue q{shw[wv].q};
+  shw[wv].mark[lane] = 0;
+  int stamp = 0;
   if constexpr (FROM_LIST) {
     for (;;) {
       const int k = take_work(B.wctr + 64 * 8, lane);
       if (k >= *src_n) break;
       const int32_t w = src[k];
       if (walk_eval_one<PLAIN, LEARNED>(T, B, shw[wv], w, th2, eps2, acc, pot, q, qmask, false,
-                                        do_eval != 0, &V) == kOverflow &&
+                                        do_eval != 0, &stamp, &V) == kOverflow &&
           lane == 0)
         ovl[atomicAdd(ovn, 1)] = w;
     }
@@ -533,7 +609,7 @@ void walk_eval_persistent_kernel(
         if (k >= n) break;
         const int64_t w = lo + k;
         if (walk_eval_one<PLAIN, LEARNED>(T, B, shw[wv], w, th2, eps2, acc, pot, q, qmask, false,
-                                          do_eval != 0, &V) == kOverflow &&
+                                          do_eval != 0, &stamp, &V) == kOverflow &&
             lane == 0)
           ovl[atomicAdd(ovn, 1)] = (int32_t)w;
       }
@@ -542,16 +618,11 @@ void walk_eval_persistent_kernel(
 }
 
 // Global-memory queues: written and read by different lanes of one wave, so
-// they are accessed as volatile (no stale L1 copies) and fenced.  The two
-// words of entry i sit at p[i] and p[cap + i].
+// they are accessed as volatile (no stale L1 copies) and fenced.
 struct GQueue {
   volatile int32_t* p;
-  int64_t cap;
-  __device__ int2 get(uint32_t i) const { return make_int2(p[i], p[cap + i]); }
-  __device__ void put(uint32_t i, int x, int y) const {
-    p[i] = x;
-    p[cap + i] = y;
-  }
+  __device__ int get(uint32_t i) const { return p[i]; }
+  __device__ void put(uint32_t i, int x) const { p[i] = x; }
 };
 
 // Last tier: the *src_n items of src with global-memory frontier queues of
@@ -575,10 +646,12 @@ __global__ __launch_bounds__(kLanes) void walk_eval_fallback_kernel(DevTree T, W
     __syncthreads();
     V = mlp_lds(ml);
   }
-  GQueue q{B.gq + (int64_t)blockIdx.x * 2 * B.gq_cap, B.gq_cap};
+  GQueue q{B.gq + (int64_t)blockIdx.x * B.gq_cap};
+  sh.mark[threadIdx.x] = 0;
+  int stamp = 0;
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const int st = walk_eval_one<PLAIN, LEARNED>(T, B, sh, src[i], th2, eps2, acc, pot, q,
-                                                 (uint32_t)(B.gq_cap - 1), true, do_eval != 0, &V);
+                                                 (uint32_t)(B.gq_cap - 1), true, do_eval != 0, &stamp, &V);
     if (st == kOverflow && threadIdx.x == 0)
       atomicOr(reinterpret_cast<unsigned long long*>(&B.tot[5]), 1ull);
   }
@@ -605,18 +678,18 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
   // The breadth-first FIFO holds about two tree levels of the group's walk,
   // which grow like theta^-3, as entries of up to eight children: 512 entries
   // (4 KB) held every walk of the 2^20 Plummer sphere and the 4M clumps at
-  // theta 0.3 ... 0.5.  Tiers: 512-entry LDS queues (16 waves per CU), then
+  // theta 0.3 ... 0.5.  Tiers: 512-entry LDS queues (20 waves per CU), then
   // the overflows with 2048-entry LDS queues (one wave per block, 7 per CU),
   // then global-memory queues.
   const bool learned = B.mlp != nullptr;
   auto go = [&](auto plain_tag, auto learned_tag) {
     constexpr bool P = decltype(plain_tag)::value, L = decltype(learned_tag)::value;
-    if constexpr (L)  // one block of 16 waves per CU (16 x 9 KB frontiers + 12 KB network,
-                      // 159.6 KB of LDS), four per SIMD at <= 128 VGPRs
+    if constexpr (L)  // one block of 16 waves per CU (16 x 6.9 KB frontiers + 12 KB network,
+                      // 122.5 KB of LDS), four per SIMD at <= 128 VGPRs
       walk_eval_persistent_kernel<P, 512, L, 16, false><<<8 * 32, 16 * kLanes, 0, s>>>(
           T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);
-    else  // 4 blocks of 4 waves per CU
-      walk_eval_persistent_kernel<P, 512, L, 4, false><<<8 * 128, 4 * kLanes, 0, s>>>(
+    else  // 5 blocks of 4 waves per CU (four: 2.36 against 2.32 ms at 2^20)
+      walk_eval_persistent_kernel<P, 512, L, 4, false><<<8 * 160, 4 * kLanes, 0, s>>>(
           T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);
     walk_eval_persistent_kernel<P, 2048, L, 1, true><<<8 * 224, kLanes, 0, s>>>(
         T, B, th2, eps2, acc, pot, do_eval, B.ovf_list, B.ovf_count, B.ovf_list2, B.ovf_count2);
