@@ -59,6 +59,18 @@ int lds_queue_entries() {
   return q;
 }
 
+// The counters of a walk in one block of kCtlBytes: totals, work counters,
+// overflow counts and the ticket, each on its own cache line.
+constexpr size_t kCtlBytes = 9 * 256 + 4 * 256;
+void set_ctl(WalkBufs& b, void* base) {
+  unsigned char* p = (unsigned char*)base;
+  b.wctr = (int32_t*)p;
+  b.tot = (int64_t*)(p + 9 * 256);
+  b.ovf_count = (int32_t*)(p + 10 * 256);
+  b.ovf_count2 = (int32_t*)(p + 11 * 256);
+  b.ticket = (int32_t*)(p + 12 * 256);
+}
+
 }  // namespace
 
 // Network of the learned criterion: FP32 master parameters, Adam moments,
@@ -132,9 +144,16 @@ struct octgrav_tree : DevAlloc {
   std::unique_ptr<BuildPools> build_pools;
 
   int64_t* tot_host = nullptr;  // page-locked copy of the totals (read after every call)
+  int64_t* tot_host_dev = nullptr;  // its device address (finish_kernel writes it)
+  // The walk's counters (totals, work counters, overflow counts, ticket): one
+  // allocation for the handle's life, outside the pools, so that counters which
+  // the last call left reset (ctl_clean) stay so when the tree is rebuilt.
+  void* ctl = nullptr;
+  bool ctl_clean = false;
 
   ~octgrav_tree() {
     if (tot_host) hipHostFree(tot_host);
+    if (ctl) hipFree(ctl);
     for (void* p : allocs) hipFree(p);
     for (hipEvent_t e : ev)
       if (e) hipEventDestroy(e);
@@ -335,24 +354,32 @@ struct octgrav_tree : DevAlloc {
     wb.c_off = (int64_t*)p;
     if ((rc = dalloc(&p, (size_t)(ng + 1) * 8))) return rc;
     wb.l_off = (int64_t*)p;
-    if ((rc = dalloc(&p, 8 * 8))) return rc;
-    wb.tot = (int64_t*)p;
-    if (!tot_host && hipHostMalloc((void**)&tot_host, 8 * 8) != hipSuccess) {
-      (void)hipGetLastError();  // read_tot then copies into pageable memory
-      tot_host = nullptr;
+    if (!ctl) {
+      if (alloc_fault() || hipMalloc(&ctl, kCtlBytes) != hipSuccess) {
+        (void)hipGetLastError();
+        ctl = nullptr;
+        return fail(OCTGRAV_ENOMEM, "device allocation failed");
+      }
+      ctl_clean = false;
+    }
+    set_ctl(wb, ctl);
+    if (!tot_host) {
+      if (hipHostMalloc((void**)&tot_host, kFinishHost * 8) != hipSuccess) {
+        (void)hipGetLastError();  // read_tot then copies into pageable memory
+        tot_host = nullptr;
+      } else if (hipHostGetDevicePointer((void**)&tot_host_dev, tot_host, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        tot_host_dev = nullptr;
+      }
     }
     if ((rc = dalloc(&p, (size_t)scan_scratch_entries(ng) * 8))) return rc;
     wb.blk = (int64_t*)p;
     if ((rc = dalloc(&p, (size_t)std::max(ng, nw) * 4))) return rc;
     wb.ovf_list = (int32_t*)p;
-    if ((rc = dalloc(&p, 4))) return rc;
-    wb.ovf_count = (int32_t*)p;
     if ((rc = dalloc(&p, (size_t)std::max(ng, nw) * 4))) return rc;
     wb.ovf_list2 = (int32_t*)p;
-    if ((rc = dalloc(&p, 4))) return rc;
-    wb.ovf_count2 = (int32_t*)p;
-    if ((rc = dalloc(&p, 9 * 64 * 4))) return rc;
-    wb.wctr = (int32_t*)p;
+    if ((rc = dalloc(&p, (size_t)nw * 32))) return rc;
+    wb.dpart = (double*)p;
     // Fallback frontier queues: a breadth-first FIFO never holds more than
     // two consecutive levels, hence at most twice the widest level.
     int64_t cap = 64;
@@ -618,12 +645,51 @@ static Path choose_path(uint32_t flags) {
   return Path::FusedWave;
 }
 
-static int launch_fused(const octgrav_tree* t, Path p, float theta, float eps, bool plain,
+static int launch_fused(octgrav_tree* t, Path p, float theta, float eps, bool plain,
                         bool do_eval, float* acc, float* pot) {
+  t->ctl_clean = false;
   int rc = p == Path::FusedWave
                ? launch_walk_eval(t->dt, t->wb, theta, eps, plain, do_eval, acc, pot, t->stream)
                : launch_walk_eval_block(t->dt, t->wb, theta, eps, plain, do_eval, acc, pot, t->stream);
   return rc ? rc : launch_totals(t->dt, t->wb, t->stream);
+}
+
+// One call of the fused wave path with the scratch of b, and its totals in
+// tot8: the first tier and the finishing kernel, whose totals come back through
+// page-locked memory.  The later tiers run only when that reports items left
+// over (no work item of the benchmark sets, from theta 0.3 up), followed by the
+// finishing kernel again; without page-locked memory they always run.
+// *clean: the counters of b are reset.  Events (timed): ev[4] after the
+// evaluation, ev[5] at the end.
+static int fused_wave_forces(octgrav_tree* t, const WalkBufs& b, double* scratch, bool* clean,
+                             float theta, float eps, bool plain, float* acc, float* pot, bool timed,
+                             int64_t* tot8) {
+  int64_t* host = t->tot_host_dev;
+  int parts = (*clean ? 0 : kWalkInit) | kWalkFirst | (host ? 0 : kWalkRest);
+  *clean = false;
+  for (;;) {
+    if (launch_walk_eval(t->dt, b, theta, eps, plain, true, acc, pot, t->stream, parts))
+      return fail(OCTGRAV_EHIP, "walk+evaluation launch failed");
+    if (timed) hipEventRecord(t->ev[4], t->stream);
+    const bool last = parts & kWalkRest;
+    if (launch_finish(t->dt, b, scratch, t->d_diag, host, last, t->stream))
+      return fail(OCTGRAV_EHIP, "finish launch failed");
+    if (timed) hipEventRecord(t->ev[5], t->stream);
+    if (!host) {
+      if (hipMemcpyAsync(tot8, b.tot, 8 * 8, hipMemcpyDeviceToHost, t->stream) != hipSuccess)
+        return fail(OCTGRAV_EHIP, "totals copy failed");
+    }
+    if (hipStreamSynchronize(t->stream) != hipSuccess)
+      return fail(OCTGRAV_EHIP, std::string("device error: ") + hipGetErrorString(hipGetLastError()));
+    if (host) std::memcpy(tot8, t->tot_host, 8 * 8);
+    if (debug_trace())
+      std::fprintf(stderr, "octgrav: fused wave, items %lld, left to the later tiers %lld%s\n",
+                   (long long)t->dt.nw, host ? (long long)t->tot_host[8] : -1ll, last ? " (run)" : "");
+    if (last || t->tot_host[8] == 0) break;
+    parts = kWalkRest;
+  }
+  *clean = true;
+  return OCTGRAV_OK;
 }
 
 // While alive, the handle's walks read the offset test's records at theta
@@ -695,6 +761,15 @@ int octgrav_forces_ex(octgrav_tree* t, float theta, float eps, float* acc, float
       if (timed) {
         for (int k = 0; k < 4; ++k) hipEventRecord(t->ev[k], t->stream);
       }
+      if (path == Path::FusedWave) {
+        t->wb.export_lists = 0;
+        if (int rc = fused_wave_forces(t, t->wb, t->d_diag_part, &t->ctl_clean, theta, eps, plain,
+                                       acc, pot, timed, tot))
+          return rc;
+        if (tot[5]) return fail(OCTGRAV_ECAPACITY, "fallback walk frontier overflow");
+        break;
+      }
+      t->ctl_clean = false;
       if (path != Path::TwoPass) {
         // Fused walk + evaluation: no lists in memory, no host round trip.
         t->wb.export_lists = 0;
@@ -795,10 +870,7 @@ int octgrav_forces_noalloc(octgrav_tree* t, float theta, float eps, float* acc, 
       return (unsigned char*)base + at;
     };
     WalkBufs b = t->wb;
-    b.tot = (int64_t*)take(8 * 8);
-    b.wctr = (int32_t*)take(9 * 64 * 4);
-    b.ovf_count = (int32_t*)take(4);
-    b.ovf_count2 = (int32_t*)take(4);
+    set_ctl(b, take(kCtlBytes));
     b.c_off = (int64_t*)take(8);  // only [0] is written without list export
     b.l_off = (int64_t*)take(8);
     b.cnt = (int32_t*)take((size_t)ng * 16);
@@ -806,6 +878,9 @@ int octgrav_forces_noalloc(octgrav_tree* t, float theta, float eps, float* acc, 
     b.ovf_list2 = (int32_t*)take((size_t)std::max(ng, nw) * 4);
     double* part = (double*)take((size_t)diag_scratch_entries(t->h.n) * 8);
     const size_t limit = noalloc_limit(), qbytes = (size_t)t->wb.gq_cap * 4;
+    // The per-item sums, where they fit beside one queue; else the diagnostics
+    // are summed over the particles.
+    b.dpart = off + (size_t)nw * 32 + 256 + qbytes <= limit ? (double*)take((size_t)nw * 32) : nullptr;
     if (off + qbytes > limit)
       return fail(OCTGRAV_EINVAL, "tree needs " + std::to_string(off + qbytes) +
                                       " bytes of scratch; octgrav_forces_noalloc has " +
@@ -818,18 +893,22 @@ int octgrav_forces_noalloc(octgrav_tree* t, float theta, float eps, float* acc, 
     b.tr_s = nullptr;
     t->counts_valid = false;
     t->have_diag = false;
-    const Path path = t->learned ? Path::FusedWave : choose_path(0);
-    const int rc = path == Path::FusedWave
-                       ? launch_walk_eval(t->dt, b, theta, eps, false, true, acc, pot, t->stream)
-                       : launch_walk_eval_block(t->dt, b, theta, eps, false, true, acc, pot, t->stream);
-    if (rc || launch_totals(t->dt, b, t->stream) || launch_diag(t->dt, acc, pot, part, t->d_diag, t->stream))
+    int64_t tot[8];
+    bool clean = false;  // other calls use the same array: the counters are reset each time
+    t->ctl_clean = false;  // the totals are copied into the handle's below
+    if (b.dpart) {
+      if (int rc = fused_wave_forces(t, b, part, &clean, theta, eps, false, acc, pot, false, tot)) return rc;
+      if (tot[5]) return fail(OCTGRAV_ECAPACITY, "fallback walk frontier overflow");
+    } else if (launch_walk_eval(t->dt, b, theta, eps, false, true, acc, pot, t->stream) ||
+               launch_totals(t->dt, b, t->stream) ||
+               launch_diag(t->dt, acc, pot, part, t->d_diag, t->stream)) {
       return fail(OCTGRAV_EHIP, "walk+evaluation launch failed");
+    }
     // The call's totals and per-group records become the handle's, as after
     // octgrav_forces (last_counts, mac_stats read them there).
     if (hipMemcpyAsync(t->wb.tot, b.tot, 8 * 8, hipMemcpyDeviceToDevice, t->stream) != hipSuccess ||
         hipMemcpyAsync(t->wb.cnt, b.cnt, (size_t)ng * 16, hipMemcpyDeviceToDevice, t->stream) != hipSuccess)
       return fail(OCTGRAV_EHIP, "record copy failed");
-    int64_t tot[8];
     if (int rc2 = t->read_tot(tot)) return rc2;
     if (tot[5]) return fail(OCTGRAV_ECAPACITY, "fallback walk frontier overflow");
     t->counts_valid = true;
@@ -846,6 +925,7 @@ int octgrav_forces_noalloc(octgrav_tree* t, float theta, float eps, float* acc, 
 static int lists_to_device(octgrav_tree* t, float theta, uint32_t flags, int64_t* n_c,
                            int64_t* n_l) {
   t->counts_valid = false;
+  t->ctl_clean = false;
   int64_t tot[8];
   if (t->learned && (flags & (OCTGRAV_TWO_PASS | OCTGRAV_FUSED_BLOCK)))
     return fail(OCTGRAV_EINVAL, "the learned criterion runs on the fused wave path only");
@@ -1043,6 +1123,7 @@ int octgrav_mac_collect(octgrav_tree* t, float theta_lo, float theta_hi, float e
     // Band lists of every group (count walk, offsets, write walk in band mode).
     // They replace the handle's lists: the counts of the last forces call are gone.
     t->counts_valid = false;
+    t->ctl_clean = false;
     WalkBufs saved = t->wb;
     t->wb.band = 1;
     t->wb.band_hi2 = theta_hi * theta_hi;

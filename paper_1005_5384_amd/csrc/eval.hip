@@ -262,7 +262,7 @@ int launch_eval(const DevTree& T, const WalkBufs& B, float eps, bool plain, floa
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int64_t diag_scratch_entries(int64_t) { return 4 * kDiagBlocks; }
+int64_t diag_scratch_entries(int64_t) { return 8 * kDiagBlocks; }
 
 int launch_diag(const DevTree& T, const float* acc, const float* pot, double* part_sums,
                 double* out4, void* stream) {

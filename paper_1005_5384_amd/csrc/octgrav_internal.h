@@ -95,6 +95,9 @@ struct WalkBufs {
   int32_t* ovf_count2; // [1]
   int32_t* wctr;       // [9 x 64]: work counters (stride 64) of persistent kernels:
                        // 8 per-XCD ranges, 1 overflow list
+  int32_t* ticket;     // [1]: blocks of finish_kernel that are done
+  double* dpart;       // [4 nw]: FP64 sums (m a, 1/2 m phi) of each work item's targets,
+                       // written by the fused wave kernels (NULL: not written)
   int32_t* gq;         // global frontier queues for the fallback walk: gq_cap words each
   int64_t gq_cap;      // entries per queue (power of two)
   int32_t gq_waves;    // queues (waves) of the fallback walk
@@ -135,8 +138,20 @@ int launch_scan(const DevTree& T, const WalkBufs& B, void* stream, int64_t g0 = 
 int launch_totals(const DevTree& T, const WalkBufs& B, void* stream, int64_t g0 = 0, int64_t ng = -1);
 int launch_eval(const DevTree& T, const WalkBufs& B, float eps, bool plain, float* acc,
                 float* pot, void* stream, int64_t w0 = 0, int64_t nw = -1);
+// Fused wave walk + evaluation.  parts: kWalkInit resets the counters, kWalkFirst
+// is the first tier (every work item), kWalkRest the later tiers (the items whose
+// frontier outgrew it).
+constexpr int kWalkInit = 1, kWalkFirst = 2, kWalkRest = 4, kWalkAll = 7;
 int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps, bool plain,
-                     bool do_eval, float* acc, float* pot, void* stream);
+                     bool do_eval, float* acc, float* pot, void* stream, int parts = kWalkAll);
+// After a fused wave evaluation: interaction totals (B.tot) and the FP64
+// diagnostics (diag[4]) from the per-item and per-group records, copied to
+// host (device pointer of page-locked memory, kFinishHost entries: the totals,
+// then the number of items the first tier left over; or NULL).  Unless items
+// were left over and !last, it also resets the counters as kWalkInit does.
+constexpr int kFinishHost = 9;
+int launch_finish(const DevTree& T, const WalkBufs& B, double* scratch, double* diag, int64_t* host,
+                  bool last, void* stream);
 int launch_walk_eval_block(const DevTree& T, const WalkBufs& B, float theta, float eps, bool plain,
                            bool do_eval, float* acc, float* pot, void* stream);
 // Walk records (nc x 32 B, the layout of DevTree::wrec) of the centre-of-mass
@@ -225,7 +240,7 @@ int64_t kinetic_scratch_entries();
 int launch_diag(const DevTree& T, const float* acc, const float* pot, double* part_sums,
                 double* out4, void* stream);
 int64_t scan_scratch_entries(int64_t ng);
-int64_t diag_scratch_entries(int64_t n);
+int64_t diag_scratch_entries(int64_t n);  // also of launch_finish
 
 // The file-scope device scratch array of octgrav_forces_noalloc: its size,
 // and its device address on the current device (looked up on the first call

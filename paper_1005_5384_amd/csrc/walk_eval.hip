@@ -49,6 +49,7 @@
 // candidates, same network arithmetic, same reduction order).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -223,6 +224,21 @@ struct WItem {
     }
   }
 };
+
+// Sums of the four values of lanes 0 ... 31 in a fixed order, stored by lanes 0
+// ... 3 (each step halves the values a lane carries: 12 word exchanges
+// instead of 40).
+__device__ __forceinline__ void store_item_sums(const double* d, int lane, double* out) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  double k0 = b0 ? d[2] : d[0], k1 = b0 ? d[3] : d[1];
+  k0 += __shfl_xor(b0 ? d[0] : d[2], 1);
+  k1 += __shfl_xor(b0 ? d[1] : d[3], 1);
+  double v = b1 ? k1 : k0;
+  v += __shfl_xor(b1 ? k0 : k1, 2);
+#pragma unroll
+  for (int o = 4; o < 32; o <<= 1) v += __shfl_xor(v, o);
+  if (lane < 4) out[((lane & 1) << 1) | (lane >> 1)] = v;
+}
 
 enum : int { kOverflow = 0, kDone = 1, kFallBack = 2 };
 
@@ -508,6 +524,7 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
     }
   }
   wave_lds_sync();
+  double d[4] = {0.0, 0.0, 0.0, 0.0};  // m a, 1/2 m phi of this lane's target
   if (lane < it.nt) {
     float s[4] = {0.f, 0.f, 0.f, 0.f}, cc[4] = {0.f, 0.f, 0.f, 0.f};
     for (int sl = 0; sl < it.S; ++sl) {
@@ -528,11 +545,18 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
     if (PLAIN) s[3] += self;
     else neu_add(s[3], cc[3], self);
     const int64_t o = T.perm[first + lane];
-    acc[3 * o + 0] = s[0] + cc[0];
-    acc[3 * o + 1] = s[1] + cc[1];
-    acc[3 * o + 2] = s[2] + cc[2];
-    if (pot) pot[o] = s[3] + cc[3];
+    const float a[4] = {s[0] + cc[0], s[1] + cc[1], s[2] + cc[2], s[3] + cc[3]};
+    acc[3 * o + 0] = a[0];
+    acc[3 * o + 1] = a[1];
+    acc[3 * o + 2] = a[2];
+    const double m = it.xi.w;
+    for (int k = 0; k < 3; ++k) d[k] = m * (double)a[k];
+    if (pot) {
+      pot[o] = a[3];
+      d[3] = 0.5 * m * (double)a[3];
+    }
   }
+  if (B.dpart) store_item_sums(d, lane, B.dpart + 4 * w);
   wave_lds_sync();
   return kDone;
 }
@@ -657,24 +681,117 @@ __global__ __launch_bounds__(kLanes) void walk_eval_fallback_kernel(DevTree T, W
   }
 }
 
-__global__ void fused_init_kernel(WalkBufs B) {
-  if (threadIdx.x < 8) B.tot[threadIdx.x] = 0;
-  if (threadIdx.x < 9) B.wctr[64 * threadIdx.x] = 0;
-  if (threadIdx.x == 0) {
+// The counters a call starts from, by threads [0, 64) of one block.
+__device__ __forceinline__ void reset_counters(const WalkBufs& B, int t) {
+  if (t < 9) B.wctr[64 * t] = 0;
+  if (t == 0) {
     *B.ovf_count = 0;
     *B.ovf_count2 = 0;
-    B.c_off[0] = 0;  // base of an offsets scan of the counts this walk writes
+    *B.ticket = 0;
+    B.tot[5] = 0;
+    B.c_off[0] = 0;  // base of an offsets scan of the counts the walk writes
     B.l_off[0] = 0;
   }
+}
+
+__global__ void fused_init_kernel(WalkBufs B) {
+  if (threadIdx.x < 8) B.tot[threadIdx.x] = 0;
+  reset_counters(B, threadIdx.x);
+}
+
+// End of a call in one launch: totals and diagnostics summed per block over a
+// contiguous range of work items, then by the last block to finish over the
+// blocks in order (both fixed orders), written to the device, to the host's
+// page-locked copy, and the counters reset for the next call.  Replaces an
+// initial reset, a totals kernel, two diagnostics kernels over the particles
+// (21 + 5 us at 2^20, bound by the gather of the masses) and a copy.
+constexpr int kFinT = 256, kFinBlocks = 256;
+struct FinRec {
+  double d[4];
+  int64_t t[4];
+};
+
+__device__ __forceinline__ void block_sum_rec(FinRec& r, FinRec* sh) {
+  sh[threadIdx.x] = r;
+  __syncthreads();
+  for (int o = kFinT / 2; o > 0; o >>= 1) {
+    if (threadIdx.x < o)
+      for (int k = 0; k < 4; ++k) {
+        sh[threadIdx.x].d[k] += sh[threadIdx.x + o].d[k];
+        sh[threadIdx.x].t[k] += sh[threadIdx.x + o].t[k];
+      }
+    __syncthreads();
+  }
+  r = sh[0];
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kFinT) void finish_kernel(DevTree T, WalkBufs B, FinRec* rec,
+                                                       double* diag, int64_t* host, int last) {
+  __shared__ FinRec sh[kFinT];
+  __shared__ int is_last;
+  const int t = threadIdx.x, nb = gridDim.x;
+  const int64_t per = (T.nw + nb - 1) / nb;
+  const int64_t lo = blockIdx.x * per, hi = lo + per < T.nw ? lo + per : T.nw;
+  FinRec r{};
+  for (int64_t i = lo + t; i < hi; i += kFinT) {
+    const int2 wk = reinterpret_cast<const int2*>(T.work)[i];
+    const double2* dp = reinterpret_cast<const double2*>(B.dpart + 4 * i);
+    const double2 a = dp[0], b = dp[1];
+    const int4 c = reinterpret_cast<const int4*>(B.cnt)[wk.x];
+    const int64_t sz = T.ginfo[4 * (int64_t)wk.x + 1];
+    r.d[0] += a.x;
+    r.d[1] += a.y;
+    r.d[2] += b.x;
+    r.d[3] += b.y;
+    if (wk.y == 0) {
+      r.t[0] += c.x;
+      r.t[1] += c.y;
+      r.t[2] += sz * c.x;
+      r.t[3] += sz * c.z;
+    }
+  }
+  block_sum_rec(r, sh);
+  if (nb > 1) {
+    if (t < 4) {
+      __hip_atomic_store(&rec[blockIdx.x].d[t], r.d[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&rec[blockIdx.x].t[t], r.t[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();  // (also waits for the stores)
+    if (t == 0)
+      is_last = __hip_atomic_fetch_add(B.ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == nb - 1;
+    __syncthreads();
+    if (!is_last) return;
+    r = FinRec{};
+    if (t < nb)  // nb <= kFinT
+      for (int k = 0; k < 4; ++k) {
+        r.d[k] = __hip_atomic_load(&rec[t].d[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        r.t[k] = __hip_atomic_load(&rec[t].t[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    block_sum_rec(r, sh);
+  }
+  const int left = *B.ovf_count;
+  if (t < 4) {
+    diag[t] = r.d[t];
+    B.tot[t] = r.t[t];
+  }
+  if (host) {
+    if (t < 4) host[t] = r.t[t];
+    else if (t < 8) host[t] = B.tot[t];
+    else if (t == 8) host[t] = left;
+  }
+  if (t == 0) *B.ticket = 0;  // also when the later tiers and a second finish follow
+  __syncthreads();
+  if (last || left == 0) reset_counters(B, t);
 }
 
 }  // namespace
 
 int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps, bool plain,
-                     bool do_eval, float* acc, float* pot, void* stream) {
+                     bool do_eval, float* acc, float* pot, void* stream, int parts) {
   hipStream_t s = (hipStream_t)stream;
   const float th2 = theta * theta, eps2 = eps * eps;
-  fused_init_kernel<<<1, 64, 0, s>>>(B);
+  if (parts & kWalkInit) fused_init_kernel<<<1, 64, 0, s>>>(B);
   // The breadth-first FIFO holds about two tree levels of the group's walk,
   // which grow like theta^-3, as entries of up to eight children: 512 entries
   // (4 KB) held every walk of the 2^20 Plummer sphere and the 4M clumps at
@@ -684,17 +801,21 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
   const bool learned = B.mlp != nullptr;
   auto go = [&](auto plain_tag, auto learned_tag) {
     constexpr bool P = decltype(plain_tag)::value, L = decltype(learned_tag)::value;
-    if constexpr (L)  // one block of 16 waves per CU (16 x 6.9 KB frontiers + 12 KB network,
-                      // 122.5 KB of LDS), four per SIMD at <= 128 VGPRs
-      walk_eval_persistent_kernel<P, 512, L, 16, false><<<8 * 32, 16 * kLanes, 0, s>>>(
-          T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);
-    else  // 5 blocks of 4 waves per CU (four: 2.36 against 2.32 ms at 2^20)
-      walk_eval_persistent_kernel<P, 512, L, 4, false><<<8 * 160, 4 * kLanes, 0, s>>>(
-          T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);
-    walk_eval_persistent_kernel<P, 2048, L, 1, true><<<8 * 224, kLanes, 0, s>>>(
-        T, B, th2, eps2, acc, pot, do_eval, B.ovf_list, B.ovf_count, B.ovf_list2, B.ovf_count2);
-    walk_eval_fallback_kernel<P, L><<<B.gq_waves, kLanes, 0, s>>>(T, B, th2, eps2, acc, pot, do_eval,
-                                                                 B.ovf_list2, B.ovf_count2);
+    if (parts & kWalkFirst) {
+      if constexpr (L)  // one block of 16 waves per CU (16 x 6.9 KB frontiers + 12 KB network,
+                        // 122.5 KB of LDS), four per SIMD at <= 128 VGPRs
+        walk_eval_persistent_kernel<P, 512, L, 16, false><<<8 * 32, 16 * kLanes, 0, s>>>(
+            T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);
+      else  // 5 blocks of 4 waves per CU (four: 2.36 against 2.32 ms at 2^20)
+        walk_eval_persistent_kernel<P, 512, L, 4, false><<<8 * 160, 4 * kLanes, 0, s>>>(
+            T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);
+    }
+    if (parts & kWalkRest) {
+      walk_eval_persistent_kernel<P, 2048, L, 1, true><<<8 * 224, kLanes, 0, s>>>(
+          T, B, th2, eps2, acc, pot, do_eval, B.ovf_list, B.ovf_count, B.ovf_list2, B.ovf_count2);
+      walk_eval_fallback_kernel<P, L><<<B.gq_waves, kLanes, 0, s>>>(
+          T, B, th2, eps2, acc, pot, do_eval, B.ovf_list2, B.ovf_count2);
+    }
   };
   if (learned) {
     if (plain) go(std::true_type{}, std::true_type{});
@@ -703,6 +824,16 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
     if (plain) go(std::true_type{}, std::false_type{});
     else go(std::false_type{}, std::false_type{});
   }
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_finish(const DevTree& T, const WalkBufs& B, double* scratch, double* diag, int64_t* host,
+                  bool last, void* stream) {
+  // One block up to 1024 items (four per thread), then a block per 256.
+  static_assert(kFinBlocks <= kFinT, "the last block reads one record per thread");
+  const int nb = T.nw <= 1024 ? 1 : (int)std::min<int64_t>(kFinBlocks, (T.nw + kFinT - 1) / kFinT);
+  finish_kernel<<<nb, kFinT, 0, (hipStream_t)stream>>>(T, B, reinterpret_cast<FinRec*>(scratch), diag,
+                                                       host, last);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
