@@ -111,7 +111,7 @@ __device__ __forceinline__ float4 load_f4(const float4* p) {
 // and index arithmetic on scalar operands cost four slow instructions
 // per term before: compares and every instruction with a scalar-register
 // operand issue at half the rate of arithmetic on vector registers.
-template <bool PLAIN, typename SH>
+template <bool PLAIN, int TEAM, typename SH>
 struct WItem {
   const DevTree& T;
   SH& sh;
@@ -123,6 +123,15 @@ struct WItem {
   Sum4 acc4;
   int64_t nsrc = 0;
   int stamp;  // last value written to sh.mark (never reused by this wave)
+  int turn = 0;  // tiles until this wave evaluates one (teams)
+
+  // Whether the next tile is this wave's: the waves of a team take turns.
+  __device__ bool mine() {
+    if constexpr (TEAM == 1) return true;
+    const bool m = turn == 0;
+    turn = m ? TEAM - 1 : turn - 1;
+    return m;
+  }
 
   __device__ int tile_size() const { return S * c; }
 
@@ -130,7 +139,7 @@ struct WItem {
   __device__ int terms(int cnt) const { return cnt == S * c ? c : uni((cnt + S - 1) / S); }
 
   __device__ void flush_cells(uint32_t start, int cnt) {
-    if (!do_eval) return;
+    if (!do_eval || !mine()) return;
     const float4* mp = reinterpret_cast<const float4*>(T.mp);
     const int k = terms(cnt);
     if (lane < S * k) {
@@ -186,6 +195,7 @@ struct WItem {
     const float4* part = reinterpret_cast<const float4*>(T.part);
     const int ex = incl - ln, rel = first - ex, tile = tile_size();
     for (int u0 = 0; u0 < total; u0 += tile) {
+      if (!mine()) continue;
       const int cnt = min(tile, total - u0);
       const int k = terms(cnt);
       ++stamp;
@@ -247,8 +257,12 @@ enum : int { kOverflow = 0, kDone = 1, kFallBack = 2 };
 // with LEARNED, kFallBack (nothing written but the trace) if the group's
 // budget is exceeded, *nband = band candidates visited.  cw is the value of
 // cnt[g].w written by a walk with the theta test.
-template <bool PLAIN, bool LEARNED, typename SH, typename Q>
-__device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64_t w,
+//
+// TEAM > 1: the block's TEAM waves all call it for the same item, walk the tree
+// alike and evaluate every TEAM-th tile each (sh[wave]: their LDS areas); the
+// first wave adds the partial sums in wave order.
+template <bool PLAIN, bool LEARNED, int TEAM, typename SH, typename Q>
+__device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH* shw, int64_t w,
                               float th2, float eps2, float* __restrict__ acc,
                               float* __restrict__ pot, Q q, uint32_t qmask, bool gmem_q,
                               bool do_eval, int cw, int* nband_out, int* stamp,
@@ -268,7 +282,10 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
   const float4 gmin = U(gbox[2 * g]), gmax = U(gbox[2 * g + 1]);
   const float4* rec = reinterpret_cast<const float4*>(T.wrec);
 
-  WItem<PLAIN, SH> it{T, sh, in_vgpr(eps2)};
+  const int wave = TEAM == 1 ? 0 : uni((int)threadIdx.x / kLanes);
+  SH& sh = shw[wave];
+  WItem<PLAIN, TEAM, SH> it{T, sh, in_vgpr(eps2)};
+  it.turn = wave;
   it.lane = lane;
   it.nt = uni(min(kChunk, gi.y - wk.y));
   it.S = kLanes / it.nt;
@@ -510,7 +527,7 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
     }
     cw = 2 * nband;
   }
-  if (lane == 0 && wk.y == 0)  // per-group counts; the totals are reduced afterwards
+  if (lane == 0 && wk.y == 0 && wave == 0)  // per-group counts; the totals are reduced afterwards
     reinterpret_cast<int4*>(B.cnt)[g] = make_int4((int)ctail, (int)ltail, (int)it.nsrc, cw);
   if (!do_eval) return kDone;
 
@@ -525,20 +542,36 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
   }
   wave_lds_sync();
   double d[4] = {0.0, 0.0, 0.0, 0.0};  // m a, 1/2 m phi of this lane's target
-  if (lane < it.nt) {
-    float s[4] = {0.f, 0.f, 0.f, 0.f}, cc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int sl = 0; sl < it.S; ++sl) {
-      const float* r = red + (sl * it.nt + lane) * 8;
+  float s[4] = {0.f, 0.f, 0.f, 0.f}, cc[4] = {0.f, 0.f, 0.f, 0.f};
+  auto add = [&](const float* r) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (PLAIN) {
-          s[k] += r[k];
-        } else {
-          neu_add(s[k], cc[k], r[k]);
-          neu_add(s[k], cc[k], r[4 + k]);
-        }
+    for (int k = 0; k < 4; ++k) {
+      if (PLAIN) {
+        s[k] += r[k];
+      } else {
+        neu_add(s[k], cc[k], r[k]);
+        neu_add(s[k], cc[k], r[4 + k]);
       }
     }
+  };
+  if (lane < it.nt)
+    for (int sl = 0; sl < it.S; ++sl) add(red + (sl * it.nt + lane) * 8);
+  if constexpr (TEAM > 1) {
+    // behind the slices' sums in the tile: [32][8] floats per wave
+    float* own = reinterpret_cast<float*>(sh.tile + 2 * kTileW) + lane * 8;
+    if (lane < it.nt && wave != 0)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        own[k] = s[k];
+        own[4 + k] = cc[k];
+      }
+    __syncthreads();
+    if (wave != 0) return kDone;
+    if (lane < it.nt)
+      for (int k = 1; k < TEAM; ++k)
+        add(reinterpret_cast<const float*>(shw[k].tile + 2 * kTileW) + lane * 8);
+  }
+  if (lane < it.nt) {
     // The target itself is in its own leaf: its self term added -m_i/eps to
     // the potential and nothing to the acceleration; remove that same value.
     const float self = self_term(it.xi.w, eps2);
@@ -563,14 +596,14 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
 
 // One work item, with the theta re-walk of a group over its budget.
 template <bool PLAIN, bool LEARNED, typename SH, typename Q>
-__device__ int walk_eval_one(const DevTree& T, const WalkBufs& B, SH& sh, int64_t w, float th2,
+__device__ int walk_eval_one(const DevTree& T, const WalkBufs& B, SH* sh, int64_t w, float th2,
                              float eps2, float* acc, float* pot, Q q, uint32_t qmask, bool gmem_q,
                              bool do_eval, int* stamp, const MlpView* mv) {
   int nb = 0;
-  const int st = walk_eval_item<PLAIN, LEARNED>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q,
+  const int st = walk_eval_item<PLAIN, LEARNED, 1>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q,
                                                 do_eval, 0, &nb, stamp, mv);
   if (!LEARNED || st != kFallBack) return st;
-  return walk_eval_item<PLAIN, false>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q, do_eval,
+  return walk_eval_item<PLAIN, false, 1>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q, do_eval,
                                       2 * nb + 1, &nb, stamp, mv);
 }
 
@@ -583,9 +616,9 @@ __device__ __forceinline__ int take_work(int32_t* ctr, int lane) {
 
 // Persistent blocks of NW independent waves (with the learned criterion
 // they share one LDS copy of the network, loaded once per block).  Without
-// FROM_LIST each XCD owns a contiguous (Morton) range of work items, handed
+// FROM_LIST each XCD owns runs of consecutive (Morton-ordered) work items, handed
 // out one at a time through a per-XCD counter (work items differ a lot in
-// cost), and a wave whose XCD's range is exhausted helps the other XCDs;
+// cost), and a wave whose XCD's items are exhausted helps the other XCDs;
 // with FROM_LIST the items are the *src_n entries of src (the overflows of
 // an earlier tier), handed out through one counter.  Items whose frontier
 // outgrows this kernel's LDS queue are appended to (ovl, ovn).  Blocks of 16
@@ -607,7 +640,7 @@ void walk_eval_persistent_kernel(
     __syncthreads();
     V = mlp_lds(ml);
   }
-  const int wv = threadIdx.x / kLanes, lane = threadIdx.x & (kLanes - 1);
+  const int wv = uni((int)threadIdx.x / kLanes), lane = threadIdx.x & (kLanes - 1);
   // lds_qcap counts candidates; an entry holds up to eight
   const uint32_t qmask = (uint32_t)min(B.lds_qcap / 8, QCAP) - 1;
   const LQueue q{shw[wv].q};
@@ -618,27 +651,71 @@ void walk_eval_persistent_kernel(
       const int k = take_work(B.wctr + 64 * 8, lane);
       if (k >= *src_n) break;
       const int32_t w = src[k];
-      if (walk_eval_one<PLAIN, LEARNED>(T, B, shw[wv], w, th2, eps2, acc, pot, q, qmask, false,
+      if (walk_eval_one<PLAIN, LEARNED>(T, B, shw + wv, w, th2, eps2, acc, pot, q, qmask, false,
                                         do_eval != 0, &stamp, &V) == kOverflow &&
           lane == 0)
         ovl[atomicAdd(ovn, 1)] = w;
     }
   } else {
-    const int64_t per = (T.nw + 7) / 8;
+    // Runs of kDeal consecutive items are dealt to the XCDs in turn: equal
+    // shares of dense and sparse regions, and neighbours that share an L2.
+    // (One contiguous range per XCD left its slowest XCD to the others' help: 260
+    // against 249 us on a 200k galaxy at theta = 0.75; runs of 1 or 512 items cost
+    // 1 % more at 2^20 and above.)  A wave's first item is its rank among its XCD's
+    // waves (no atomic before any work), the next ones come from that XCD's
+    // counter, then from the other XCDs' in turn.  A block notes the counters it
+    // found used up, so that its other waves do not try them again.
+    constexpr int kDeal = 64;
+    __shared__ int used_up;
+    if (threadIdx.x == 0) used_up = 0;
+    __syncthreads();
+    const int waves = (int)(gridDim.x >> 3) * NW;
+    const int n = (int)((T.nw + 8 * kDeal - 1) / (8 * kDeal)) * kDeal;
+    int first = (int)(blockIdx.x >> 3) + wv * (int)(gridDim.x >> 3);
     for (int s = 0; s < 8; ++s) {
       const int x = (blockIdx.x + s) & 7;
-      const int64_t lo = x * per, n = max((int64_t)0, min(per, T.nw - lo));
       for (;;) {
-        const int k = take_work(B.wctr + 64 * x, lane);
-        if (k >= n) break;
-        const int64_t w = lo + k;
-        if (walk_eval_one<PLAIN, LEARNED>(T, B, shw[wv], w, th2, eps2, acc, pot, q, qmask, false,
+        int k = first;
+        if (k < 0) {
+          if (uni(*(volatile int*)&used_up) >> x & 1) break;
+          k = take_work(B.wctr + 64 * x, lane) + waves;
+        }
+        first = -1;
+        if (k >= n) {
+          if (lane == 0) atomicOr(&used_up, 1 << x);
+          break;
+        }
+        const int64_t w = ((int64_t)(k / kDeal) * 8 + x) * kDeal + k % kDeal;
+        if (w >= T.nw) continue;
+        if (walk_eval_one<PLAIN, LEARNED>(T, B, shw + wv, w, th2, eps2, acc, pot, q, qmask, false,
                                           do_eval != 0, &stamp, &V) == kOverflow &&
             lane == 0)
           ovl[atomicAdd(ovn, 1)] = (int32_t)w;
       }
     }
   }
+}
+
+// One block of NW waves per work item, for trees with too few items to fill
+// the chip with a wave each: the item's latency is its walk plus 1 / NW of its
+// tiles, and no wave waits for a work counter.  (The walk itself, about a
+// microsecond per dependent gather, is repeated by every wave: the chip would
+// be idle otherwise.)  Blocks go to the XCDs in turn, so consecutive items,
+// which cost alike, do too (contiguous ranges per XCD: 10 % longer).
+template <bool PLAIN, int QCAP, int NW>
+__global__ __launch_bounds__(NW * kLanes) void walk_eval_team_kernel(DevTree T, WalkBufs B, float th2,
+                                                                     float eps2, float* acc,
+                                                                     float* pot) {
+  __shared__ WShared<QCAP> shw[NW];
+  const int64_t w = blockIdx.x;
+  const int wv = uni((int)threadIdx.x / kLanes);
+  const uint32_t qmask = (uint32_t)min(B.lds_qcap / 8, QCAP) - 1;
+  shw[wv].mark[threadIdx.x & (kLanes - 1)] = 0;
+  int stamp = 0, nb = 0;
+  if (walk_eval_item<PLAIN, false, NW>(T, B, shw, w, th2, eps2, acc, pot, LQueue{shw[wv].q}, qmask,
+                                       false, true, 0, &nb, &stamp, nullptr) == kOverflow &&
+      threadIdx.x == 0)
+    B.ovf_list[atomicAdd(B.ovf_count, 1)] = (int32_t)w;
 }
 
 // Global-memory queues: written and read by different lanes of one wave, so
@@ -674,7 +751,7 @@ __global__ __launch_bounds__(kLanes) void walk_eval_fallback_kernel(DevTree T, W
   sh.mark[threadIdx.x] = 0;
   int stamp = 0;
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    const int st = walk_eval_one<PLAIN, LEARNED>(T, B, sh, src[i], th2, eps2, acc, pot, q,
+    const int st = walk_eval_one<PLAIN, LEARNED>(T, B, &sh, src[i], th2, eps2, acc, pot, q,
                                                  (uint32_t)(B.gq_cap - 1), true, do_eval != 0, &stamp, &V);
     if (st == kOverflow && threadIdx.x == 0)
       atomicOr(reinterpret_cast<unsigned long long*>(&B.tot[5]), 1ull);
@@ -799,6 +876,17 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
   // the overflows with 2048-entry LDS queues (one wave per block, 7 per CU),
   // then global-memory queues.
   const bool learned = B.mlp != nullptr;
+  // Waves per work item.  With fewer than about 13000 items (2.5 for each of the
+  // 5120 waves the chip holds) one wave per item leaves a long tail, or most of
+  // the chip idle; measured with 1 / 2 / 4 / 8 waves per item, in us: 79 items (1000
+  // bodies) 57 / 46 / 43 / 40, 368 items 114 / 78 / 62 / 58, 655 items 136 / 95 / 75 / 86,
+  // 1042 items 160 / 108 / 92 / 104, 2590 items 212 / 169 / 155 / 211, 4314 items 164 / 129 /
+  // 134 / 196, 7241 items 388 / 336 / 366 / 577, 12641 items 249 / 246 / 309 / -, 24905 items
+  // 368 / 391 / - / -.  (Not with the learned criterion: every wave would run the
+  // network.)
+  int team = 1;
+  if (!learned && do_eval && !B.export_lists)
+    team = T.nw <= 512 ? 8 : T.nw <= 3500 ? 4 : T.nw <= 13000 ? 2 : 1;
   auto go = [&](auto plain_tag, auto learned_tag) {
     constexpr bool P = decltype(plain_tag)::value, L = decltype(learned_tag)::value;
     if (parts & kWalkFirst) {
@@ -806,6 +894,12 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
                         // 122.5 KB of LDS), four per SIMD at <= 128 VGPRs
         walk_eval_persistent_kernel<P, 512, L, 16, false><<<8 * 32, 16 * kLanes, 0, s>>>(
             T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);
+      else if (team == 8)
+        walk_eval_team_kernel<P, 512, 8><<<(unsigned)T.nw, 8 * kLanes, 0, s>>>(T, B, th2, eps2, acc, pot);
+      else if (team == 4)
+        walk_eval_team_kernel<P, 512, 4><<<(unsigned)T.nw, 4 * kLanes, 0, s>>>(T, B, th2, eps2, acc, pot);
+      else if (team == 2)
+        walk_eval_team_kernel<P, 512, 2><<<(unsigned)T.nw, 2 * kLanes, 0, s>>>(T, B, th2, eps2, acc, pot);
       else  // 5 blocks of 4 waves per CU (four: 2.36 against 2.32 ms at 2^20)
         walk_eval_persistent_kernel<P, 512, L, 4, false><<<8 * 160, 4 * kLanes, 0, s>>>(
             T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);

@@ -66,3 +66,39 @@ def test_padding_at_a_target():
         O = oracle.Tree(pos, m, n_leaf, n_group)
         ar, _ = O.forces(0.8, 1e-6)
         assert oracle.rel_err(acc.double().cpu().numpy(), ar).max() <= 1e-4
+
+
+@pytest.mark.parametrize("n", [40, 900, 9000, 20000, 70000, 230000])
+@pytest.mark.parametrize("cap", [None, "64"])
+def test_waves_per_item(n, cap, monkeypatch):
+    """Sizes on every branch of the waves-per-item rule (8, 4, 2, 1), with queues
+    that hold every walk and with queues so small that items go to the later
+    tiers: the same counts, diagnostics that match the outputs, forces against
+    the oracle's on a sample of groups."""
+    pos, m = W.plummer(n, 21)
+    if cap:
+        monkeypatch.setenv("OCTGRAV_LDS_QUEUE", cap)
+    T = og.Tree(pos, m, 16, 64)
+    monkeypatch.delenv("OCTGRAV_LDS_QUEUE", raising=False)
+    O = oracle.Tree(pos, m, 16, 64)
+    acc, pot = T.forces(0.6, 0.01)
+    g = T.group_counts()
+    co, _, lo, _ = O.lists(0.6)
+    assert np.array_equal(g[:, 0], np.diff(co)) and np.array_equal(g[:, 1], np.diff(lo))
+    c = T.last_counts()
+    assert c["n_c"] == co[-1] and c["n_l"] == lo[-1]
+    a, p = acc.double().cpu().numpy(), pot.double().cpu().numpy()
+    sel = np.random.default_rng(2).choice(O.n_groups, min(200, O.n_groups), replace=False)
+    ar, pr = O.forces(0.6, 0.01, groups=sel)
+    k = ~np.isnan(pr)
+    ea, ep = oracle.rel_err(a[k], ar[k]), oracle.rel_err(p[k], pr[k])
+    assert np.median(ea) <= 1e-5 and ea.max() <= 1e-4 and ep.max() <= 1e-4
+    mom, w = T.diagnostics()
+    md = m.astype(np.float64)
+    # FP64 sums of the same FP32 outputs in another order
+    scale = np.abs(md[:, None] * a).sum(0)
+    assert (np.abs(mom - (md[:, None] * a).sum(0)) <= 1e-12 * scale).all()
+    assert abs(w - 0.5 * (md * p).sum()) <= 1e-12 * np.abs(md * p).sum()
+    again = T.forces(0.6, 0.01)
+    assert (again[0] == acc).all() and (again[1] == pot).all()
+    assert T.diagnostics()[1] == w and (T.diagnostics()[0] == mom).all()
