@@ -75,8 +75,17 @@ void set_ctl(WalkBufs& b, void* base) {
 
 // Network of the learned criterion: FP32 master parameters, Adam moments,
 // the last gradient, the packed BF16 inference image and training scratch.
+// Page-locked copy of a step's results.
+struct MlpHost {
+  double loss;
+  float v[kMlpParams];
+};
+
 struct octgrav_mlp {
   hipStream_t stream = nullptr;
+  MlpHost *host = nullptr, *host_dev = nullptr;  // and its device address
+  bool host_tried = false;
+
   void *P = nullptr, *mom1 = nullptr, *mom2 = nullptr, *grad = nullptr, *pk = nullptr,
        *d_loss = nullptr, *scratch = nullptr;
   int64_t scratch_b = 0;
@@ -84,6 +93,22 @@ struct octgrav_mlp {
 
   ~octgrav_mlp() {
     for (void* p : allocs) hipFree(p);
+    if (host) hipHostFree(host);
+  }
+  // The page-locked buffer, or NULL if there is none to be had.
+  MlpHost* host_buffer() {
+    if (!host_tried) {
+      host_tried = true;
+      if (hipHostMalloc((void**)&host, sizeof(MlpHost)) != hipSuccess) {
+        (void)hipGetLastError();
+        host = nullptr;
+      } else if (hipHostGetDevicePointer((void**)&host_dev, host, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        hipHostFree(host);
+        host = nullptr;
+      }
+    }
+    return host;
   }
   int alloc(void** p, size_t bytes) {
     if (alloc_fault() || hipMalloc(p, std::max<size_t>(bytes, 256)) != hipSuccess) {
@@ -1411,9 +1436,14 @@ int octgrav_mlp_get_moments(const octgrav_mlp* m, float* mom1, float* mom2) {
 int octgrav_mlp_get_params(const octgrav_mlp* m, float* params) {
   g_err.clear();
   if (!m || !params) return fail(OCTGRAV_EINVAL, "NULL argument");
-  if (hipStreamSynchronize(m->stream) != hipSuccess ||
-      hipMemcpy(params, m->P, kMlpParams * 4, hipMemcpyDeviceToHost) != hipSuccess)
+  // Through page-locked memory where there is some: one asynchronous copy and
+  // one wait.
+  MlpHost* h = const_cast<octgrav_mlp*>(m)->host_buffer();
+  if (hipMemcpyAsync(h ? h->v : params, m->P, kMlpParams * 4, hipMemcpyDeviceToHost, m->stream) !=
+          hipSuccess ||
+      hipStreamSynchronize(m->stream) != hipSuccess)
     return fail(OCTGRAV_EHIP, "parameter copy-back failed");
+  if (h) std::memcpy(params, h->v, kMlpParams * 4);
   return OCTGRAV_OK;
 }
 
@@ -1421,7 +1451,7 @@ int octgrav_mlp_forward(octgrav_mlp* m, const float* x, int64_t b, float* y) {
   g_err.clear();
   if (!m) return fail(OCTGRAV_EINVAL, "NULL handle");
   if (b < 0 || (b > 0 && (!x || !y))) return fail(OCTGRAV_EINVAL, "bad batch arguments");
-  if (launch_mlp_forward(m->pk, x, b, y, nullptr, nullptr, m->stream) ||
+  if (launch_mlp_forward(m->pk, x, b, y, m->stream) ||
       hipStreamSynchronize(m->stream) != hipSuccess)
     return fail(OCTGRAV_EHIP, "forward failed");
   return OCTGRAV_OK;
@@ -1434,13 +1464,21 @@ int octgrav_mlp_loss_grad(octgrav_mlp* m, const float* x, const float* target, i
   if (b < 1 || !x || !target) return fail(OCTGRAV_EINVAL, "bad batch arguments");
   if (!(tau > 0.0f && tau < 1.0f)) return fail(OCTGRAV_EINVAL, "tau must be in (0, 1)");
   if (int rc = m->reserve(b)) return rc;
+  // The results come back through page-locked memory that the last kernel
+  // writes; without it, through copies.
+  MlpHost* h = m->host_buffer();
   if (launch_mlp_loss_grad(m->pk, x, target, b, tau, (float*)m->scratch, (float*)m->grad,
-                           (double*)m->d_loss, m->stream) ||
-      hipMemcpyAsync(loss, m->d_loss, 8, hipMemcpyDeviceToHost, m->stream) != hipSuccess ||
-      (grad && hipMemcpyAsync(grad, m->grad, kMlpParams * 4, hipMemcpyDeviceToHost, m->stream) !=
-                   hipSuccess) ||
+                           (double*)m->d_loss, h && grad ? m->host_dev->v : nullptr,
+                           h ? &m->host_dev->loss : nullptr, m->stream) ||
+      (!h && (hipMemcpyAsync(loss, m->d_loss, 8, hipMemcpyDeviceToHost, m->stream) != hipSuccess ||
+              (grad && hipMemcpyAsync(grad, m->grad, kMlpParams * 4, hipMemcpyDeviceToHost,
+                                      m->stream) != hipSuccess))) ||
       hipStreamSynchronize(m->stream) != hipSuccess)
     return fail(OCTGRAV_EHIP, "loss/gradient failed");
+  if (h) {
+    *loss = h->loss;
+    if (grad) std::memcpy(grad, h->v, kMlpParams * 4);
+  }
   return OCTGRAV_OK;
 }
 
@@ -1452,9 +1490,8 @@ int octgrav_mlp_adam(octgrav_mlp* m, float lr, float beta1, float beta2, float e
     return fail(OCTGRAV_EINVAL, "bad Adam arguments");
   const float c1 = (float)(1.0 - std::pow((double)beta1, step));
   const float c2 = (float)(1.0 - std::pow((double)beta2, step));
-  if (launch_mlp_adam((float*)m->P, (float*)m->mom1, (float*)m->mom2, (const float*)m->grad, lr,
-                      beta1, beta2, eps, c1, c2, m->stream) ||
-      launch_mlp_pack((const float*)m->P, m->pk, m->stream) ||
+  if (launch_mlp_adam((float*)m->P, (float*)m->mom1, (float*)m->mom2, (const float*)m->grad, m->pk,
+                      lr, beta1, beta2, eps, c1, c2, m->stream) ||
       hipStreamSynchronize(m->stream) != hipSuccess)
     return fail(OCTGRAV_EHIP, "Adam step failed");
   return OCTGRAV_OK;

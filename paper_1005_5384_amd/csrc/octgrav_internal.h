@@ -170,16 +170,17 @@ int launch_mac_labels(const DevTree& T, const WalkBufs& B, const int32_t* groups
                       const int64_t* out_off, const float* acc_direct, float eps, float* feat,
                       float* label, int32_t* gout, int32_t* cout, int64_t npairs, void* stream);
 // Network of the learned criterion: pack FP32 parameters into the BF16
-// inference image; batch forward (a1s / a2s: B x 64 pre-activations, may be
-// NULL); loss + gradient of a batch (scratch arrays B x 64 / B); Adam step.
+// inference image; batch forward; loss + gradient of a batch (hgrad / hloss:
+// device addresses of page-locked host copies, or NULL); Adam step, which also
+// updates the image.
 int launch_mlp_pack(const float* P, void* pk, void* stream);
-int launch_mlp_forward(const void* pk, const float* x, int64_t B, float* y, float* a1s, float* a2s,
-                       void* stream);
+int launch_mlp_forward(const void* pk, const float* x, int64_t B, float* y, void* stream);
 int launch_mlp_loss_grad(const void* pk, const float* x, const float* tgt, int64_t B, float tau,
-                         float* scratch, float* grad, double* loss, void* stream);
+                         float* scratch, float* grad, double* loss, float* hgrad, double* hloss,
+                         void* stream);
 int64_t mlp_train_scratch_floats(int64_t B);  // scratch of launch_mlp_loss_grad
-int launch_mlp_adam(float* P, float* m, float* v, const float* g, float lr, float b1, float b2,
-                    float eps, float c1, float c2, void* stream);
+int launch_mlp_adam(float* P, float* m, float* v, const float* g, void* pk, float lr, float b1,
+                    float b2, float eps, float c1, float c2, void* stream);
 // Device tree build (same result as build_host_tree, computed on the GPU).
 // The persistent arrays are allocated through DevAlloc (owned by the
 // caller); DeviceArrays receives the FP64 boxes / moments, the unsigned
