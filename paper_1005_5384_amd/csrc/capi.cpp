@@ -323,7 +323,16 @@ struct octgrav_tree : DevAlloc {
     }
     std::vector<int32_t> iperm(n);
     for (int64_t i = 0; i < n; ++i) iperm[h.perm[i]] = (int32_t)i;
-    if ((rc = upload(fcell, &dt.fcell)) || (rc = upload(iperm, &dt.iperm))) return rc;
+    std::vector<int32_t> wwork;
+    wwork.reserve(h.work.size());
+    for (int cls = 0; cls < kItemClasses; ++cls)
+      for (int64_t w = 0; w < nw; ++w) {
+        const int32_t g = h.work[2 * w], off = h.work[2 * w + 1];
+        if (item_class(std::min(kChunk, h.ginfo[4 * (int64_t)g + 1] - off)) == cls)
+          wwork.insert(wwork.end(), {g, off});
+      }
+    if ((rc = upload(fcell, &dt.fcell)) || (rc = upload(iperm, &dt.iperm)) || (rc = upload(wwork, &dt.wwork)))
+      return rc;
     if ((rc = upload(h.part, &dt.part)) || (rc = upload(h.perm, &dt.perm)) ||
         (rc = upload(h.topo, &dt.topo)) || (rc = upload(geo_dev, &dt.geo)) ||
         (rc = upload(wrec, &dt.wrec)) ||

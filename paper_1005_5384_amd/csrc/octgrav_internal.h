@@ -9,6 +9,13 @@ namespace octgrav {
 
 constexpr int kMaxDepth = 21;   // levels below the root cube (63-bit Morton keys)
 constexpr int kChunk = 32;      // targets per evaluation work item
+// Work items by targets, the classes that are handed out one after the other
+// (0 first): more than 24, more than 16, more than 8, the rest.
+constexpr int kItemClasses = 4;
+constexpr int kItemBound[3] = {24, 16, 8};
+constexpr int item_class(int targets) {
+  return targets > kItemBound[0] ? 0 : targets > kItemBound[1] ? 1 : targets > kItemBound[2] ? 2 : 3;
+}
 
 // Host tree (Sec. 2.1), FP64 geometry and moments, FP32 device images.
 struct HostTree {
@@ -76,7 +83,11 @@ struct DevTree {
   const float* mp;       // float4 x3 [nc]
   const int32_t* ginfo;  // int4 [ng]
   const float* gbox;     // float4 x2 [ng]
-  const int32_t* work;   // int2 [nw]
+  const int32_t* work;   // int2 [nw] {group, first target in it}, in group order
+  // The same items as the fused wave kernels take them: class by class
+  // (item_class), each in group order.  An item's time grows with its targets (64 /
+  // slices terms per tile), and the last items to start should be short ones.
+  const int32_t* wwork;
   int64_t n, nc, ng, nw;
 };
 

@@ -684,12 +684,12 @@ __global__ void images_kernel(Cells C, int64_t nc, const double* __restrict__ bo
 // particle ranges partition the particles, so marking each group at its first
 // particle and compacting orders them by first particle.
 // (Also clears the nc + 1 per-group chunk counts that group_fill_kernel
-// fills and the chunk scan reads.)
+// fills and the chunk scan reads: chunks of each item class.)
 __global__ void group_mark_kernel(Cells C, int64_t nc, int n_group, int32_t* __restrict__ at,
-                                  int32_t* __restrict__ nchunk) {
+                                  int4* __restrict__ nchunk) {
   const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (c > nc) return;
-  nchunk[c] = 0;
+  nchunk[c] = make_int4(0, 0, 0, 0);
   if (c == nc) return;
   const bool cand = C.n[c] <= n_group || C.nc[c] == 0;
   const bool top = c == 0 || C.n[C.parent[c]] > n_group;
@@ -707,7 +707,7 @@ __global__ void group_fill_kernel(const int32_t* __restrict__ at, const int32_t*
                                   const int32_t* __restrict__ pre, int64_t n, Cells C,
                                   const double* __restrict__ box, int32_t* __restrict__ groups,
                                   int4* __restrict__ ginfo, float4* __restrict__ gbox,
-                                  int32_t* __restrict__ nchunk) {
+                                  int4* __restrict__ nchunk) {
   const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (i >= n || !f[i]) return;
   const int64_t g = pre[i];
@@ -717,14 +717,37 @@ __global__ void group_fill_kernel(const int32_t* __restrict__ at, const int32_t*
   const double* bx = box + 6 * (int64_t)c;
   gbox[2 * g] = make_float4((float)bx[0], (float)bx[1], (float)bx[2], 0.0f);
   gbox[2 * g + 1] = make_float4((float)bx[3], (float)bx[4], (float)bx[5], 0.0f);
-  nchunk[g] = (C.n[c] + kChunk - 1) / kChunk;
+  const int32_t rest = C.n[c] % kChunk;
+  int32_t k[kItemClasses] = {0, 0, 0, 0};
+  k[item_class(kChunk)] = C.n[c] / kChunk;
+  for (int q = 0; q < kItemClasses; ++q) k[q] += rest > 0 && item_class(rest) == q;
+  nchunk[g] = make_int4(k[0], k[1], k[2], k[3]);
 }
 
-__global__ void work_kernel(const int32_t* __restrict__ nchunk, const int32_t* __restrict__ pre,
-                            const int32_t* __restrict__ ngp, int2* __restrict__ work) {
+struct Int4Sum {
+  __host__ __device__ int4 operator()(const int4& a, const int4& b) const {
+    return make_int4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+  }
+};
+
+// Work items in group order (work) and class by class (wwork); pre and all:
+// chunks of each class in the groups before, and in all groups.
+__global__ void work_kernel(const int4* __restrict__ pre, const int4* __restrict__ all,
+                            const int4* __restrict__ ginfo, const int32_t* __restrict__ ngp,
+                            int2* __restrict__ work, int2* __restrict__ wwork) {
   const int64_t g = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (g >= *ngp) return;
-  for (int k = 0; k < nchunk[g]; ++k) work[pre[g] + k] = make_int2((int32_t)g, k * kChunk);
+  const int4 p = pre[g], t = *all;
+  const int32_t n = ginfo[g].y, at = p.x + p.y + p.z + p.w;
+  const int32_t begin[kItemClasses] = {p.x, t.x + p.y, t.x + t.y + p.z, t.x + t.y + t.z + p.w};
+  for (int32_t k = 0, off = 0; off < n; ++k, off += kChunk) {
+    const int2 w = make_int2((int32_t)g, off);
+    const int c = item_class(n - off < kChunk ? n - off : kChunk);
+    work[at + k] = w;
+    // a group's full chunks come before its rest, which may be of the same class
+    for (int q = 0; q < kItemClasses; ++q)
+      if (c == q) wwork[begin[q] + (q == item_class(kChunk) ? k : 0)] = w;
+  }
 }
 
 // The build's scalars the host needs, gathered in one place on the device so
@@ -739,7 +762,7 @@ struct BuildInfo {
 // The group and work-item counts and the leaf count (sum of the images
 // kernel's nb per-block counts).
 __global__ __launch_bounds__(kT) void counts_kernel(const int32_t* __restrict__ ngp,
-                                                    const int32_t* __restrict__ nwp,
+                                                    const int4* __restrict__ nwp,
                                                     const int32_t* __restrict__ leaf_part,
                                                     int64_t nb, BuildInfo* __restrict__ info) {
   __shared__ int sh[kT / 64];
@@ -748,7 +771,7 @@ __global__ __launch_bounds__(kT) void counts_kernel(const int32_t* __restrict__ 
   t = block_sum(t, sh);
   if (threadIdx.x == 0) {
     info->ng = *ngp;
-    info->nw = *nwp;
+    info->nw = nwp->x + nwp->y + nwp->z + nwp->w;
     info->leaves = t;
   }
 }
@@ -783,6 +806,15 @@ int exclusive_sum(const T* in, T* out, int64_t n, Scratch& S, hipStream_t s) {
   void* tmp = S.get<char>((int64_t)bytes);
   if (!tmp) return -2;
   return hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, (int)n, s) == hipSuccess ? 0 : -1;
+}
+
+template <typename T, typename Op>
+int exclusive_scan(const T* in, T* out, int64_t n, T init, Op op, Scratch& S, hipStream_t s) {
+  size_t bytes = 0;
+  if (hipcub::DeviceScan::ExclusiveScan(nullptr, bytes, in, out, op, init, (int)n, s) != hipSuccess) return -1;
+  void* tmp = S.get<char>((int64_t)bytes);
+  if (!tmp) return -2;
+  return hipcub::DeviceScan::ExclusiveScan(tmp, bytes, in, out, op, init, (int)n, s) == hipSuccess ? 0 : -1;
 }
 
 }  // namespace
@@ -1050,8 +1082,8 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   int32_t* at = S.get<int32_t>(n);
   int32_t* f = S.get<int32_t>(n + 1);
   int32_t* fpre = S.get<int32_t>(n + 1);
-  int32_t* nchunk = S.get<int32_t>(ngcap + 1);
-  int32_t* cpre = S.get<int32_t>(ngcap + 1);
+  int4* nchunk = S.get<int4>(ngcap + 1);
+  int4* cpre = S.get<int4>(ngcap + 1);
   if (!at || !f || !fpre || !nchunk || !cpre) return fail("device allocation failed");
   if (hipMemsetAsync(at, 0xff, (size_t)n * 4, s) != hipSuccess) return fail("memset failed");
   group_mark_kernel<<<blocks(nc + 1), kT, 0, s>>>(C, nc, n_group, at, nchunk);
@@ -1060,13 +1092,15 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   int32_t* groups = nullptr;
   int4* ginfo = nullptr;
   float4* gbox = nullptr;
-  int2* work = nullptr;
+  int2 *work = nullptr, *wwork = nullptr;
   if (!A((void**)&groups, (size_t)ngcap * 4) || !A((void**)&ginfo, (size_t)ngcap * 16) ||
-      !A((void**)&gbox, (size_t)ngcap * 32) || !A((void**)&work, (size_t)nwcap * 8))
+      !A((void**)&gbox, (size_t)ngcap * 32) || !A((void**)&work, (size_t)nwcap * 8) ||
+      !A((void**)&wwork, (size_t)nwcap * 8))
     return fail("device allocation failed");
   group_fill_kernel<<<blocks(n), kT, 0, s>>>(at, f, fpre, n, C, box, groups, ginfo, gbox, nchunk);
-  if (exclusive_sum(nchunk, cpre, ngcap + 1, S, s)) return fail("scan failed");
-  work_kernel<<<blocks(ngcap), kT, 0, s>>>(nchunk, cpre, fpre + n, work);
+  if (exclusive_scan(nchunk, cpre, ngcap + 1, make_int4(0, 0, 0, 0), Int4Sum(), S, s))
+    return fail("scan failed");
+  work_kernel<<<blocks(ngcap), kT, 0, s>>>(cpre, cpre + ngcap, ginfo, fpre + n, work, wwork);
   counts_kernel<<<1, kT, 0, s>>>(fpre + n, cpre + ngcap, nleaf, nbi, info);
   if (!fetch(offsetof(BuildInfo, ng), sizeof(BuildInfo) - offsetof(BuildInfo, ng)))
     return fail("group and work counts failed");
@@ -1087,6 +1121,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   dt.ginfo = reinterpret_cast<const int32_t*>(ginfo);
   dt.gbox = reinterpret_cast<const float*>(gbox);
   dt.work = reinterpret_cast<const int32_t*>(work);
+  dt.wwork = reinterpret_cast<const int32_t*>(wwork);
   dt.n = n;
   dt.nc = nc;
   dt.ng = ng;

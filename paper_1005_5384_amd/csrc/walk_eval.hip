@@ -274,7 +274,7 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH* shw, int6
     if constexpr (LEARNED) return uni(v);
     else return v;
   };
-  const int2 wk0 = reinterpret_cast<const int2*>(T.work)[w];
+  const int2 wk0 = reinterpret_cast<const int2*>(T.wwork)[w];
   const int2 wk = make_int2(U(wk0.x), U(wk0.y));
   const int64_t g = wk.x;
   const int4 gi = U(reinterpret_cast<const int4*>(T.ginfo)[g]);
@@ -812,7 +812,7 @@ __global__ __launch_bounds__(kFinT) void finish_kernel(DevTree T, WalkBufs B, Fi
   const int64_t lo = blockIdx.x * per, hi = lo + per < T.nw ? lo + per : T.nw;
   FinRec r{};
   for (int64_t i = lo + t; i < hi; i += kFinT) {
-    const int2 wk = reinterpret_cast<const int2*>(T.work)[i];
+    const int2 wk = reinterpret_cast<const int2*>(T.wwork)[i];
     const double2* dp = reinterpret_cast<const double2*>(B.dpart + 4 * i);
     const double2 a = dp[0], b = dp[1];
     const int4 c = reinterpret_cast<const int4*>(B.cnt)[wk.x];
@@ -876,17 +876,16 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
   // the overflows with 2048-entry LDS queues (one wave per block, 7 per CU),
   // then global-memory queues.
   const bool learned = B.mlp != nullptr;
-  // Waves per work item.  With fewer than about 13000 items (2.5 for each of the
+  // Waves per work item.  With fewer than about 11000 items (two for each of the
   // 5120 waves the chip holds) one wave per item leaves a long tail, or most of
   // the chip idle; measured with 1 / 2 / 4 / 8 waves per item, in us: 79 items (1000
-  // bodies) 57 / 46 / 43 / 40, 368 items 114 / 78 / 62 / 58, 655 items 136 / 95 / 75 / 86,
-  // 1042 items 160 / 108 / 92 / 104, 2590 items 212 / 169 / 155 / 211, 4314 items 164 / 129 /
-  // 134 / 196, 7241 items 388 / 336 / 366 / 577, 12641 items 249 / 246 / 309 / -, 24905 items
-  // 368 / 391 / - / -.  (Not with the learned criterion: every wave would run the
-  // network.)
+  // bodies) 106 / 47 / 42 / 40, 368 items 159 / 79 / 61 / 56, 655 items 180 / 93 / 71 / 84,
+  // 1198 items 227 / 130 / 97 / 127, 2590 items 213 / 130 / 156 / 218, 5008 items 261 / 214 /
+  // 252 / 395, 7580 items 180 / 163 / 205 / 328, 12641 items 237 / 244 / 318 / 530.  (Not
+  // with the learned criterion: every wave would run the network.)
   int team = 1;
   if (!learned && do_eval && !B.export_lists)
-    team = T.nw <= 512 ? 8 : T.nw <= 3500 ? 4 : T.nw <= 13000 ? 2 : 1;
+    team = T.nw <= 512 ? 8 : T.nw <= 2000 ? 4 : T.nw <= 11000 ? 2 : 1;
   auto go = [&](auto plain_tag, auto learned_tag) {
     constexpr bool P = decltype(plain_tag)::value, L = decltype(learned_tag)::value;
     if (parts & kWalkFirst) {

@@ -86,3 +86,20 @@ def test_device_build_deep_chains_outgrow_the_cell_arrays():
     m = rng.uniform(0.5, 1.5, pos.shape[0]).astype(np.float32)
     H, D = _same_tree(pos, m, 1, 1)
     assert H.stats["n_cells"] > 2 * pos.shape[0] + 64
+
+
+@pytest.mark.parametrize("n_group", [8, 33, 64, 200])
+def test_forces_match_across_builds_for_every_item_class(n_group):
+    """Work items of every size class, in the order both builds hand them out: the
+    same forces bit for bit (an item missing or taken twice would show)."""
+    import torch
+    pos, m = W.milky_way(30000, 12)
+    A = og.Tree(pos, m, 8, n_group)
+    B = og.Tree(pos, m, 8, n_group, device_build=True)
+    assert A.stats["n_work"] == B.stats["n_work"]
+    nan = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda")
+    a = A.forces(0.6, 0.01, acc=nan(30000, 3), pot=nan(30000))
+    b = B.forces(0.6, 0.01, acc=nan(30000, 3), pot=nan(30000))
+    assert torch.isfinite(a[0]).all() and torch.isfinite(a[1]).all()
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    assert A.last_counts() == B.last_counts() and A.diagnostics()[1] == B.diagnostics()[1]
