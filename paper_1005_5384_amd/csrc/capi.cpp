@@ -187,7 +187,16 @@ struct octgrav_tree : DevAlloc {
     if (eval_stream) hipStreamDestroy(eval_stream);
   }
 
-  int alloc(void** p, size_t bytes) override { return dalloc(p, bytes); }
+  // Arrays that live as long as the handle (or, with the pool, the tree).
+  Arena arena;
+  int alloc(void** p, size_t bytes) override {
+    if (pool) return dalloc(p, bytes);
+    if (alloc_fault()) return fail(OCTGRAV_ENOMEM, "device allocation failed (injected)");
+    *p = arena.take(bytes);
+    if (!*p) return fail(OCTGRAV_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    return OCTGRAV_OK;
+  }
+  void expect(size_t bytes) override { arena.expect(bytes); }
 
   // Device-built trees keep the FP64 boxes and moments, the boundary image,
   // the particle order and the FP32 moments on the device until an export
@@ -270,7 +279,7 @@ struct octgrav_tree : DevAlloc {
   template <typename T>
   int upload(const std::vector<T>& v, const T** out) {
     void* p = nullptr;
-    if (int rc = dalloc(&p, v.size() * sizeof(T))) return rc;
+    if (int rc = alloc(&p, v.size() * sizeof(T))) return rc;
     if (!v.empty() && hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
       return fail(OCTGRAV_EHIP, "hipMemcpy (tree upload) failed");
     *out = (const T*)p;
@@ -331,6 +340,7 @@ struct octgrav_tree : DevAlloc {
         if (item_class(std::min(kChunk, h.ginfo[4 * (int64_t)g + 1] - off)) == cls)
           wwork.insert(wwork.end(), {g, off});
       }
+    expect((size_t)n * 24 + (size_t)nc * 144 + (size_t)ng * 48 + (size_t)nw * 16 + 16 * 256);
     if ((rc = upload(fcell, &dt.fcell)) || (rc = upload(iperm, &dt.iperm)) || (rc = upload(wwork, &dt.wwork)))
       return rc;
     if ((rc = upload(h.part, &dt.part)) || (rc = upload(h.perm, &dt.perm)) ||
@@ -373,8 +383,8 @@ struct octgrav_tree : DevAlloc {
     return alloc_walk_buffers();
   }
 
-  // Walk and list buffers, scratch, events and the evaluation stream (after
-  // the tree arrays are on the device, from either build).
+  // Walk buffers, scratch and timing events (after the tree arrays are on the
+  // device, from either build).
   int alloc_walk_buffers() {
     const int64_t n = h.n, ng = h.n_groups(), nw = h.n_work();
     if (dt.nc >= (int64_t(1) << 29))  // the walks' queue entries hold cell id << 3
@@ -382,11 +392,13 @@ struct octgrav_tree : DevAlloc {
                                       " cells; the walks address at most 2^29 - 1");
     int rc;
     void* p;
-    if ((rc = dalloc(&p, (size_t)ng * 16))) return rc;
+    expect((size_t)(ng + 1) * 32 + (size_t)scan_scratch_entries(ng) * 8 +
+           (size_t)std::max(ng, nw) * 8 + (size_t)nw * 32 + (size_t)diag_scratch_entries(n) * 8 + 16 * 256);
+    if ((rc = alloc(&p, (size_t)ng * 16))) return rc;
     wb.cnt = (int32_t*)p;
-    if ((rc = dalloc(&p, (size_t)(ng + 1) * 8))) return rc;
+    if ((rc = alloc(&p, (size_t)(ng + 1) * 8))) return rc;
     wb.c_off = (int64_t*)p;
-    if ((rc = dalloc(&p, (size_t)(ng + 1) * 8))) return rc;
+    if ((rc = alloc(&p, (size_t)(ng + 1) * 8))) return rc;
     wb.l_off = (int64_t*)p;
     if (!ctl) {
       if (alloc_fault() || hipMalloc(&ctl, kCtlBytes) != hipSuccess) {
@@ -406,13 +418,13 @@ struct octgrav_tree : DevAlloc {
         tot_host_dev = nullptr;
       }
     }
-    if ((rc = dalloc(&p, (size_t)scan_scratch_entries(ng) * 8))) return rc;
+    if ((rc = alloc(&p, (size_t)scan_scratch_entries(ng) * 8))) return rc;
     wb.blk = (int64_t*)p;
-    if ((rc = dalloc(&p, (size_t)std::max(ng, nw) * 4))) return rc;
+    if ((rc = alloc(&p, (size_t)std::max(ng, nw) * 4))) return rc;
     wb.ovf_list = (int32_t*)p;
-    if ((rc = dalloc(&p, (size_t)std::max(ng, nw) * 4))) return rc;
+    if ((rc = alloc(&p, (size_t)std::max(ng, nw) * 4))) return rc;
     wb.ovf_list2 = (int32_t*)p;
-    if ((rc = dalloc(&p, (size_t)nw * 32))) return rc;
+    if ((rc = alloc(&p, (size_t)nw * 32))) return rc;
     wb.dpart = (double*)p;
     // Fallback frontier queues: a breadth-first FIFO never holds more than
     // two consecutive levels, hence at most twice the widest level.
@@ -422,25 +434,39 @@ struct octgrav_tree : DevAlloc {
     wb.gq_waves = fallback_waves();
     // At most 4 GiB of queues.
     while (wb.gq_waves > 64 && (int64_t)wb.gq_waves * cap * 4 > (int64_t(1) << 32)) wb.gq_waves >>= 1;
-    if ((rc = dalloc(&p, (size_t)wb.gq_waves * cap * 4))) return rc;
-    wb.gq = (int32_t*)p;
+    wb.gq = nullptr;  // allocated when a later tier first runs (fallback_queues)
     wb.lds_qcap = lds_queue_entries();
     wb.export_lists = 0;
     wb.cap_c = wb.cap_l = 0;
     wb.c_ids = wb.l_ids = nullptr;
-    if ((rc = dalloc(&p, (size_t)diag_scratch_entries(n) * 8))) return rc;
+    if ((rc = alloc(&p, (size_t)diag_scratch_entries(n) * 8))) return rc;
     d_diag_part = (double*)p;
-    if ((rc = dalloc(&p, 4 * 8))) return rc;
+    if ((rc = alloc(&p, 4 * 8))) return rc;
     d_diag = (double*)p;
     for (hipEvent_t& e : ev)
       if (!e && hipEventCreate(&e) != hipSuccess) return fail(OCTGRAV_EHIP, "hipEventCreate failed");
+    gwork.clear();  // built on first use (group_work)
+    dev = true;
+    return OCTGRAV_OK;
+  }
+
+  // The queues of the last walk tier, up to 4 GiB that most handles never use:
+  // allocated before its first launch.
+  int fallback_queues() {
+    if (wb.gq) return OCTGRAV_OK;
+    void* p = nullptr;
+    if (int rc = dalloc(&p, (size_t)wb.gq_waves * wb.gq_cap * 4)) return rc;
+    wb.gq = (int32_t*)p;
+    return OCTGRAV_OK;
+  }
+
+  // The second stream of the pipelined two-pass path and its events.
+  int pipeline_stream() {
     for (hipEvent_t& e : bev)
       if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
         return fail(OCTGRAV_EHIP, "hipEventCreate failed");
     if (!eval_stream && hipStreamCreateWithFlags(&eval_stream, hipStreamNonBlocking) != hipSuccess)
       return fail(OCTGRAV_EHIP, "hipStreamCreate failed");
-    gwork.clear();  // built on first use (group_work)
-    dev = true;
     return OCTGRAV_OK;
   }
 
@@ -500,6 +526,8 @@ struct octgrav_tree : DevAlloc {
 
   int two_pass_pipelined(float theta, float eps, bool plain, float* acc, float* pot) {
     if (int rc = group_work()) return rc;
+    if (int rc = pipeline_stream()) return rc;
+    if (int rc = fallback_queues()) return rc;
     const int64_t ng = h.n_groups();
     const int nb = (int)std::min<int64_t>(kBatches, std::max<int64_t>(1, ng / 256));
     WalkBufs ws = wb;  // slotted lists: no offsets scan between the walk and the evaluation
@@ -534,6 +562,7 @@ struct octgrav_tree : DevAlloc {
   // Count walk + offsets, then sizes the lists (a host read-back only when
   // the current capacity might not suffice), then the write walk.
   int lists_on_device(float theta, bool timed) {
+    if (int rc = fallback_queues()) return rc;
     if (timed) hipEventRecord(ev[0], stream);
     if (launch_walk(dt, wb, theta, 0, stream)) return fail(OCTGRAV_EHIP, "count walk launch failed");
     if (timed) hipEventRecord(ev[1], stream);
@@ -682,6 +711,7 @@ static Path choose_path(uint32_t flags) {
 static int launch_fused(octgrav_tree* t, Path p, float theta, float eps, bool plain,
                         bool do_eval, float* acc, float* pot) {
   t->ctl_clean = false;
+  if (int rc = t->fallback_queues()) return rc;
   int rc = p == Path::FusedWave
                ? launch_walk_eval(t->dt, t->wb, theta, eps, plain, do_eval, acc, pot, t->stream)
                : launch_walk_eval_block(t->dt, t->wb, theta, eps, plain, do_eval, acc, pot, t->stream);
@@ -695,13 +725,17 @@ static int launch_fused(octgrav_tree* t, Path p, float theta, float eps, bool pl
 // finishing kernel again; without page-locked memory they always run.
 // *clean: the counters of b are reset.  Events (timed): ev[4] after the
 // evaluation, ev[5] at the end.
-static int fused_wave_forces(octgrav_tree* t, const WalkBufs& b, double* scratch, bool* clean,
+static int fused_wave_forces(octgrav_tree* t, WalkBufs b, double* scratch, bool* clean,
                              float theta, float eps, bool plain, float* acc, float* pot, bool timed,
                              int64_t* tot8) {
   int64_t* host = t->tot_host_dev;
   int parts = (*clean ? 0 : kWalkInit) | kWalkFirst | (host ? 0 : kWalkRest);
   *clean = false;
   for (;;) {
+    if ((parts & kWalkRest) && !b.gq) {
+      if (int rc = t->fallback_queues()) return rc;
+      b.gq = t->wb.gq;
+    }
     if (launch_walk_eval(t->dt, b, theta, eps, plain, true, acc, pot, t->stream, parts))
       return fail(OCTGRAV_EHIP, "walk+evaluation launch failed");
     if (timed) hipEventRecord(t->ev[4], t->stream);
@@ -804,6 +838,7 @@ int octgrav_forces_ex(octgrav_tree* t, float theta, float eps, float* acc, float
         break;
       }
       t->ctl_clean = false;
+      if (int rc = t->fallback_queues()) return rc;
       if (path != Path::TwoPass) {
         // Fused walk + evaluation: no lists in memory, no host round trip.
         t->wb.export_lists = 0;
@@ -960,6 +995,7 @@ static int lists_to_device(octgrav_tree* t, float theta, uint32_t flags, int64_t
                            int64_t* n_l) {
   t->counts_valid = false;
   t->ctl_clean = false;
+  if (int rc = t->fallback_queues()) return rc;
   int64_t tot[8];
   if (t->learned && (flags & (OCTGRAV_TWO_PASS | OCTGRAV_FUSED_BLOCK)))
     return fail(OCTGRAV_EINVAL, "the learned criterion runs on the fused wave path only");
@@ -1158,6 +1194,7 @@ int octgrav_mac_collect(octgrav_tree* t, float theta_lo, float theta_hi, float e
     // They replace the handle's lists: the counts of the last forces call are gone.
     t->counts_valid = false;
     t->ctl_clean = false;
+    if (int rc = t->fallback_queues()) return rc;
     WalkBufs saved = t->wb;
     t->wb.band = 1;
     t->wb.band_hi2 = theta_hi * theta_hi;
@@ -1282,6 +1319,7 @@ static int mac_trace_impl(octgrav_tree* t, float theta, const int32_t* sel, int6
   if (!off || !n_out || !fell_back) return fail(OCTGRAV_EINVAL, "off, n_out and fell_back must be non-NULL");
   try {
     t->counts_valid = false;
+    if (int rc = t->fallback_queues()) return rc;
     const int64_t ng = t->h.n_groups();
     if (!sel) n_sel = ng;
     t->wb.export_lists = 0;

@@ -776,26 +776,16 @@ __global__ __launch_bounds__(kT) void counts_kernel(const int32_t* __restrict__ 
   }
 }
 
-// Scratch allocations of one build: fresh ones freed on every exit, or slots
-// of a pool kept for the next build.
+// Scratch allocations of one build: cut from an arena freed on every exit, or
+// slots of a pool kept for the next build.
 struct Scratch {
   SeqPool* pool = nullptr;
-  std::vector<void*> p;
-  explicit Scratch(SeqPool* sp) : pool(sp) {}
-  ~Scratch() {
-    for (void* q : p) hipFree(q);
-  }
+  Arena arena;
+  explicit Scratch(SeqPool* sp, size_t expect = 0) : pool(sp) { arena.expect(expect); }
   template <typename T>
   T* get(int64_t count) {
-    const size_t bytes = std::max<size_t>((size_t)count * sizeof(T), 256);
-    if (pool) return static_cast<T*>(pool->take(bytes));
-    void* q = nullptr;
-    if (hipMalloc(&q, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    p.push_back(q);
-    return static_cast<T*>(q);
+    const size_t bytes = (size_t)count * sizeof(T);
+    return static_cast<T*>(pool ? pool->take(bytes) : arena.take(bytes));
   }
 };
 
@@ -818,6 +808,30 @@ int exclusive_scan(const T* in, T* out, int64_t n, T init, Op op, Scratch& S, hi
 }
 
 }  // namespace
+
+void* Arena::take(size_t bytes) {
+  bytes = (std::max<size_t>(bytes, 1) + 255) & ~size_t(255);
+  if (bytes > left) {
+    const size_t want = std::max(bytes, next);
+    void* q = nullptr;
+    if (hipMalloc(&q, want) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    chunks.push_back(q);
+    at = static_cast<char*>(q);
+    left = want;
+    next = 0;
+  }
+  void* p = at;
+  at += bytes;
+  left -= bytes;
+  return p;
+}
+
+Arena::~Arena() {
+  for (void* q : chunks) hipFree(q);
+}
 
 void* SeqPool::take(size_t bytes) {
   bytes = std::max<size_t>(bytes, 256);
@@ -862,8 +876,11 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     pools->outer.rewind();
     pools->cells.rewind();
   }
-  Scratch S(pools ? &pools->outer : nullptr);
-  Scratch CS(pools ? &pools->cells : nullptr);
+  // About what the arrays below add up to (the sort's and the scans' scratch
+  // included); what a build needs beyond that is allocated on its own.
+  Scratch S(pools ? &pools->outer : nullptr, (size_t)n * 96 + (1 << 20));
+  Scratch CS(pools ? &pools->cells : nullptr, (size_t)n * 48 + (1 << 13));
+  alloc.expect((size_t)n * 24 + 1024);  // order, particles, inverse order
   auto fail = [&](const char* what) {
     err = what;
     return -1;
@@ -1054,6 +1071,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
 
   double* box = nullptr;
   double* mp64 = nullptr;
+  alloc.expect((size_t)nc * 376 + (size_t)n / 2 + 8192);  // the arrays per cell, group and item
   if (!A((void**)&box, (size_t)nc * 48) || !A((void**)&mp64, (size_t)nc * 80))
     return fail("device allocation failed");
   moments_kernel<true><<<blocks(nc), kT, 0, s>>>(C, part, 0, nc, box, mp64);
