@@ -782,61 +782,110 @@ __global__ void fused_init_kernel(WalkBufs B) {
 // page-locked copy, and the counters reset for the next call.  Replaces an
 // initial reset, a totals kernel, two diagnostics kernels over the particles
 // (21 + 5 us at 2^20, bound by the gather of the masses) and a copy.
-constexpr int kFinT = 256, kFinBlocks = 256;
+constexpr int kFinT = 1024, kFinBlocks = 256;
 struct FinRec {
   double d[4];
   int64_t t[4];
 };
 
-__device__ __forceinline__ void block_sum_rec(FinRec& r, FinRec* sh) {
-  sh[threadIdx.x] = r;
-  __syncthreads();
-  for (int o = kFinT / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o)
-      for (int k = 0; k < 4; ++k) {
-        sh[threadIdx.x].d[k] += sh[threadIdx.x + o].d[k];
-        sh[threadIdx.x].t[k] += sh[threadIdx.x + o].t[k];
-      }
-    __syncthreads();
+// Sum over the wave of four values per lane; lane l < 4 gets that of value
+// ((l & 1) << 1) | (l >> 1).
+template <typename V>
+__device__ __forceinline__ V wave_sum4(const V* d, int lane) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  V k0 = b0 ? d[2] : d[0], k1 = b0 ? d[3] : d[1];
+  k0 += __shfl_xor(b0 ? d[0] : d[2], 1);
+  k1 += __shfl_xor(b0 ? d[1] : d[3], 1);
+  V v = b1 ? k1 : k0;
+  v += __shfl_xor(b1 ? k0 : k1, 2);
+#pragma unroll
+  for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+struct FinShared {
+  double d[4][kFinT / 64];
+  int64_t t[4][kFinT / 64];
+};
+
+// Sum over the block, in thread t < 4 for components t of both.
+__device__ __forceinline__ void block_sum_rec(FinRec& r, double* d, int64_t* n, FinShared& sh) {
+  const int t = threadIdx.x, lane = t & 63;
+  const double sd = wave_sum4(r.d, lane);
+  const int64_t st = wave_sum4((const long long*)r.t, lane);
+  if (lane < 4) {
+    const int k = ((lane & 1) << 1) | (lane >> 1);
+    sh.d[k][t >> 6] = sd;
+    sh.t[k][t >> 6] = st;
   }
-  r = sh[0];
+  __syncthreads();
+  if (t < 4) {
+    *d = 0.0;
+    *n = 0;
+    for (int w = 0; w < kFinT / 64; ++w) {
+      *d += sh.d[t][w];
+      *n += sh.t[t][w];
+    }
+  }
   __syncthreads();
 }
 
 __global__ __launch_bounds__(kFinT) void finish_kernel(DevTree T, WalkBufs B, FinRec* rec,
                                                        double* diag, int64_t* host, int last) {
-  __shared__ FinRec sh[kFinT];
+  __shared__ FinShared sh;
   __shared__ int is_last;
   const int t = threadIdx.x, nb = gridDim.x;
   const int64_t per = (T.nw + nb - 1) / nb;
   const int64_t lo = blockIdx.x * per, hi = lo + per < T.nw ? lo + per : T.nw;
   FinRec r{};
-  for (int64_t i = lo + t; i < hi; i += kFinT) {
-    const int2 wk = reinterpret_cast<const int2*>(T.wwork)[i];
-    const double2* dp = reinterpret_cast<const double2*>(B.dpart + 4 * i);
-    const double2 a = dp[0], b = dp[1];
-    const int4 c = reinterpret_cast<const int4*>(B.cnt)[wk.x];
-    const int64_t sz = T.ginfo[4 * (int64_t)wk.x + 1];
-    r.d[0] += a.x;
-    r.d[1] += a.y;
-    r.d[2] += b.x;
-    r.d[3] += b.y;
-    if (wk.y == 0) {
-      r.t[0] += c.x;
-      r.t[1] += c.y;
-      r.t[2] += sz * c.x;
-      r.t[3] += sz * c.z;
+  for (int64_t i0 = lo + t; i0 < hi; i0 += 4 * kFinT) {  // four items' loads at a time
+    int2 wk[4];
+    double2 a[4], b[4];
+    int4 c[4];
+    int sz[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t i = i0 + q * kFinT < hi ? i0 + q * kFinT : hi - 1;
+      wk[q] = reinterpret_cast<const int2*>(T.wwork)[i];
+      const double2* dp = reinterpret_cast<const double2*>(B.dpart + 4 * i);
+      a[q] = dp[0];
+      b[q] = dp[1];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      c[q] = reinterpret_cast<const int4*>(B.cnt)[wk[q].x];
+      sz[q] = T.ginfo[4 * (int64_t)wk[q].x + 1];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (i0 + q * kFinT >= hi) break;
+      r.d[0] += a[q].x;
+      r.d[1] += a[q].y;
+      r.d[2] += b[q].x;
+      r.d[3] += b[q].y;
+      if (wk[q].y == 0) {
+        r.t[0] += c[q].x;
+        r.t[1] += c[q].y;
+        r.t[2] += (int64_t)sz[q] * c[q].x;
+        r.t[3] += (int64_t)sz[q] * c[q].z;
+      }
     }
   }
-  block_sum_rec(r, sh);
+  double sd;
+  int64_t st;
+  block_sum_rec(r, &sd, &st, sh);
   if (nb > 1) {
     if (t < 4) {
-      __hip_atomic_store(&rec[blockIdx.x].d[t], r.d[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&rec[blockIdx.x].t[t], r.t[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&rec[blockIdx.x].d[t], sd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&rec[blockIdx.x].t[t], st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();  // (also waits for the stores)
-    if (t == 0)
-      is_last = __hip_atomic_fetch_add(B.ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == nb - 1;
+    // The record is written and read by agent-scope atomics, which do not rest
+    // in this XCD's L2; thread 0's wave wrote it and waits for that, so the ticket
+    // needs no release (which would write the whole L2 back: 5 us).
+    if (t == 0) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      is_last = __hip_atomic_fetch_add(B.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nb - 1;
+    }
     __syncthreads();
     if (!is_last) return;
     r = FinRec{};
@@ -845,15 +894,15 @@ __global__ __launch_bounds__(kFinT) void finish_kernel(DevTree T, WalkBufs B, Fi
         r.d[k] = __hip_atomic_load(&rec[t].d[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         r.t[k] = __hip_atomic_load(&rec[t].t[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-    block_sum_rec(r, sh);
+    block_sum_rec(r, &sd, &st, sh);
   }
   const int left = *B.ovf_count;
   if (t < 4) {
-    diag[t] = r.d[t];
-    B.tot[t] = r.t[t];
+    diag[t] = sd;
+    B.tot[t] = st;
   }
   if (host) {
-    if (t < 4) host[t] = r.t[t];
+    if (t < 4) host[t] = st;
     else if (t < 8) host[t] = B.tot[t];
     else if (t == 8) host[t] = left;
   }
@@ -922,9 +971,11 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
 
 int launch_finish(const DevTree& T, const WalkBufs& B, double* scratch, double* diag, int64_t* host,
                   bool last, void* stream) {
-  // One block up to 1024 items (four per thread), then a block per 256.
+  // One block up to four items per thread (4.2 us at 79 items, 4.9 at 1042, 23 at
+  // 16300); more blocks need the second level, a ticket and the records' way
+  // through memory (about 6 us).
   static_assert(kFinBlocks <= kFinT, "the last block reads one record per thread");
-  const int nb = T.nw <= 1024 ? 1 : (int)std::min<int64_t>(kFinBlocks, (T.nw + kFinT - 1) / kFinT);
+  const int nb = T.nw <= 4 * kFinT ? 1 : (int)std::min<int64_t>(kFinBlocks, (T.nw + kFinT - 1) / kFinT);
   finish_kernel<<<nb, kFinT, 0, (hipStream_t)stream>>>(T, B, reinterpret_cast<FinRec*>(scratch), diag,
                                                        host, last);
   return hipGetLastError() == hipSuccess ? 0 : -1;
