@@ -72,6 +72,22 @@ __global__ void bbox_kernel(const float* __restrict__ pos, const float* __restri
   if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = sh[threadIdx.x][0];
 }
 
+// The host's root cube of a bounding box (FP64, the same operations): cube =
+// corner xyz, side, grid step, 1 / step.
+__device__ void root_cube_of(const double lo[3], const double hi[3], double* __restrict__ cube) {
+#pragma clang fp contract(off)
+  const double e1 = hi[1] - lo[1], e2 = hi[2] - lo[2], e0 = hi[0] - lo[0];
+  const double e12 = e1 < e2 ? e2 : e1;
+  const double ext = e0 < e12 ? e12 : e0;
+  int e = 1;
+  if (ext > 0) (void)frexp(ext, &e);
+  const double side = ext > 0 ? ldexp(1.0, e) : 1.0;
+  for (int k = 0; k < 3; ++k) cube[k] = (lo[k] + hi[k]) * 0.5 - 0.5 * side;
+  cube[3] = side;
+  cube[4] = ldexp(side, -kMaxDepth);
+  cube[5] = ldexp(1.0 / side, kMaxDepth);
+}
+
 // Root cube from the bounding-box partials with the host's rules (min / max
 // keeping the earlier of equal values, combined over contiguous ranges in
 // index order; the cube of the largest extent rounded up to a power of two,
@@ -105,16 +121,7 @@ __global__ __launch_bounds__(kT) void root_kernel(const float* __restrict__ part
     lo[k] = sh[k][0];
     hi[k] = sh[3 + k][0];
   }
-  const double e1 = hi[1] - lo[1], e2 = hi[2] - lo[2], e0 = hi[0] - lo[0];
-  const double e12 = e1 < e2 ? e2 : e1;
-  const double ext = e0 < e12 ? e12 : e0;
-  int e = 1;
-  if (ext > 0) (void)frexp(ext, &e);
-  const double side = ext > 0 ? ldexp(1.0, e) : 1.0;
-  for (int k = 0; k < 3; ++k) cube[k] = (lo[k] + hi[k]) * 0.5 - 0.5 * side;
-  cube[3] = side;
-  cube[4] = ldexp(side, -kMaxDepth);
-  cube[5] = ldexp(1.0 / side, kMaxDepth);
+  root_cube_of(lo, hi, cube);
 }
 
 // The host's grid coordinate: floor, then exact against the grid planes.
@@ -141,12 +148,10 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v) {
 // cube: corner xyz, side, grid step, 1 / step (root_kernel).  Also packs
 // each particle as (x, y, z, m) in input order, so that the gather after the
 // sort reads one aligned 16-byte record per particle.
-__global__ void keys_kernel(const float* __restrict__ pos, const float* __restrict__ mass,
-                            int64_t n, const double* __restrict__ cube,
-                            uint64_t* __restrict__ key, int32_t* __restrict__ idx,
-                            float4* __restrict__ packed) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i >= n) return;
+__device__ __forceinline__ void particle_key(const float* __restrict__ pos,
+                                             const float* __restrict__ mass, int64_t i,
+                                             const double* cube, uint64_t* __restrict__ key,
+                                             int32_t* __restrict__ idx, float4* __restrict__ packed) {
   const double step = cube[4], inv = cube[5];
   const float x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
   const uint32_t u0 = grid_coord((double)x, cube[0], step, inv);
@@ -155,6 +160,15 @@ __global__ void keys_kernel(const float* __restrict__ pos, const float* __restri
   key[i] = spread3(u0) | spread3(u1) << 1 | spread3(u2) << 2;
   idx[i] = (int32_t)i;
   packed[i] = make_float4(x, y, z, mass[i]);
+}
+
+__global__ void keys_kernel(const float* __restrict__ pos, const float* __restrict__ mass,
+                            int64_t n, const double* __restrict__ cube,
+                            uint64_t* __restrict__ key, int32_t* __restrict__ idx,
+                            float4* __restrict__ packed) {
+  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
+  if (i >= n) return;
+  particle_key(pos, mass, i, cube, key, idx, packed);
 }
 
 struct Cells {
@@ -622,28 +636,24 @@ __global__ __launch_bounds__(kT) void moments_kernel(Cells C, const float4* __re
 }
 
 
-// FP32 images of every cell: topology, boundary (centre of the tight box,
-// side = largest extent; the device copy carries the leaf flag in the side's
-// sign bit), walk record, moments, depth, and the learned criterion's cell features
-// with the host's FP32 expressions.
-__global__ void images_kernel(Cells C, int64_t nc, const double* __restrict__ box,
-                              const double* __restrict__ mp64, int4* __restrict__ topo,
-                              float4* __restrict__ geo_host, float4* __restrict__ geo,
-                              float4* __restrict__ wrec, float4* __restrict__ mp,
-                              float4* __restrict__ fcell, int32_t* __restrict__ depth,
-                              int32_t* __restrict__ leaf_part) {
+// Arrays of FP32 images per cell (images_kernel).
+struct Images {
+  int4* topo;
+  float4 *geo_host, *geo, *wrec, *mp, *fcell;
+  int32_t* depth;
+};
+
+// FP32 images of one cell: topology, boundary (centre of the tight box, side =
+// largest extent; the device copy carries the leaf flag in the side's sign
+// bit), walk record, moments, depth, and the learned criterion's cell
+// features with the host's FP32 expressions.
+__device__ __forceinline__ void cell_image(const Cells& C, int64_t c, const double* __restrict__ box,
+                                           const double* __restrict__ mp64, const Images& I) {
 #pragma clang fp contract(off)
-  __shared__ int sh[kT / 64];
-  const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
-  // the block's leaf count (one store per block: same-address atomics
-  // from every wave serialise)
-  const int nl = block_sum(c < nc && C.nc[c < nc ? c : 0] == 0 ? 1 : 0, sh);
-  if (threadIdx.x == 0) leaf_part[blockIdx.x] = nl;
-  if (c >= nc) return;
   const int4 tp = make_int4(C.fc[c], C.nc[c], C.first[c], C.n[c]);
-  topo[c] = tp;
+  I.topo[c] = tp;
   const int32_t dc = C.depth[c];
-  depth[c] = dc;
+  I.depth[c] = dc;
   const double* bx = box + 6 * c;
   double l = 0;
   float g[3];
@@ -652,18 +662,18 @@ __global__ void images_kernel(Cells C, int64_t nc, const double* __restrict__ bo
     l = hmax(l, bx[3 + k] - bx[k]);
   }
   const float lf = (float)l;
-  geo_host[c] = make_float4(g[0], g[1], g[2], lf);
+  I.geo_host[c] = make_float4(g[0], g[1], g[2], lf);
   const float4 gd = make_float4(g[0], g[1], g[2], tp.y == 0 ? -lf : lf);
-  geo[c] = gd;
-  wrec[2 * c] = gd;
-  wrec[2 * c + 1] = make_float4(__int_as_float(tp.x), __int_as_float(tp.y), __int_as_float(tp.z),
-                                __int_as_float(tp.w));
+  I.geo[c] = gd;
+  I.wrec[2 * c] = gd;
+  I.wrec[2 * c + 1] = make_float4(__int_as_float(tp.x), __int_as_float(tp.y), __int_as_float(tp.z),
+                                  __int_as_float(tp.w));
   const double* q = mp64 + 10 * c;
   const float m[10] = {(float)q[1], (float)q[2], (float)q[3], (float)q[0], (float)q[4],
                        (float)q[5], (float)q[6], (float)q[7], (float)q[8], (float)q[9]};
-  mp[3 * c] = make_float4(m[0], m[1], m[2], m[3]);
-  mp[3 * c + 1] = make_float4(m[4], m[5], m[6], m[7]);
-  mp[3 * c + 2] = make_float4(m[8], m[9], 0.0f, 0.0f);
+  I.mp[3 * c] = make_float4(m[0], m[1], m[2], m[3]);
+  I.mp[3 * c + 1] = make_float4(m[4], m[5], m[6], m[7]);
+  I.mp[3 * c + 2] = make_float4(m[8], m[9], 0.0f, 0.0f);
   const float mtot = (float)mp64[0];
   const float M = m[3];
   const float qn = sqrtf((m[4] * m[4] + m[5] * m[5] + m[6] * m[6]) +
@@ -673,11 +683,67 @@ __global__ void images_kernel(Cells C, int64_t nc, const double* __restrict__ bo
     const float d = m[k] - g[k];
     s2 += d * d;
   }
-  fcell[2 * c] = make_float4(log10f(M / mtot) / 3.0f, qn / (M * lf * lf),
-                             (float)(bx[3] - bx[0]) / lf, (float)(bx[4] - bx[1]) / lf);
-  fcell[2 * c + 1] = make_float4((float)(bx[5] - bx[2]) / lf,
-                                 log2f(1.0f + (float)dc) / log2f(22.0f), sqrtf(s2) / lf,
-                                 0.0f);
+  I.fcell[2 * c] = make_float4(log10f(M / mtot) / 3.0f, qn / (M * lf * lf),
+                               (float)(bx[3] - bx[0]) / lf, (float)(bx[4] - bx[1]) / lf);
+  I.fcell[2 * c + 1] = make_float4((float)(bx[5] - bx[2]) / lf,
+                                   log2f(1.0f + (float)dc) / log2f(22.0f), sqrtf(s2) / lf, 0.0f);
+}
+
+// cell_image of every cell, and the leaves of each block's cells.
+__global__ void images_kernel(Cells C, int64_t nc, const double* __restrict__ box,
+                              const double* __restrict__ mp64, Images I,
+                              int32_t* __restrict__ leaf_part) {
+  __shared__ int sh[kT / 64];
+  const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
+  // the block's leaf count (one store per block: same-address atomics
+  // from every wave serialise)
+  const int nl = block_sum(c < nc && C.nc[c < nc ? c : 0] == 0 ? 1 : 0, sh);
+  if (threadIdx.x == 0) leaf_part[blockIdx.x] = nl;
+  if (c < nc) cell_image(C, c, box, mp64, I);
+}
+
+__device__ __forceinline__ bool is_group(const Cells& C, int64_t c, int n_group) {
+  const bool cand = C.n[c] <= n_group || C.nc[c] == 0;
+  const bool top = c == 0 || C.n[C.parent[c]] > n_group;
+  return cand && top;
+}
+
+// Arrays per group.
+struct Groups {
+  int32_t* cell;
+  int4* info;
+  float4* box;
+};
+
+// Writes group g, cell c; returns its chunks per item class.
+__device__ __forceinline__ int4 write_group(const Cells& C, int64_t g, int32_t c,
+                                            const double* __restrict__ box, const Groups& G) {
+  G.cell[g] = c;
+  G.info[g] = make_int4(C.first[c], C.n[c], c, 0);
+  const double* bx = box + 6 * (int64_t)c;
+  G.box[2 * g] = make_float4((float)bx[0], (float)bx[1], (float)bx[2], 0.0f);
+  G.box[2 * g + 1] = make_float4((float)bx[3], (float)bx[4], (float)bx[5], 0.0f);
+  const int32_t rest = C.n[c] % kChunk;
+  int32_t k[kItemClasses] = {0, 0, 0, 0};
+  k[item_class(kChunk)] = C.n[c] / kChunk;
+  for (int q = 0; q < kItemClasses; ++q) k[q] += rest > 0 && item_class(rest) == q;
+  return make_int4(k[0], k[1], k[2], k[3]);
+}
+
+// Work items of group g of n particles, in group order (work) and class by
+// class (wwork); p and t: chunks of each class in the groups before, and in all.
+__device__ __forceinline__ void write_items(int64_t g, int32_t n, int4 p, int4 t,
+                                            int2* __restrict__ work, int2* __restrict__ wwork) {
+  const int32_t at = p.x + p.y + p.z + p.w;
+  const int32_t begin[kItemClasses] = {p.x, t.x + p.y, t.x + t.y + p.z, t.x + t.y + t.z + p.w};
+  for (int32_t k = 0, off = 0; off < n; ++k, off += kChunk) {
+    const int2 w = make_int2((int32_t)g, off);
+    const int c = item_class(n - off < kChunk ? n - off : kChunk);
+    work[at + k] = w;
+    // a group's full chunks come before its rest, which may be of the same class
+    for (int q = 0; q < kItemClasses; ++q)
+      if (c == q) wwork[begin[q] + (q == item_class(kChunk) ? k : 0)] = w;
+  }
 }
 
 // Groups: the maximal cells with at most n_group particles, or leaves; their
@@ -691,9 +757,7 @@ __global__ void group_mark_kernel(Cells C, int64_t nc, int n_group, int32_t* __r
   if (c > nc) return;
   nchunk[c] = make_int4(0, 0, 0, 0);
   if (c == nc) return;
-  const bool cand = C.n[c] <= n_group || C.nc[c] == 0;
-  const bool top = c == 0 || C.n[C.parent[c]] > n_group;
-  if (cand && top) at[C.first[c]] = (int32_t)c;
+  if (is_group(C, c, n_group)) at[C.first[c]] = (int32_t)c;
 }
 
 // Group-start flags of the n particles, and a 0 at f[n] for the scan.
@@ -705,23 +769,11 @@ __global__ void flag_kernel(const int32_t* __restrict__ at, int64_t n, int32_t* 
 
 __global__ void group_fill_kernel(const int32_t* __restrict__ at, const int32_t* __restrict__ f,
                                   const int32_t* __restrict__ pre, int64_t n, Cells C,
-                                  const double* __restrict__ box, int32_t* __restrict__ groups,
-                                  int4* __restrict__ ginfo, float4* __restrict__ gbox,
+                                  const double* __restrict__ box, Groups G,
                                   int4* __restrict__ nchunk) {
   const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (i >= n || !f[i]) return;
-  const int64_t g = pre[i];
-  const int32_t c = at[i];
-  groups[g] = c;
-  ginfo[g] = make_int4(C.first[c], C.n[c], c, 0);
-  const double* bx = box + 6 * (int64_t)c;
-  gbox[2 * g] = make_float4((float)bx[0], (float)bx[1], (float)bx[2], 0.0f);
-  gbox[2 * g + 1] = make_float4((float)bx[3], (float)bx[4], (float)bx[5], 0.0f);
-  const int32_t rest = C.n[c] % kChunk;
-  int32_t k[kItemClasses] = {0, 0, 0, 0};
-  k[item_class(kChunk)] = C.n[c] / kChunk;
-  for (int q = 0; q < kItemClasses; ++q) k[q] += rest > 0 && item_class(rest) == q;
-  nchunk[g] = make_int4(k[0], k[1], k[2], k[3]);
+  nchunk[pre[i]] = write_group(C, pre[i], at[i], box, G);
 }
 
 struct Int4Sum {
@@ -730,24 +782,13 @@ struct Int4Sum {
   }
 };
 
-// Work items in group order (work) and class by class (wwork); pre and all:
-// chunks of each class in the groups before, and in all groups.
+// Work items of every group; pre and all: chunks of each class in the groups
+// before, and in all groups.
 __global__ void work_kernel(const int4* __restrict__ pre, const int4* __restrict__ all,
                             const int4* __restrict__ ginfo, const int32_t* __restrict__ ngp,
                             int2* __restrict__ work, int2* __restrict__ wwork) {
   const int64_t g = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (g >= *ngp) return;
-  const int4 p = pre[g], t = *all;
-  const int32_t n = ginfo[g].y, at = p.x + p.y + p.z + p.w;
-  const int32_t begin[kItemClasses] = {p.x, t.x + p.y, t.x + t.y + p.z, t.x + t.y + t.z + p.w};
-  for (int32_t k = 0, off = 0; off < n; ++k, off += kChunk) {
-    const int2 w = make_int2((int32_t)g, off);
-    const int c = item_class(n - off < kChunk ? n - off : kChunk);
-    work[at + k] = w;
-    // a group's full chunks come before its rest, which may be of the same class
-    for (int q = 0; q < kItemClasses; ++q)
-      if (c == q) wwork[begin[q] + (q == item_class(kChunk) ? k : 0)] = w;
-  }
+  if (g < *ngp) write_items(g, ginfo[g].y, pre[g], *all, work, wwork);
 }
 
 // The build's scalars the host needs, gathered in one place on the device so
@@ -758,6 +799,235 @@ struct BuildInfo {
   int32_t bad;     // input check (bbox_kernel)
   int32_t ng, nw, leaves;
 };
+
+// ---- small trees: one block does in two launches (around the sort) what the
+// kernels above do in about 50, which for a few thousand particles are all
+// launch and latency.  The same functions and orders, so the same tree.
+// Rebuild of a Plummer sphere, many launches against one block, in us:
+//   300: 176 / 74    1000: 187 / 88    3000: 210 / 127    5003: 237 / 172
+//   8192: 237 / 215  12000: 243 / 275  16384: 242 / 341
+// one block's time grows by 17 us per 1000 particles, so the line lies at the
+// largest power of two (of keys in LDS) before the two meet.
+constexpr int kSmallN = 8192;  // sorted keys in LDS: 64 KB
+constexpr int kSmallT = 1024;
+
+// Exclusive prefix of v over the block in thread order, and the block total.
+__device__ int small_exclusive(int v, int* total, int* sh) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int incl = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(incl, o);
+    if (lane >= o) incl += t;
+  }
+  if (lane == 63) sh[w] = incl;
+  __syncthreads();
+  int base = 0, tot = 0;
+  for (int k = 0; k < kSmallT / 64; ++k) {
+    base += k < w ? sh[k] : 0;
+    tot += sh[k];
+  }
+  __syncthreads();
+  *total = tot;
+  return base + incl - v;
+}
+
+// Input check, root cube and keys.
+__global__ __launch_bounds__(kSmallT) void small_keys_kernel(const float* __restrict__ pos,
+                                                             const float* __restrict__ mass, int n,
+                                                             BuildInfo* __restrict__ info,
+                                                             uint64_t* __restrict__ key,
+                                                             int32_t* __restrict__ idx,
+                                                             float4* __restrict__ packed) {
+  __shared__ float sh[kSmallT / 64][6];
+  __shared__ int bad[kSmallT / 64];
+  __shared__ double cube[6];
+  const int t = threadIdx.x;
+  float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  int bd = 0;
+  for (int i = t; i < n; i += kSmallT) {
+    for (int k = 0; k < 3; ++k) {
+      const float x = pos[3 * i + k];
+      v[k] = x < v[k] ? x : v[k];
+      v[3 + k] = v[3 + k] < x ? x : v[3 + k];
+      if (!(fabsf(x) < 0x1p60f)) bd |= 1;  // also catches NaN
+    }
+    const float m = mass[i];
+    if (!(m > 0.0f) || !(m < INFINITY)) bd |= 2;
+  }
+  for (int o = 32; o > 0; o >>= 1)
+    for (int k = 0; k < 6; ++k) {
+      const float b = __shfl_xor(v[k], o);
+      v[k] = k < 3 ? (b < v[k] ? b : v[k]) : (v[k] < b ? b : v[k]);
+    }
+  for (int o = 32; o > 0; o >>= 1) bd |= __shfl_xor(bd, o);
+  if ((t & 63) == 0) {
+    for (int k = 0; k < 6; ++k) sh[t >> 6][k] = v[k];
+    bad[t >> 6] = bd;
+  }
+  __syncthreads();
+  if (t == 0) {
+    double lo[3], hi[3];
+    int b = 0;
+    for (int k = 0; k < 3; ++k) {
+      float a = sh[0][k], c = sh[0][3 + k];
+      for (int w = 1; w < kSmallT / 64; ++w) {
+        a = sh[w][k] < a ? sh[w][k] : a;
+        c = c < sh[w][3 + k] ? sh[w][3 + k] : c;
+      }
+      lo[k] = a;
+      hi[k] = c;
+    }
+    for (int w = 0; w < kSmallT / 64; ++w) b |= bad[w];
+    root_cube_of(lo, hi, cube);
+    for (int k = 0; k < 6; ++k) info->cube[k] = cube[k];
+    info->bad = b;
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += kSmallT) particle_key(pos, mass, i, cube, key, idx, packed);
+}
+
+// Everything after the sort.  Cell, image, group and item arrays hold cap
+// cells and n groups; more than cap cells are flagged (lv[].overflow) and the
+// host builds level by level.
+__global__ __launch_bounds__(kSmallT) void small_tree_kernel(
+    Cells C, const uint64_t* __restrict__ key, const int32_t* __restrict__ perm,
+    const float4* __restrict__ packed, int n, int n_leaf, int n_group, int cap,
+    float4* __restrict__ part, int32_t* __restrict__ iperm, double* box, double* mp64, Images I,
+    Groups G, int32_t* at, int4* nchunk, int2* __restrict__ work, int2* __restrict__ wwork,
+    BuildInfo* __restrict__ info) {
+  __shared__ uint64_t skey[kSmallN];
+  __shared__ int sh[kSmallT / 64];
+  __shared__ int lbegs[kMaxDepth + 3];
+  const int t = threadIdx.x;
+  for (int i = t; i < n; i += kSmallT) {
+    skey[i] = key[i];
+    at[i] = -1;
+    const int32_t p = perm[i];
+    part[i] = packed[p];
+    iperm[p] = i;
+  }
+  if (t == 0) {
+    C.first[0] = 0;
+    C.n[0] = n;
+    C.depth[0] = 0;
+    C.parent[0] = -1;
+    C.fc[0] = -1;
+    C.nc[0] = 0;
+  }
+  __syncthreads();
+
+  // Subdivision: eight lanes per cell, as the level kernels.
+  int beg = 0, end = 1, levels = 0;
+  for (int L = 0; L <= kMaxDepth && beg < end; ++L) {
+    if (t == 0) lbegs[L] = beg;
+    int carry = 0;
+    for (int base = beg; base < end; base += kSmallT / 8) {
+      const int j = base + t / 8, d = t & 7;
+      const bool valid = j < end;
+      int a = 0, b = 0;
+      bool split = false;
+      if (valid) {
+        a = C.first[j];
+        b = a + C.n[j];
+        split = !(b - a <= n_leaf || L == kMaxDepth);
+      }
+      int l = a;
+      if (split && d > 0) {
+        const int sh3 = 3 * (kMaxDepth - 1 - L);
+        int h = b;
+        while (l < h) {
+          const int mid = l + ((h - l) >> 1);
+          if ((int)((skey[mid] >> sh3) & 7) < d) l = mid + 1;
+          else h = mid;
+        }
+      }
+      const int nx = __shfl_down(l, 1, 8);
+      const int hi = d == 7 ? b : nx;
+      const bool child = split && hi > l;
+      int k, before, step;
+      octant_counts(child, &k, &before);
+      const int ex = __shfl(small_exclusive(d == 0 && valid ? k : 0, &step, sh), (t & 63) & ~7);
+      if (end + carry + step > cap) {  // uniform
+        if (t == 0) info->lv[L].overflow = 1;
+        return;
+      }
+      const int first = end + carry + ex;
+      if (d == 0 && valid && k > 0) {
+        C.fc[j] = first;
+        C.nc[j] = k;
+      }
+      if (child) {
+        const int ch = first + before;
+        C.first[ch] = l;
+        C.n[ch] = hi - l;
+        C.depth[ch] = L + 1;
+        C.parent[ch] = j;
+        C.fc[ch] = -1;
+        C.nc[ch] = 0;
+      }
+      carry += step;
+    }
+    if (t == 0) info->lv[L] = Level{beg, end, carry, 0, 0};
+    beg = end;
+    end += carry;
+    levels = L + 1;
+    __syncthreads();
+  }
+  const int nc = beg;
+  if (t >= levels && t < kMaxDepth + 2) info->lv[t] = Level{nc, nc, 0, 0, 0};
+  if (t == 0) lbegs[levels] = nc;
+  __syncthreads();
+
+  // Boxes and moments: the leaves, then level by level upwards (the deepest
+  // level holds only leaves).
+  for (int c = t; c < nc; c += kSmallT) cell_moments<true>(C, part, c, box, mp64);
+  __syncthreads();
+  for (int L = levels - 2; L >= 0; --L) {
+    for (int c = lbegs[L] + t; c < lbegs[L + 1]; c += kSmallT) cell_moments<false>(C, part, c, box, mp64);
+    __syncthreads();
+  }
+
+  // Images, leaves and group marks.
+  int nl = 0;
+  for (int c = t; c < nc; c += kSmallT) {
+    cell_image(C, c, box, mp64, I);
+    nl += C.nc[c] == 0;
+    if (is_group(C, c, n_group)) at[C.first[c]] = c;
+  }
+  int leaves;
+  small_exclusive(nl, &leaves, sh);  // (its barriers also order the marks)
+
+  // Groups in particle order, then their work items.
+  const int per = (n + kSmallT - 1) / kSmallT;
+  const int i0 = min(n, t * per), i1 = min(n, i0 + per);
+  int k = 0, ng;
+  for (int i = i0; i < i1; ++i) k += at[i] >= 0;
+  int g = small_exclusive(k, &ng, sh);
+  for (int i = i0; i < i1; ++i)
+    if (at[i] >= 0) {
+      nchunk[g] = write_group(C, g, at[i], box, G);
+      ++g;
+    }
+  __syncthreads();
+  const int gper = (ng + kSmallT - 1) / kSmallT;
+  const int g0 = min(ng, t * gper), g1 = min(ng, g0 + gper);
+  int4 s = make_int4(0, 0, 0, 0), p, tot;
+  const Int4Sum add;
+  for (int i = g0; i < g1; ++i) s = add(s, nchunk[i]);
+  p.x = small_exclusive(s.x, &tot.x, sh);
+  p.y = small_exclusive(s.y, &tot.y, sh);
+  p.z = small_exclusive(s.z, &tot.z, sh);
+  p.w = small_exclusive(s.w, &tot.w, sh);
+  for (int i = g0; i < g1; ++i) {
+    write_items(i, G.info[i].y, p, tot, work, wwork);
+    p = add(p, nchunk[i]);
+  }
+  if (t == 0) {
+    info->ng = ng;
+    info->nw = tot.x + tot.y + tot.z + tot.w;
+    info->leaves = leaves;
+  }
+}
 
 // The group and work-item counts and the leaf count (sum of the images
 // kernel's nb per-block counts).
@@ -880,7 +1150,6 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   // included); what a build needs beyond that is allocated on its own.
   Scratch S(pools ? &pools->outer : nullptr, (size_t)n * 96 + (1 << 20));
   Scratch CS(pools ? &pools->cells : nullptr, (size_t)n * 48 + (1 << 13));
-  alloc.expect((size_t)n * 24 + 1024);  // order, particles, inverse order
   auto fail = [&](const char* what) {
     err = what;
     return -1;
@@ -915,7 +1184,6 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   // is safe on any input values).
   const float* pos = pos_in;
   const float* mass = mass_in;
-  if (hipMemsetAsync(&info->bad, 0, 4, s) != hipSuccess) return fail("memset failed");
   if (!inputs_on_device) {
     float* p = S.get<float>(3 * n);
     float* q = S.get<float>(n);
@@ -927,13 +1195,17 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     mass = q;
   }
   const bool check = inputs_on_device;  // then bbox_kernel checks them
+  const bool small = n <= kSmallN;
 
   // Root cube (the host's rule on the device's bounding box).
-  const int nbb = (int)std::min<int64_t>(1024, blocks(n));
-  float* bbp = S.get<float>(6 * nbb);
-  if (!bbp) return fail("device allocation failed");
-  bbox_kernel<<<nbb, kT, 0, s>>>(pos, check ? mass : nullptr, n, bbp, &info->bad);
-  root_kernel<<<1, kT, 0, s>>>(bbp, nbb, info->cube);
+  if (!small) {
+    if (hipMemsetAsync(&info->bad, 0, 4, s) != hipSuccess) return fail("memset failed");
+    const int nbb = (int)std::min<int64_t>(1024, blocks(n));
+    float* bbp = S.get<float>(6 * nbb);
+    if (!bbp) return fail("device allocation failed");
+    bbox_kernel<<<nbb, kT, 0, s>>>(pos, check ? mass : nullptr, n, bbp, &info->bad);
+    root_kernel<<<1, kT, 0, s>>>(bbp, nbb, info->cube);
+  }
 
   // Keys and the stable sort (ties keep the input order).
   uint64_t* key = S.get<uint64_t>(n);
@@ -943,7 +1215,10 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   if (!key || !key2 || !idx || alloc.alloc((void**)&perm, (size_t)n * 4)) return fail("device allocation failed");
   float4* packed = S.get<float4>(n);
   if (!packed) return fail("device allocation failed");
-  keys_kernel<<<blocks(n), kT, 0, s>>>(pos, mass, n, info->cube, key, idx, packed);
+  if (small)
+    small_keys_kernel<<<1, kSmallT, 0, s>>>(pos, mass, (int)n, info, key, idx, packed);
+  else
+    keys_kernel<<<blocks(n), kT, 0, s>>>(pos, mass, n, info->cube, key, idx, packed);
   size_t sbytes = 0;
   if (hipcub::DeviceRadixSort::SortPairs(nullptr, sbytes, key, key2, idx, perm, (int)n, 0, 63, s) !=
       hipSuccess)
@@ -977,10 +1252,65 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   if (!grow(cap)) return fail("device allocation failed");
   std::vector<int64_t> level_beg{0};
   int64_t lbeg = 0, lend = 1;
+  // The scalars of the levels, once fetched: the verdict on the inputs and the
+  // root cube; without an overflow also the level ranges (lbeg = lend = all
+  // cells then).
+  auto read_levels = [&]() -> const char* {
+    if (hinfo->bad & 1) return "positions must be finite with |x| < 2^60";
+    if (hinfo->bad & 2) return "masses must be finite and > 0";
+    for (int k = 0; k < 3; ++k) h.corner[k] = hinfo->cube[k];
+    h.side = hinfo->cube[3];
+    bool over = false;
+    for (const Level& v : hinfo->lv) over = over || v.overflow;
+    if (over) return nullptr;
+    int levels = 0;
+    for (int L = 0; L <= kMaxDepth && hinfo->lv[L].end > hinfo->lv[L].beg; ++L) {
+      h.max_level_cells = std::max(h.max_level_cells, hinfo->lv[L].end - hinfo->lv[L].beg);
+      if (hinfo->lv[L].total > 0) h.max_depth = L + 1;
+      level_beg.push_back(hinfo->lv[L].end);
+      lbeg = lend = hinfo->lv[L].end;
+      levels = L + 1;
+    }
+    if (pools) pools->last_levels = levels;
+    return nullptr;
+  };
+
+  // Persistent device arrays of the tree, for up to ncb cells and ngb groups.
+  float4 *part = nullptr, *geo_host = nullptr, *geo = nullptr, *wrec = nullptr, *mp = nullptr,
+         *fcell = nullptr, *gbox = nullptr;
+  int32_t *iperm = nullptr, *depth = nullptr, *groups = nullptr;
+  double *box = nullptr, *mp64 = nullptr;
+  int4 *topo = nullptr, *ginfo = nullptr;
+  int2 *work = nullptr, *wwork = nullptr;
+  auto A = [&](auto** p, int64_t count) {
+    return alloc.alloc((void**)p, (size_t)count * sizeof(**p)) == 0;
+  };
+  auto persistent = [&](int64_t ncb, int64_t ngb) {
+    const int64_t nwb = ngb + n / kChunk + 1;  // a rest per group and the full chunks
+    alloc.expect((size_t)n * 20 + (size_t)ncb * 308 + (size_t)ngb * 52 + (size_t)nwb * 16 + 16 * 256);
+    return A(&part, n) && A(&iperm, n) && A(&box, 6 * ncb) && A(&mp64, 10 * ncb) && A(&topo, ncb) &&
+           A(&geo_host, ncb) && A(&geo, ncb) && A(&wrec, 2 * ncb) && A(&mp, 3 * ncb) &&
+           A(&fcell, 2 * ncb) && A(&depth, ncb) && A(&groups, ngb) && A(&ginfo, ngb) &&
+           A(&gbox, 2 * ngb) && A(&work, nwb) && A(&wwork, nwb);
+  };
+  bool done = false;
+  if (small) {
+    const int64_t ngb = std::min(cap, n);
+    int32_t* at = S.get<int32_t>(n);
+    int4* nchunk = S.get<int4>(ngb);
+    if (!persistent(cap, ngb) || !at || !nchunk) return fail("device allocation failed");
+    small_tree_kernel<<<1, kSmallT, 0, s>>>(
+        C, key2, perm, packed, (int)n, n_leaf, n_group, (int)cap, part, iperm, box, mp64,
+        Images{topo, geo_host, geo, wrec, mp, fcell, depth}, Groups{groups, ginfo, gbox}, at, nchunk,
+        work, wwork, info);
+    if (!fetch(0, sizeof(BuildInfo))) return fail("build failed");
+    if (const char* e = read_levels()) return fail(e);
+    done = lbeg == lend;
+  }
   // All levels back to back with their ranges on the device (no host round
   // trip per level); a tree that outgrows the cell arrays is redone below
   // level by level, growing them.
-  {
+  if (!small) {
     Level* lv = info->lv;
     int32_t* bsum = S.get<int32_t>(kLB);
     // The octant boundaries (eight per cell) go into the unsorted keys, dead
@@ -1002,27 +1332,11 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
         emit_level_kernel<<<kLB, kT, 0, s>>>(C, key2, lv, L, n_leaf, bsum, bnd, bcap, cap);
       }
       if (!fetch(0, offsetof(BuildInfo, ng))) return fail("subdivision failed");
-      if (hinfo->bad & 1) return fail("positions must be finite with |x| < 2^60");
-      if (hinfo->bad & 2) return fail("masses must be finite and > 0");
       if (L1 == kMaxDepth || hinfo->lv[L1 + 1].end == hinfo->lv[L1 + 1].beg) break;
       L0 = L1 + 1;
       L1 = kMaxDepth;
     }
-    for (int k = 0; k < 3; ++k) h.corner[k] = hinfo->cube[k];
-    h.side = hinfo->cube[3];
-    bool over = false;
-    for (const Level& v : hinfo->lv) over = over || v.overflow;
-    if (!over) {
-      int levels = 0;
-      for (int L = 0; L <= kMaxDepth && hinfo->lv[L].end > hinfo->lv[L].beg; ++L) {
-        h.max_level_cells = std::max(h.max_level_cells, hinfo->lv[L].end - hinfo->lv[L].beg);
-        if (hinfo->lv[L].total > 0) h.max_depth = L + 1;
-        level_beg.push_back(hinfo->lv[L].end);
-        lbeg = lend = hinfo->lv[L].end;
-        levels = L + 1;
-      }
-      if (pools) pools->last_levels = levels;
-    }
+    if (const char* e = read_levels()) return fail(e);
   }
   if (lbeg < lend) {  // the arrays overflowed: level by level with growth
     const int32_t root[6] = {0, (int32_t)n, 0, -1, -1, 0};
@@ -1060,68 +1374,42 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     if (!pools && hipStreamSynchronize(s) != hipSuccess) return fail("subdivision failed");
   }
   const int64_t nc = lend;
+  if (!done) {
+    // Groups <= cells, so that the group and item counts come back in one copy at
+    // the end.
+    if (!persistent(nc, nc)) return fail("device allocation failed");
+    gather_kernel<<<blocks(n), kT, 0, s>>>(packed, perm, n, part, iperm);
+    moments_kernel<true><<<blocks(nc), kT, 0, s>>>(C, part, 0, nc, box, mp64);
+    for (int L = h.max_depth - 1; L >= 0; --L) {  // the deepest level holds only leaves
+      const int64_t a = level_beg[L], b = level_beg[L + 1];
+      if (b > a) moments_kernel<false><<<blocks(b - a), kT, 0, s>>>(C, part, a, b, box, mp64);
+    }
+    const int64_t nbi = blocks(nc);
+    int32_t* nleaf = S.get<int32_t>(nbi);
+    if (!nleaf) return fail("device allocation failed");
+    images_kernel<<<blocks(nc), kT, 0, s>>>(
+        C, nc, box, mp64, Images{topo, geo_host, geo, wrec, mp, fcell, depth}, nleaf);
 
-  // Persistent device arrays of the tree.
-  auto A = [&](void** p, size_t bytes) { return alloc.alloc(p, bytes) == 0; };
-  float4* part = nullptr;
-  int32_t* iperm = nullptr;
-  if (!A((void**)&part, (size_t)n * 16) || !A((void**)&iperm, (size_t)n * 4))
-    return fail("device allocation failed");
-  gather_kernel<<<blocks(n), kT, 0, s>>>(packed, perm, n, part, iperm);
-
-  double* box = nullptr;
-  double* mp64 = nullptr;
-  alloc.expect((size_t)nc * 376 + (size_t)n / 2 + 8192);  // the arrays per cell, group and item
-  if (!A((void**)&box, (size_t)nc * 48) || !A((void**)&mp64, (size_t)nc * 80))
-    return fail("device allocation failed");
-  moments_kernel<true><<<blocks(nc), kT, 0, s>>>(C, part, 0, nc, box, mp64);
-  for (int L = h.max_depth - 1; L >= 0; --L) {  // the deepest level holds only leaves
-    const int64_t a = level_beg[L], b = level_beg[L + 1];
-    if (b > a) moments_kernel<false><<<blocks(b - a), kT, 0, s>>>(C, part, a, b, box, mp64);
+    // Groups and work chunks.
+    const int64_t ngcap = nc;
+    int32_t* at = S.get<int32_t>(n);
+    int32_t* f = S.get<int32_t>(n + 1);
+    int32_t* fpre = S.get<int32_t>(n + 1);
+    int4* nchunk = S.get<int4>(ngcap + 1);
+    int4* cpre = S.get<int4>(ngcap + 1);
+    if (!at || !f || !fpre || !nchunk || !cpre) return fail("device allocation failed");
+    if (hipMemsetAsync(at, 0xff, (size_t)n * 4, s) != hipSuccess) return fail("memset failed");
+    group_mark_kernel<<<blocks(nc + 1), kT, 0, s>>>(C, nc, n_group, at, nchunk);
+    flag_kernel<<<blocks(n + 1), kT, 0, s>>>(at, n, f);
+    if (exclusive_sum(f, fpre, n + 1, S, s)) return fail("scan failed");
+    group_fill_kernel<<<blocks(n), kT, 0, s>>>(at, f, fpre, n, C, box, Groups{groups, ginfo, gbox}, nchunk);
+    if (exclusive_scan(nchunk, cpre, ngcap + 1, make_int4(0, 0, 0, 0), Int4Sum(), S, s))
+      return fail("scan failed");
+    work_kernel<<<blocks(ngcap), kT, 0, s>>>(cpre, cpre + ngcap, ginfo, fpre + n, work, wwork);
+    counts_kernel<<<1, kT, 0, s>>>(fpre + n, cpre + ngcap, nleaf, nbi, info);
+    if (!fetch(offsetof(BuildInfo, ng), sizeof(BuildInfo) - offsetof(BuildInfo, ng)))
+      return fail("group and work counts failed");
   }
-  int4* topo = nullptr;
-  float4 *geo_host = nullptr, *geo = nullptr, *wrec = nullptr, *mp = nullptr, *fcell = nullptr;
-  int32_t* depth = nullptr;
-  if (!A((void**)&topo, (size_t)nc * 16) || !A((void**)&geo_host, (size_t)nc * 16) ||
-      !A((void**)&geo, (size_t)nc * 16) || !A((void**)&wrec, (size_t)nc * 32) ||
-      !A((void**)&mp, (size_t)nc * 48) || !A((void**)&fcell, (size_t)nc * 32) ||
-      !A((void**)&depth, (size_t)nc * 4))
-    return fail("device allocation failed");
-  const int64_t nbi = blocks(nc);
-  int32_t* nleaf = S.get<int32_t>(nbi);
-  if (!nleaf) return fail("device allocation failed");
-  images_kernel<<<blocks(nc), kT, 0, s>>>(C, nc, box, mp64, topo, geo_host, geo, wrec, mp, fcell,
-                                          depth, nleaf);
-
-  // Groups and work chunks, sized by bounds known here (groups <= cells,
-  // work items <= groups + n / kChunk), so that their counts come back in
-  // one copy at the end.
-  const int64_t ngcap = nc, nwcap = nc + n / kChunk + 1;
-  int32_t* at = S.get<int32_t>(n);
-  int32_t* f = S.get<int32_t>(n + 1);
-  int32_t* fpre = S.get<int32_t>(n + 1);
-  int4* nchunk = S.get<int4>(ngcap + 1);
-  int4* cpre = S.get<int4>(ngcap + 1);
-  if (!at || !f || !fpre || !nchunk || !cpre) return fail("device allocation failed");
-  if (hipMemsetAsync(at, 0xff, (size_t)n * 4, s) != hipSuccess) return fail("memset failed");
-  group_mark_kernel<<<blocks(nc + 1), kT, 0, s>>>(C, nc, n_group, at, nchunk);
-  flag_kernel<<<blocks(n + 1), kT, 0, s>>>(at, n, f);
-  if (exclusive_sum(f, fpre, n + 1, S, s)) return fail("scan failed");
-  int32_t* groups = nullptr;
-  int4* ginfo = nullptr;
-  float4* gbox = nullptr;
-  int2 *work = nullptr, *wwork = nullptr;
-  if (!A((void**)&groups, (size_t)ngcap * 4) || !A((void**)&ginfo, (size_t)ngcap * 16) ||
-      !A((void**)&gbox, (size_t)ngcap * 32) || !A((void**)&work, (size_t)nwcap * 8) ||
-      !A((void**)&wwork, (size_t)nwcap * 8))
-    return fail("device allocation failed");
-  group_fill_kernel<<<blocks(n), kT, 0, s>>>(at, f, fpre, n, C, box, groups, ginfo, gbox, nchunk);
-  if (exclusive_scan(nchunk, cpre, ngcap + 1, make_int4(0, 0, 0, 0), Int4Sum(), S, s))
-    return fail("scan failed");
-  work_kernel<<<blocks(ngcap), kT, 0, s>>>(cpre, cpre + ngcap, ginfo, fpre + n, work, wwork);
-  counts_kernel<<<1, kT, 0, s>>>(fpre + n, cpre + ngcap, nleaf, nbi, info);
-  if (!fetch(offsetof(BuildInfo, ng), sizeof(BuildInfo) - offsetof(BuildInfo, ng)))
-    return fail("group and work counts failed");
   const int64_t ng = hinfo->ng, nw = hinfo->nw;
   h.nc_dev = nc;
   h.ng_dev = ng;

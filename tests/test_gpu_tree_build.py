@@ -103,3 +103,39 @@ def test_forces_match_across_builds_for_every_item_class(n_group):
     assert torch.isfinite(a[0]).all() and torch.isfinite(a[1]).all()
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     assert A.last_counts() == B.last_counts() and A.diagnostics()[1] == B.diagnostics()[1]
+
+
+# The one-block build: up to 8192 particles (and the general one just past it), all in one leaf, one
+# particle per leaf, more cells than one pass of the block or than a thread's share, one group.
+@pytest.mark.parametrize("n,n_leaf,n_group", [(1, 1, 1), (3, 1, 1), (16, 16, 64), (17, 16, 64), (128, 1, 4),
+                                              (1023, 1, 1), (1025, 3, 1024), (2500, 2, 17), (8191, 1, 8),
+                                              (8192, 16, 64), (8192, 64, 200), (8193, 16, 64)])
+def test_one_block_build_matches_host(n, n_leaf, n_group):
+    _torch()
+    pos, m = W.milky_way(n, n) if n > 20 else W.plummer(n, n)
+    H, D = _same_tree(pos, m * np.random.default_rng(n).uniform(0.5, 2, n).astype(np.float32), n_leaf, n_group)
+    import torch
+    a, b = H.forces(0.5, 0.01), D.forces(0.5, 0.01)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+def test_one_block_build_outgrows_its_arrays():
+    """Chains of coincident pairs: more cells than the arrays hold, built level by level instead."""
+    _torch()
+    rng = np.random.default_rng(3)
+    p = rng.uniform(-1, 1, (300, 3))
+    pos = np.concatenate([p, p]).astype(np.float32)
+    H, D = _same_tree(pos, np.full(600, 1 / 600, np.float32), 1, 4)
+    assert H.stats["n_cells"] > 2 * 600 + 64
+
+
+def test_rebuilt_handle_crosses_the_one_block_limit():
+    """A simulation's handle rebuilt in place gives a fresh handle's forces, on either side of the limit."""
+    import torch
+    for n in (8192, 8193):
+        pos, vel, m = W.plummer_with_velocities(n, 5)
+        S = og.Sim(pos, vel, m, 16, 64)
+        S.run(0.5, 0.02, 1.0 / 64, 5)
+        p, v, acc = S.state()
+        a, _ = og.Tree(p, m, 16, 64, device_build=True).forces(0.5, 0.02)
+        assert np.array_equal(a.cpu().numpy(), acc)
