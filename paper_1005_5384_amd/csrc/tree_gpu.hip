@@ -145,30 +145,27 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v) {
   return x;
 }
 
-// cube: corner xyz, side, grid step, 1 / step (root_kernel).  Also packs
-// each particle as (x, y, z, m) in input order, so that the gather after the
-// sort reads one aligned 16-byte record per particle.
-__device__ __forceinline__ void particle_key(const float* __restrict__ pos,
-                                             const float* __restrict__ mass, int64_t i,
-                                             const double* cube, uint64_t* __restrict__ key,
-                                             int32_t* __restrict__ idx, float4* __restrict__ packed) {
+// cube: corner xyz, side, grid step, 1 / step (root_cube_of).
+__device__ __forceinline__ uint64_t particle_key(float x, float y, float z, const double* cube) {
   const double step = cube[4], inv = cube[5];
-  const float x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
   const uint32_t u0 = grid_coord((double)x, cube[0], step, inv);
   const uint32_t u1 = grid_coord((double)y, cube[1], step, inv);
   const uint32_t u2 = grid_coord((double)z, cube[2], step, inv);
-  key[i] = spread3(u0) | spread3(u1) << 1 | spread3(u2) << 2;
-  idx[i] = (int32_t)i;
-  packed[i] = make_float4(x, y, z, mass[i]);
+  return spread3(u0) | spread3(u1) << 1 | spread3(u2) << 2;
 }
 
+// Also packs each particle as (x, y, z, m) in input order, so that the gather
+// after the sort reads one aligned 16-byte record per particle.
 __global__ void keys_kernel(const float* __restrict__ pos, const float* __restrict__ mass,
                             int64_t n, const double* __restrict__ cube,
                             uint64_t* __restrict__ key, int32_t* __restrict__ idx,
                             float4* __restrict__ packed) {
   const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (i >= n) return;
-  particle_key(pos, mass, i, cube, key, idx, packed);
+  const float x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
+  key[i] = particle_key(x, y, z, cube);
+  idx[i] = (int32_t)i;
+  packed[i] = make_float4(x, y, z, mass[i]);
 }
 
 struct Cells {
@@ -800,14 +797,14 @@ struct BuildInfo {
   int32_t ng, nw, leaves;
 };
 
-// ---- small trees: one block does in two launches (around the sort) what the
-// kernels above do in about 50, which for a few thousand particles are all
-// launch and latency.  The same functions and orders, so the same tree.
-// Rebuild of a Plummer sphere, many launches against one block, in us:
-//   300: 176 / 74    1000: 187 / 88    3000: 210 / 127    5003: 237 / 172
-//   8192: 237 / 215  12000: 243 / 275  16384: 242 / 341
-// one block's time grows by 17 us per 1000 particles, so the line lies at the
-// largest power of two (of keys in LDS) before the two meet.
+// ---- small trees: three launches (keys, order, and one block for all the
+// rest) do what the kernels above do in about 55, which for a few thousand
+// particles are all launch and latency.  The same functions and orders, so the
+// same tree.  Rebuild of a Plummer sphere, many launches against three, in us:
+//   300: 176 / 66    1000: 187 / 79    3000: 210 / 99    5003: 237 / 128
+//   8192: 237 / 163
+// (the limit is what one block holds of sorted keys in LDS at a cost that is
+// still well below the other side's, which hardly grows up to 16384).
 constexpr int kSmallN = 8192;  // sorted keys in LDS: 64 KB
 constexpr int kSmallT = 1024;
 
@@ -831,13 +828,15 @@ __device__ int small_exclusive(int v, int* total, int* sh) {
   return base + incl - v;
 }
 
-// Input check, root cube and keys.
+// Input check, root cube and keys: kSmallKeys keys a block, each block after a
+// pass of its own over all positions (block 0 writes what it found).  The key
+// arithmetic in FP64 is the longer part: one block for all keys took 23 us for
+// 5003 particles, these take 9.
+constexpr int kSmallKeys = 256;
 __global__ __launch_bounds__(kSmallT) void small_keys_kernel(const float* __restrict__ pos,
                                                              const float* __restrict__ mass, int n,
                                                              BuildInfo* __restrict__ info,
-                                                             uint64_t* __restrict__ key,
-                                                             int32_t* __restrict__ idx,
-                                                             float4* __restrict__ packed) {
+                                                             uint64_t* __restrict__ key) {
   __shared__ float sh[kSmallT / 64][6];
   __shared__ int bad[kSmallT / 64];
   __shared__ double cube[6];
@@ -879,21 +878,88 @@ __global__ __launch_bounds__(kSmallT) void small_keys_kernel(const float* __rest
     }
     for (int w = 0; w < kSmallT / 64; ++w) b |= bad[w];
     root_cube_of(lo, hi, cube);
-    for (int k = 0; k < 6; ++k) info->cube[k] = cube[k];
-    info->bad = b;
+    if (blockIdx.x == 0) {
+      for (int k = 0; k < 6; ++k) info->cube[k] = cube[k];
+      info->bad = b;
+    }
   }
   __syncthreads();
-  for (int i = t; i < n; i += kSmallT) particle_key(pos, mass, i, cube, key, idx, packed);
+  const int i = blockIdx.x * kSmallKeys + t;
+  if (t < kSmallKeys && i < n) key[i] = particle_key(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], cube);
+}
+
+// The stable sort by counting: a key's place is the number of keys before it
+// in (key, index) order.  A block places kRankKeys keys: its threads hold all
+// keys between them and each compare's lane mask is counted by the scalar
+// unit.  n^2 compares over the whole device take 12 us for 5003 keys (16 for
+// 8000), where rocPRIM's block sort and merge passes took 35 in six launches.  Also writes
+// the particles in key order.
+constexpr int kRankKeys = 32;
+__global__ __launch_bounds__(kSmallT) void small_rank_kernel(const uint64_t* __restrict__ key,
+                                                             const float* __restrict__ pos,
+                                                             const float* __restrict__ mass, int n,
+                                                             uint64_t* __restrict__ sorted,
+                                                             int32_t* __restrict__ perm,
+                                                             float4* __restrict__ part,
+                                                             int32_t* __restrict__ iperm) {
+  constexpr int kHeld = kSmallN / kSmallT;
+  static_assert(64 % kRankKeys == 0, "a block's keys lie in one run of 64");
+  __shared__ int cnt[kSmallT / 64][kRankKeys];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int e0 = blockIdx.x * kRankKeys;
+  uint64_t kj[kHeld];  // of keys q * kSmallT + t; past the end larger than any key
+#pragma unroll
+  for (int q = 0; q < kHeld; ++q) {
+    const int j = q * kSmallT + t;
+    kj[q] = j < n ? key[j] : ~0ull;
+  }
+  const int jw = __builtin_amdgcn_readfirstlane(w) * 64;
+  const int run = e0 & ~63;  // the block's keys lie in run ... run + 63
+  // (the block's keys from a lane each: loaded one by one they cost a memory
+  // latency per key)
+  const uint64_t ke = key[min(e0 + (lane & (kRankKeys - 1)), n - 1)];
+  constexpr int kU = 8;
+#pragma unroll 1
+  for (int g = 0; g < kRankKeys; g += kU) {
+    uint64_t ki[kU];
+    int c[kU] = {};
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      ki[u] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(ke >> 32), g + u) << 32 |
+              (uint32_t)__builtin_amdgcn_readlane((int)ke, g + u);
+#pragma unroll
+    for (int q = 0; q < kHeld; ++q) {
+      if (q * kSmallT >= n) break;
+      const int jb = q * kSmallT + jw;  // keys jb ... jb + 63 are this wave's
+      const uint64_t tie = jb < run ? 1 : 0;
+#pragma unroll
+      for (int u = 0; u < kU; ++u) c[u] += __popcll(__ballot(kj[q] < ki[u] + tie));
+      if (jb == run)
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+          c[u] += __popcll(__ballot(kj[q] == ki[u]) & ((1ull << (e0 + g + u - run)) - 1));
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (lane == u) cnt[w][g + u] = c[u];
+  }
+  __syncthreads();
+  const int i = e0 + t;
+  if (t >= kRankKeys || i >= n) return;
+  int r = 0;
+  for (int k = 0; k < kSmallT / 64; ++k) r += cnt[k][t];
+  sorted[r] = key[i];
+  perm[r] = i;
+  iperm[i] = r;
+  part[r] = make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]);
 }
 
 // Everything after the sort.  Cell, image, group and item arrays hold cap
 // cells and n groups; more than cap cells are flagged (lv[].overflow) and the
 // host builds level by level.
 __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
-    Cells C, const uint64_t* __restrict__ key, const int32_t* __restrict__ perm,
-    const float4* __restrict__ packed, int n, int n_leaf, int n_group, int cap,
-    float4* __restrict__ part, int32_t* __restrict__ iperm, double* box, double* mp64, Images I,
-    Groups G, int32_t* at, int4* nchunk, int2* __restrict__ work, int2* __restrict__ wwork,
+    Cells C, const uint64_t* __restrict__ key, const float4* __restrict__ part, int n, int n_leaf,
+    int n_group, int cap, double* box, double* mp64, Images I, Groups G, int32_t* at, int4* nchunk, int2* __restrict__ work, int2* __restrict__ wwork,
     BuildInfo* __restrict__ info) {
   __shared__ uint64_t skey[kSmallN];
   __shared__ int sh[kSmallT / 64];
@@ -902,9 +968,6 @@ __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
   for (int i = t; i < n; i += kSmallT) {
     skey[i] = key[i];
     at[i] = -1;
-    const int32_t p = perm[i];
-    part[i] = packed[p];
-    iperm[p] = i;
   }
   if (t == 0) {
     C.first[0] = 0;
@@ -1215,19 +1278,18 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   if (!key || !key2 || !idx || alloc.alloc((void**)&perm, (size_t)n * 4)) return fail("device allocation failed");
   float4* packed = S.get<float4>(n);
   if (!packed) return fail("device allocation failed");
-  if (small)
-    small_keys_kernel<<<1, kSmallT, 0, s>>>(pos, mass, (int)n, info, key, idx, packed);
-  else
+  if (!small) {
     keys_kernel<<<blocks(n), kT, 0, s>>>(pos, mass, n, info->cube, key, idx, packed);
-  size_t sbytes = 0;
-  if (hipcub::DeviceRadixSort::SortPairs(nullptr, sbytes, key, key2, idx, perm, (int)n, 0, 63, s) !=
-      hipSuccess)
-    return fail("sort failed");
-  void* stmp = S.get<char>((int64_t)sbytes);
-  if (!stmp) return fail("device allocation failed");
-  if (hipcub::DeviceRadixSort::SortPairs(stmp, sbytes, key, key2, idx, perm, (int)n, 0, 63, s) !=
-      hipSuccess)
-    return fail("sort failed");
+    size_t sbytes = 0;
+    if (hipcub::DeviceRadixSort::SortPairs(nullptr, sbytes, key, key2, idx, perm, (int)n, 0, 63,
+                                           s) != hipSuccess)
+      return fail("sort failed");
+    void* stmp = S.get<char>((int64_t)sbytes);
+    if (!stmp) return fail("device allocation failed");
+    if (hipcub::DeviceRadixSort::SortPairs(stmp, sbytes, key, key2, idx, perm, (int)n, 0, 63, s) !=
+        hipSuccess)
+      return fail("sort failed");
+  }
 
   // Level-synchronous subdivision; cell arrays grow as needed.
   int64_t cap = 2 * n + 64;
@@ -1299,8 +1361,12 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     int32_t* at = S.get<int32_t>(n);
     int4* nchunk = S.get<int4>(ngb);
     if (!persistent(cap, ngb) || !at || !nchunk) return fail("device allocation failed");
+    small_keys_kernel<<<((int)n + kSmallKeys - 1) / kSmallKeys, kSmallT, 0, s>>>(
+        pos, mass, (int)n, info, key);
+    small_rank_kernel<<<((int)n + kRankKeys - 1) / kRankKeys, kSmallT, 0, s>>>(
+        key, pos, mass, (int)n, key2, perm, part, iperm);
     small_tree_kernel<<<1, kSmallT, 0, s>>>(
-        C, key2, perm, packed, (int)n, n_leaf, n_group, (int)cap, part, iperm, box, mp64,
+        C, key2, part, (int)n, n_leaf, n_group, (int)cap, box, mp64,
         Images{topo, geo_host, geo, wrec, mp, fcell, depth}, Groups{groups, ginfo, gbox}, at, nchunk,
         work, wwork, info);
     if (!fetch(0, sizeof(BuildInfo))) return fail("build failed");
@@ -1344,6 +1410,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     for (int k = 0; k < 6; ++k)
       if (hipMemcpyAsync(rdst[k], &root[k], 4, hipMemcpyHostToDevice, s) != hipSuccess)
         return fail("root upload failed");
+    if (small) keys_kernel<<<blocks(n), kT, 0, s>>>(pos, mass, n, info->cube, key, idx, packed);
   }
   for (int L = 0; lbeg < lend; ++L) {
     const int64_t m = lend - lbeg;

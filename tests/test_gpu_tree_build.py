@@ -139,3 +139,12 @@ def test_rebuilt_handle_crosses_the_one_block_limit():
         p, v, acc = S.state()
         a, _ = og.Tree(p, m, 16, 64, device_build=True).forces(0.5, 0.02)
         assert np.array_equal(a.cpu().numpy(), acc)
+
+
+@pytest.mark.parametrize("n", [2, 31, 33, 64, 65, 1024, 1056, 4000, 8192])
+def test_one_block_build_keeps_the_order_of_ties(n):
+    """Few distinct positions: the order within each is the input's, across lanes, waves and blocks."""
+    _torch()
+    rng = np.random.default_rng(n)
+    pos = (rng.integers(-1, 2, (n, 3)) * 0.5).astype(np.float32)
+    _same_tree(pos, rng.uniform(0.5, 2.0, n).astype(np.float32), 16, 64)
