@@ -234,11 +234,10 @@ struct SeqPool {
   SeqPool& operator=(const SeqPool&) = delete;
   ~SeqPool();
 };
-// Scratch of the device build kept between builds: whole-build arrays,
-// per-level arrays (the same slots every level) and the cell arrays.
+// Scratch of the device build kept between builds: whole-build arrays and
+// the cell arrays.
 struct BuildPools {
-  SeqPool outer, level, cells;
-  int last_levels = 0;  // non-empty levels of the previous build (0: unknown)
+  SeqPool outer, cells;
   void* pinned = nullptr;  // page-locked host copy of the build's scalars (tree_gpu.hip)
   BuildPools() = default;
   BuildPools(const BuildPools&) = delete;

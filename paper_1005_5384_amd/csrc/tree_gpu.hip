@@ -1,13 +1,13 @@
 // Octree construction on the GPU (the host build of Sec. 2.1 moved to the
 // device), bit-identical to the host build: the same 63-bit Morton keys from
 // the same FP64 grid arithmetic, a stable radix sort (ties by input index),
-// the same level-synchronous breadth-first subdivision, and FP64 boxes and
+// the same breadth-first cell order, and FP64 boxes and
 // moments bottom-up with the host's operation order (no contraction, the
 // host's min / max), so every exported array matches bitwise.
 //
-// Per level: one thread per cell finds its octant boundaries by binary search
-// in the sorted keys and counts non-empty children; a scan numbers the
-// children; a second pass writes them.  Boxes and moments: one thread per
+// Subdivision: which cells start at a particle follows from the sorted keys
+// around it (level_range), so all levels are numbered by one scan and written
+// by one kernel.  Boxes and moments: one thread per
 // cell, deepest level first.  Then the FP32 images, the walk records, the
 // learned criterion's cell features, the groups (scattered to their first
 // particle and compacted, which orders them by first particle) and the work
@@ -177,139 +177,171 @@ struct Cells {
   int32_t* nc;      // children
 };
 
-// Octant boundaries of the level's cells [lbeg, lbeg + m) at digit shift sh;
-// bd[9 j ..] and the count of non-empty children of cell lbeg + j.
-__global__ void split_kernel(Cells C, const uint64_t* __restrict__ key, int64_t lbeg, int64_t m,
-                             int L, int n_leaf, int32_t* __restrict__ bd,
-                             int32_t* __restrict__ nkid) {
-  const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (j >= m) return;
-  const int64_t c = lbeg + j;
-  const int32_t a = C.first[c], b = a + C.n[c];
-  if (C.n[c] <= n_leaf || L == kMaxDepth) {
-    nkid[j] = 0;
-    return;
-  }
-  const int sh = 3 * (kMaxDepth - 1 - L);
-  int32_t* d9 = bd + 9 * j;
-  d9[0] = a;
-  int32_t lo = a;
-  int cnt = 0;
-  for (int d = 1; d < 8; ++d) {
-    // first index in [lo, b) whose digit is >= d (digits are sorted)
-    int32_t l = lo, h = b;
-    while (l < h) {
-      const int32_t mid = l + ((h - l) >> 1);
-      if ((int)((key[mid] >> sh) & 7) < d) l = mid + 1;
-      else h = mid;
-    }
-    d9[d] = l;
-    cnt += l > lo;
-    lo = l;
-  }
-  d9[8] = b;
-  cnt += b > lo;
-  nkid[j] = cnt;
+// ---- subdivision.  A cell of level L (the particles that share L octant
+// digits) exists if its parent holds more than n_leaf particles.  For particle
+// i let lcp be the number of digits it shares with particle i - 1, and D the
+// deepest level at which the cell around it holds more than n_leaf: n_leaf + 1
+// consecutive keys share D digits, so D is the maximum, over the windows of
+// n_leaf + 1 keys that contain i, of the digits shared by the window's ends.
+// Then the cells that start at i are those of levels lcp + 1 ... D + 1, the
+// last of them a leaf.  Counting starts level by level in particle order is
+// the breadth-first numbering; the parent of a cell is the last start of the
+// level above, and the first child of a split cell the next level's cell that
+// starts with it.  (Level by level, two launches each, this was 125 us of a
+// rebuild of 262144 particles; count, scan and write are 20, with fewer gaps.
+// Whole rebuild, before and now, us: 16384 263 / 173, 65536 297 / 214, 262144
+// 394 / 300, 1M 655 / 527.)
+constexpr int kMaxLeaf = 64;            // largest n_leaf
+constexpr int kLevels = kMaxDepth + 1;  // levels 0 ... kMaxDepth
+constexpr int kST = 1024;               // particles, and threads, per block
+constexpr int kSW = kST / 64;
+
+// Octant digits shared by two keys (63 bits: the top bit is clear).
+__device__ __forceinline__ int shared_digits(uint64_t a, uint64_t b) {
+  const uint64_t x = a ^ b;
+  return x == 0 ? kMaxDepth : (__clzll((long long)x) - 1) / 3;
 }
 
-__global__ void emit_kernel(Cells C, int64_t lbeg, int64_t lend, int64_t m, int L,
-                            const int32_t* __restrict__ bd, const int32_t* __restrict__ nkid,
-                            const int32_t* __restrict__ pre) {
-  const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (j >= m || nkid[j] == 0) return;
-  const int64_t c = lbeg + j;
-  int64_t ch = lend + pre[j];
-  C.fc[c] = (int32_t)ch;
-  C.nc[c] = nkid[j];
-  const int32_t* d9 = bd + 9 * j;
-  for (int d = 0; d < 8; ++d)
-    if (d9[d + 1] > d9[d]) {
-      C.first[ch] = d9[d];
-      C.n[ch] = d9[d + 1] - d9[d];
-      C.depth[ch] = L + 1;
-      C.parent[ch] = (int32_t)c;
-      C.fc[ch] = -1;
-      C.nc[ch] = 0;
-      ++ch;
-    }
+// Digits shared by the ends of the window of n_leaf + 1 keys that starts at j
+// (-1: no such window).
+__device__ __forceinline__ int8_t window_digits(const uint64_t* key, int64_t n, int n_leaf,
+                                                int64_t j) {
+  return j >= 0 && j + n_leaf < n ? (int8_t)shared_digits(key[j], key[j + n_leaf]) : (int8_t)-1;
 }
 
-// ---- subdivision without host round trips: every level's range lives on
-// the device, so all levels are launched back to back.
-struct Level {
-  int64_t beg, end;   // the level's cells [beg, end)
-  int64_t total;      // children it emitted
-  int32_t overflow;   // the cell arrays could not hold them
-  int32_t pad;
+// out[e]: the maximum of the 2 run windows from e on, from those of run windows
+// (len entries, a block of kST threads).
+__device__ __forceinline__ void join_windows(const int8_t* in, int8_t* out, int len, int run) {
+  for (int e = threadIdx.x; e < len; e += kST) out[e] = max(in[e], in[e + run < len ? e + run : e]);
+}
+
+// The levels of the cells that start at a particle: lo ... hi (none if lo > hi).
+struct LevelRange {
+  int lo, hi;
 };
-constexpr int kLB = 512;  // blocks of the level kernels; block b owns a contiguous chunk
+__device__ __forceinline__ LevelRange level_range(const uint64_t* key, int64_t i, int D) {
+  return LevelRange{i > 0 ? shared_digits(key[i - 1], key[i]) + 1 : 0, min(D + 1, kMaxDepth)};
+}
 
-// Eight lanes per cell: lane d of the group finds the first particle of the
-// cell whose octant digit at level L is >= d (d = 0: the cell's first), all
-// eight searches at once; the next lane's boundary closes the octant.
-// Returns whether octant d is a non-empty child (false for leaves).
-struct OctantLane {
-  int64_t c;
-  int32_t lo, hi;  // the octant's particles [lo, hi)
-  bool child;
-};
-__device__ OctantLane octant_lane(const Cells& C, const uint64_t* __restrict__ key, int64_t beg,
-                                  int64_t j, bool valid, int L, int n_leaf) {
-  const int d = threadIdx.x & 7;
-  OctantLane o{beg + j, 0, 0, false};
-  int32_t a = 0, b = 0;
-  bool split = false;
-  if (valid) {
-    a = C.first[o.c];
-    b = a + C.n[o.c];
-    split = !(C.n[o.c] <= n_leaf || L == kMaxDepth);
+// Starts of each level among the wave's particles, to row[L * stride].
+__device__ __forceinline__ void count_starts(LevelRange r, int* row, int stride) {
+  const int lane = threadIdx.x & 63;
+  int v = 0;
+  const int hi = r.lo <= r.hi ? r.hi : -1;
+  for (int L = 0; L < kLevels && __any(L <= hi); ++L) {
+    const int k = __popcll(__ballot(r.lo <= L && L <= hi));
+    if (lane == L) v = k;
   }
-  int32_t l = a;
-  if (split && d > 0) {
-    const int sh = 3 * (kMaxDepth - 1 - L);
-    int32_t h = b;
-    while (l < h) {
-      const int32_t mid = l + ((h - l) >> 1);
-      if ((int)((key[mid] >> sh) & 7) < d) l = mid + 1;
-      else h = mid;
+  if (lane < kLevels) row[lane * stride] = v;
+}
+
+// Writes the cells that start at the wave's particles (this lane's: i), as
+// far as they fit cap cells; row[L * stride]: the number of the wave's first
+// cell of level L.  Particle and child counts of split cells follow later
+// (close_parent, inner cell_moments).
+__device__ __forceinline__ void write_cells(const Cells& C, const uint64_t* key, int32_t n,
+                                            int32_t i, LevelRange r, int n_leaf, int64_t cap,
+                                            const int* row, int stride) {
+  int32_t up = 0, up_end = 0;  // of the level above: this lane's cell, cells up to and with it
+  int32_t leaf = -1;
+  for (int L = 0; L < kLevels; ++L) {
+    if (!__any(r.lo <= r.hi && L <= r.hi)) break;
+    const bool m = r.lo <= L && L <= r.hi;
+    const uint64_t b = __ballot(m);
+    const int32_t c = row[L * stride] +
+                      (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0));
+    if (m && c < cap) {
+      C.first[c] = i;
+      C.depth[c] = L;
+      C.parent[c] = up_end - 1;
+      if (L == r.hi) leaf = c;
+    }
+    if (m && L > r.lo && up < cap) C.fc[up] = c;
+    up = c;
+    up_end = c + m;
+  }
+  if (leaf < 0) return;
+  int32_t l = i + 1, h = r.hi == kMaxDepth || n - i <= n_leaf ? n : i + n_leaf;
+  const int sh = 3 * (kMaxDepth - r.hi);
+  const uint64_t k = key[i] >> sh;
+  while (l < h) {
+    const int32_t mid = l + ((h - l) >> 1);
+    if (key[mid] >> sh == k) l = mid + 1;
+    else h = mid;
+  }
+  C.n[leaf] = l - i;
+  C.fc[leaf] = -1;
+  C.nc[leaf] = 0;
+}
+
+// Number of children of the parent of cell c (of nc), written by the last child.
+__device__ __forceinline__ void close_parent(const Cells& C, int64_t c, int64_t nc) {
+  const int32_t p = C.parent[c];
+  if (p >= 0 && (c + 1 == nc || C.parent[c + 1] != p)) C.nc[p] = (int32_t)(c + 1) - C.fc[p];
+}
+
+// Level ranges of the particles and each block's starts per level (cnt[L *
+// gridDim.x + block]; a 0 behind the last).
+__global__ __launch_bounds__(kST) void starts_kernel(const uint64_t* __restrict__ key, int64_t n,
+                                                     int n_leaf, uchar2* __restrict__ range,
+                                                     int32_t* __restrict__ cnt) {
+  __shared__ int8_t sw[2][kST + kMaxLeaf];
+  __shared__ int rows[kLevels][kSW];
+  const int t = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * kST, i = i0 + t;
+  const int len = kST + n_leaf;
+  for (int e = t; e < len; e += kST) sw[0][e] = window_digits(key, n, n_leaf, i0 - n_leaf + e);
+  __syncthreads();
+  int at = 0, run = 1;
+  for (; 2 * run <= n_leaf + 1; run *= 2, at ^= 1) {
+    join_windows(sw[at], sw[at ^ 1], len, run);
+    __syncthreads();
+  }
+  const int D = max(sw[at][t], sw[at][t + n_leaf - run + 1]);
+  LevelRange r{1, 0};
+  if (i < n) {
+    r = level_range(key, i, D);
+    range[i] = make_uchar2((unsigned char)r.lo, (unsigned char)r.hi);
+  }
+  count_starts(r, &rows[0][t >> 6], kSW);
+  __syncthreads();
+  if (t < kLevels) {
+    int k = 0;
+    for (int v = 0; v < kSW; ++v) k += rows[t][v];
+    cnt[(int64_t)t * gridDim.x + blockIdx.x] = k;
+  }
+  if (t == 0 && blockIdx.x == 0) cnt[(int64_t)kLevels * gridDim.x] = 0;
+}
+
+// The cells, numbered by the scan of the counts; block 0 records where each
+// level begins.
+__global__ __launch_bounds__(kST) void cells_kernel(Cells C, const uint64_t* __restrict__ key,
+                                                    int32_t n, int n_leaf,
+                                                    const uchar2* __restrict__ range,
+                                                    const int32_t* __restrict__ before,
+                                                    int64_t cap, int64_t* __restrict__ level) {
+  __shared__ int rows[kLevels][kSW];
+  const int t = threadIdx.x;
+  const int64_t i = (int64_t)blockIdx.x * kST + t;
+  LevelRange r{1, 0};
+  if (i < n) {
+    const uchar2 v = range[i];
+    r = LevelRange{v.x, v.y};
+  }
+  count_starts(r, &rows[0][t >> 6], kSW);
+  __syncthreads();
+  if (t < kLevels) {
+    int at = before[(int64_t)t * gridDim.x + blockIdx.x];
+    for (int v = 0; v < kSW; ++v) {
+      const int k = rows[t][v];
+      rows[t][v] = at;
+      at += k;
     }
   }
-  const int32_t nx = __shfl_down(l, 1, 8);
-  o.lo = l;
-  o.hi = d == 7 ? b : nx;
-  o.child = split && o.hi > o.lo;
-  return o;
-}
-
-// octant_lane from the boundaries split_level_kernel stored (bnd[8 j + d] =
-// lane d's search result, the cell's first particle where nothing was
-// searched): the same result without the searches.
-__device__ OctantLane octant_lane_stored(const Cells& C, const int32_t* __restrict__ bnd,
-                                         int64_t beg, int64_t j, bool valid, int L, int n_leaf) {
-  const int d = threadIdx.x & 7;
-  OctantLane o{beg + j, 0, 0, false};
-  int32_t b = 0, l = 0;
-  bool split = false;
-  if (valid) {
-    b = C.first[o.c] + C.n[o.c];
-    split = !(C.n[o.c] <= n_leaf || L == kMaxDepth);
-    l = bnd[8 * j + d];
-  }
-  const int32_t nx = __shfl_down(l, 1, 8);
-  o.lo = l;
-  o.hi = d == 7 ? b : nx;
-  o.child = split && o.hi > o.lo;
-  return o;
-}
-
-// Non-empty children among the eight lanes of this lane's group, and how many
-// of them come before this lane.
-__device__ void octant_counts(bool child, int* n, int* before) {
-  const uint64_t m = __ballot(child);
-  const int lane = threadIdx.x & 63, g = lane & ~7;
-  const uint32_t grp = (uint32_t)(m >> g) & 0xffu;
-  *n = __popc(grp);
-  *before = __popc(grp & ((1u << (lane - g)) - 1u));
+  if (t <= kLevels && blockIdx.x == 0) level[t] = before[(int64_t)t * gridDim.x];
+  __syncthreads();
+  write_cells(C, key, n, (int32_t)i, r, n_leaf, cap, &rows[0][t >> 6], kSW);
 }
 
 // Sum of v over the block (kT threads); every thread gets it.
@@ -321,163 +353,6 @@ __device__ int block_sum(int v, int* sh) {
   for (int k = 0; k < kT / 64; ++k) t += sh[k];
   __syncthreads();
   return t;
-}
-
-// Exclusive prefix of v over the block in thread order, and the block total.
-__device__ int block_exclusive(int v, int* total, int* sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int incl = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
-  }
-  if (lane == 63) sh[w] = incl;
-  __syncthreads();
-  int base = 0, tot = 0;
-  for (int k = 0; k < kT / 64; ++k) {
-    base += k < w ? sh[k] : 0;
-    tot += sh[k];
-  }
-  __syncthreads();
-  *total = tot;
-  return base + incl - v;
-}
-
-__global__ void level_init_kernel(Cells C, Level* lv, int32_t n) {
-  if (threadIdx.x == 0) {
-    C.first[0] = 0;
-    C.n[0] = n;
-    C.depth[0] = 0;
-    C.parent[0] = -1;
-    C.fc[0] = -1;
-    C.nc[0] = 0;
-  }
-  if (threadIdx.x < kMaxDepth + 2) {
-    const int64_t e = threadIdx.x == 0 ? 1 : 0;
-    lv[threadIdx.x] = Level{0, e, 0, 0, 0};
-  }
-}
-
-// Children of level L's cells counted per block (bsum); eight lanes per
-// cell.  A level of at most bcap cells also keeps the octant boundaries in
-// bnd for emit_level_kernel.
-__global__ __launch_bounds__(kT) void split_level_kernel(Cells C, const uint64_t* __restrict__ key,
-                                                         const Level* __restrict__ lv, int L,
-                                                         int n_leaf, int32_t* __restrict__ bsum,
-                                                         int32_t* __restrict__ bnd, int64_t bcap) {
-  __shared__ int sh[kT / 64];
-  const int64_t beg = lv[L].beg, m = lv[L].end - beg;
-  const int64_t chunk = (m + kLB - 1) / kLB;
-  const int64_t j0 = blockIdx.x * chunk, j1 = j0 + chunk < m ? j0 + chunk : m;
-  int s = 0;
-  if (m <= kLB * (kT / 64) && m <= bcap) {
-    // A level of few (large) cells: a wave per cell, lanes 8 d ... 8 d + 7
-    // find boundary d by a 9-ary search (eight probes per step), about
-    // log9 instead of log2 dependent loads.
-    const int lane = threadIdx.x & 63, d = lane >> 3, r = lane & 7;
-    const int sh3 = 3 * (kMaxDepth - 1 - L);
-    for (int64_t base = j0; base < j1; base += kT / 64) {
-      const int64_t j = base + threadIdx.x / 64;  // uniform per wave
-      if (j >= j1) break;
-      const int64_t c = beg + j;
-      const int32_t a = C.first[c], b = a + C.n[c];
-      const bool split = !(C.n[c] <= n_leaf || L == kMaxDepth);
-      int32_t l = a, h = split && d > 0 ? b : a;
-      // every lane of a group of eight holds the same l, h
-      while (__any(l < h)) {
-        const int32_t w = h - l;
-        const int32_t pr = w >= 9 ? l + (int32_t)(((int64_t)w * (r + 1)) / 9) : l + r;
-        const bool live = l < h && pr < h;
-        const bool lt = live && (int)((key[pr] >> sh3) & 7) < d;
-        const uint32_t grp = (uint32_t)(__ballot(lt) >> (lane & ~7)) & 0xffu;
-        const uint32_t fal = (uint32_t)(__ballot(live && !lt) >> (lane & ~7)) & 0xffu;
-        const int nt = __popc(grp);  // probes below d (a prefix of the group)
-        const int32_t plast = __shfl(pr, (lane & ~7) + (nt > 0 ? nt - 1 : 0));
-        const int32_t pfirst = __shfl(pr, (lane & ~7) + (nt < 8 ? nt : 7));
-        if (l < h) {
-          if (nt > 0) l = plast + 1;
-          if (fal != 0) h = pfirst;
-          else if (nt == 0) h = l;  // no live probe: nothing left
-        }
-      }
-      const int32_t nx = __shfl_down(l, 8);
-      const int32_t hi = d == 7 ? b : nx;
-      const bool child = split && hi > l && r == 0;
-      const int k = __popcll(__ballot(child));
-      if (r == 0) bnd[8 * j + d] = l;
-      s += lane == 0 ? k : 0;
-    }
-    s = block_sum(s, sh);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = s;
-    return;
-  }
-  for (int64_t base = j0; base < j1; base += kT / 8) {
-    const int64_t j = base + threadIdx.x / 8;
-    const OctantLane o = octant_lane(C, key, beg, j, j < j1, L, n_leaf);
-    int k, before;
-    octant_counts(o.child, &k, &before);
-    if (j < j1 && m <= bcap) bnd[8 * j + (threadIdx.x & 7)] = o.lo;
-    if ((threadIdx.x & 7) == 0 && j < j1) s += k;
-  }
-  s = block_sum(s, sh);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = s;
-}
-
-// Writes level L's children in cell order; eight lanes per cell, one per
-// octant, with the boundaries split_level_kernel kept (searched again for a
-// level of more than bcap cells).  Every block sums the per-block children
-// counts before its own (its first child's offset) and all of them (the
-// level's total, for the capacity check); block 0 records the total and the
-// next level's range (empty after an overflow, which it flags there).
-__global__ __launch_bounds__(kT) void emit_level_kernel(Cells C, const uint64_t* __restrict__ key,
-                                                        Level* __restrict__ lv, int L,
-                                                        int n_leaf,
-                                                        const int32_t* __restrict__ bsum,
-                                                        const int32_t* __restrict__ bnd,
-                                                        int64_t bcap, int64_t cap) {
-  __shared__ int sh[kT / 64];
-  static_assert(kLB == 2 * kT, "two block sums per thread");
-  const int i0 = 2 * (int)threadIdx.x, blk = (int)blockIdx.x;
-  const int s0 = bsum[i0], s1 = bsum[i0 + 1];
-  const int preceding = block_sum((i0 < blk ? s0 : 0) + (i0 + 1 < blk ? s1 : 0), sh);
-  const int total = block_sum(s0 + s1, sh);
-  const int64_t beg = lv[L].beg, end = lv[L].end, m = end - beg;
-  const bool over = lv[L].overflow || end + total > cap;
-  if (blk == 0 && threadIdx.x == 0) {
-    lv[L].total = over ? 0 : total;
-    if (L + 1 < kMaxDepth + 2) lv[L + 1] = Level{end, over ? end : end + total, 0, over, 0};
-  }
-  if (over) return;
-  const int64_t chunk = (m + kLB - 1) / kLB;
-  const int64_t j0 = blockIdx.x * chunk, j1 = j0 + chunk < m ? j0 + chunk : m;
-  int64_t carry = preceding;
-  for (int64_t base = j0; base < j1; base += kT / 8) {
-    const int64_t j = base + threadIdx.x / 8;
-    const bool valid = j < j1;
-    const OctantLane o = m <= bcap ? octant_lane_stored(C, bnd, beg, j, valid, L, n_leaf)
-                                   : octant_lane(C, key, beg, j, valid, L, n_leaf);
-    int k, before;
-    octant_counts(o.child, &k, &before);
-    const bool lead = (threadIdx.x & 7) == 0;
-    int step = 0;
-    const int ex = __shfl(block_exclusive(lead && valid ? k : 0, &step, sh),
-                          (int)(threadIdx.x & 63) & ~7);
-    const int64_t first = end + carry + ex;
-    if (lead && valid && k > 0) {
-      C.fc[o.c] = (int32_t)first;
-      C.nc[o.c] = k;
-    }
-    if (o.child) {
-      const int64_t ch = first + before;
-      C.first[ch] = o.lo;
-      C.n[ch] = o.hi - o.lo;
-      C.depth[ch] = L + 1;
-      C.parent[ch] = (int32_t)o.c;
-      C.fc[ch] = -1;
-      C.nc[ch] = 0;
-    }
-    carry += step;
-  }
 }
 
 __global__ void gather_kernel(const float4* __restrict__ packed, const int32_t* __restrict__ perm,
@@ -502,7 +377,8 @@ __device__ __forceinline__ double hmax(double a, double b) { return a < b ? b : 
 // sums start at +0 and the inputs are finite).
 constexpr int kMomChunk = 16;
 // LEAVES: cell c if it is a leaf, else nothing; otherwise cell c if it has
-// children (whose moments are done), else nothing.
+// children (whose moments are done), else nothing; then also its particle
+// count.
 template <bool LEAVES>
 __device__ __forceinline__ void cell_moments(const Cells& C, const float4* __restrict__ part,
                                              int64_t c, double* __restrict__ box,
@@ -512,7 +388,7 @@ __device__ __forceinline__ void cell_moments(const Cells& C, const float4* __res
   double M = 0, sx = 0, sy = 0, sz = 0;
   double Q[6] = {0, 0, 0, 0, 0, 0};
   double com[3];
-  const bool leaf = C.nc[c] == 0;
+  const bool leaf = C.fc[c] < 0;
   if (leaf != LEAVES) return;
   if (LEAVES) {
     const int32_t f = C.first[c], e = f + C.n[c];
@@ -559,6 +435,7 @@ __device__ __forceinline__ void cell_moments(const Cells& C, const float4* __res
     // Children in two batches of four (a batch's loads first, then its sums
     // in child order), which keeps the kernel at a few waves per SIMD.
     const int32_t f = C.fc[c], nk = C.nc[c];  // 1 ... 8 children
+    C.n[c] = C.first[f + nk - 1] + C.n[f + nk - 1] - C.first[c];
 #pragma unroll 1
     for (int h = 0; h < nk; h += 4) {
       double cb[4][6], cm[4][4];
@@ -620,18 +497,20 @@ __device__ __forceinline__ void cell_moments(const Cells& C, const float4* __res
   for (int k = 0; k < 6; ++k) q[4 + k] = Q[k];
 }
 
-// The leaves among cells [a, b) (all cells: leaves need only their
-// particles), or the cells with children among [a, b) (one level, after the
-// levels below), one thread per cell.
+// One thread per cell.  LEAVES: the leaves among all cells [a, b) (leaves need
+// only their particles), and every parent's number of children; otherwise the
+// cells with children among the cells [a, b) of one level, after the levels
+// below.
 template <bool LEAVES>
 __global__ __launch_bounds__(kT) void moments_kernel(Cells C, const float4* __restrict__ part,
                                                      int64_t a, int64_t b,
                                                      double* __restrict__ box,
                                                      double* __restrict__ mp64) {
   const int64_t c = a + (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (c < b) cell_moments<LEAVES>(C, part, c, box, mp64);
+  if (c >= b) return;
+  if (LEAVES) close_parent(C, c, b);
+  cell_moments<LEAVES>(C, part, c, box, mp64);
 }
-
 
 // Arrays of FP32 images per cell (images_kernel).
 struct Images {
@@ -791,20 +670,18 @@ __global__ void work_kernel(const int4* __restrict__ pre, const int4* __restrict
 // The build's scalars the host needs, gathered in one place on the device so
 // that one copy fetches them.
 struct BuildInfo {
-  Level lv[kMaxDepth + 2];
+  int64_t level[kLevels + 1];  // where each level's cells begin; all cells
   double cube[6];  // root_kernel
   int32_t bad;     // input check (bbox_kernel)
   int32_t ng, nw, leaves;
 };
 
 // ---- small trees: three launches (keys, order, and one block for all the
-// rest) do what the kernels above do in about 55, which for a few thousand
-// particles are all launch and latency.  The same functions and orders, so the
+// rest) do what the kernels above and below do in about 30, which for a few
+// thousand particles are all launch and latency.  The same functions and orders, so the
 // same tree.  Rebuild of a Plummer sphere, many launches against three, in us:
-//   300: 176 / 66    1000: 187 / 79    3000: 210 / 99    5003: 237 / 128
-//   8192: 237 / 163
-// (the limit is what one block holds of sorted keys in LDS at a cost that is
-// still well below the other side's, which hardly grows up to 16384).
+//   300: 148 / 61    1000: 151 / 73    3000: 166 / 95    5003: 169 / 122
+//   8192: 170 / 159  12000: 183 / 232 (with this limit doubled)
 constexpr int kSmallN = 8192;  // sorted keys in LDS: 64 KB
 constexpr int kSmallT = 1024;
 
@@ -955,95 +832,81 @@ __global__ __launch_bounds__(kSmallT) void small_rank_kernel(const uint64_t* __r
 }
 
 // Everything after the sort.  Cell, image, group and item arrays hold cap
-// cells and n groups; more than cap cells are flagged (lv[].overflow) and the
-// host builds level by level.
+// cells and n groups; for more cells it only counts them, and the host calls
+// it again with larger arrays.
 __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
     Cells C, const uint64_t* __restrict__ key, const float4* __restrict__ part, int n, int n_leaf,
-    int n_group, int cap, double* box, double* mp64, Images I, Groups G, int32_t* at, int4* nchunk, int2* __restrict__ work, int2* __restrict__ wwork,
-    BuildInfo* __restrict__ info) {
+    int n_group, int cap, double* box, double* mp64, Images I, Groups G, int32_t* at, int4* nchunk,
+    int2* __restrict__ work, int2* __restrict__ wwork, BuildInfo* __restrict__ info) {
+  constexpr int kHeld = kSmallN / kSmallT, kRows = kSmallN / 64;
   __shared__ uint64_t skey[kSmallN];
+  __shared__ int8_t sw[2][kSmallN + kMaxLeaf];
+  __shared__ int rows[kLevels * kRows];
   __shared__ int sh[kSmallT / 64];
-  __shared__ int lbegs[kMaxDepth + 3];
-  const int t = threadIdx.x;
+  __shared__ int lbegs[kLevels + 1];
+  const int t = threadIdx.x, w = t >> 6;
   for (int i = t; i < n; i += kSmallT) {
     skey[i] = key[i];
     at[i] = -1;
   }
-  if (t == 0) {
-    C.first[0] = 0;
-    C.n[0] = n;
-    C.depth[0] = 0;
-    C.parent[0] = -1;
-    C.fc[0] = -1;
-    C.nc[0] = 0;
-  }
   __syncthreads();
 
-  // Subdivision: eight lanes per cell, as the level kernels.
-  int beg = 0, end = 1, levels = 0;
-  for (int L = 0; L <= kMaxDepth && beg < end; ++L) {
-    if (t == 0) lbegs[L] = beg;
-    int carry = 0;
-    for (int base = beg; base < end; base += kSmallT / 8) {
-      const int j = base + t / 8, d = t & 7;
-      const bool valid = j < end;
-      int a = 0, b = 0;
-      bool split = false;
-      if (valid) {
-        a = C.first[j];
-        b = a + C.n[j];
-        split = !(b - a <= n_leaf || L == kMaxDepth);
-      }
-      int l = a;
-      if (split && d > 0) {
-        const int sh3 = 3 * (kMaxDepth - 1 - L);
-        int h = b;
-        while (l < h) {
-          const int mid = l + ((h - l) >> 1);
-          if ((int)((skey[mid] >> sh3) & 7) < d) l = mid + 1;
-          else h = mid;
-        }
-      }
-      const int nx = __shfl_down(l, 1, 8);
-      const int hi = d == 7 ? b : nx;
-      const bool child = split && hi > l;
-      int k, before, step;
-      octant_counts(child, &k, &before);
-      const int ex = __shfl(small_exclusive(d == 0 && valid ? k : 0, &step, sh), (t & 63) & ~7);
-      if (end + carry + step > cap) {  // uniform
-        if (t == 0) info->lv[L].overflow = 1;
-        return;
-      }
-      const int first = end + carry + ex;
-      if (d == 0 && valid && k > 0) {
-        C.fc[j] = first;
-        C.nc[j] = k;
-      }
-      if (child) {
-        const int ch = first + before;
-        C.first[ch] = l;
-        C.n[ch] = hi - l;
-        C.depth[ch] = L + 1;
-        C.parent[ch] = j;
-        C.fc[ch] = -1;
-        C.nc[ch] = 0;
-      }
-      carry += step;
-    }
-    if (t == 0) info->lv[L] = Level{beg, end, carry, 0, 0};
-    beg = end;
-    end += carry;
-    levels = L + 1;
+  // Subdivision.
+  const int len = n + n_leaf;
+  for (int e = t; e < len; e += kSmallT) sw[0][e] = window_digits(skey, n, n_leaf, e - n_leaf);
+  __syncthreads();
+  int cur = 0, run = 1;
+  static_assert(kSmallT == kST, "join_windows");
+  for (; 2 * run <= n_leaf + 1; run *= 2, cur ^= 1) {
+    join_windows(sw[cur], sw[cur ^ 1], len, run);
     __syncthreads();
   }
-  const int nc = beg;
-  if (t >= levels && t < kMaxDepth + 2) info->lv[t] = Level{nc, nc, 0, 0, 0};
-  if (t == 0) lbegs[levels] = nc;
+  LevelRange r[kHeld];
+#pragma unroll
+  for (int q = 0; q < kHeld; ++q) {
+    const int i = q * kSmallT + t;
+    r[q] = LevelRange{1, 0};
+    if (i < n) r[q] = level_range(skey, i, max(sw[cur][i], sw[cur][i + n_leaf - run + 1]));
+    if (q * kSmallT < n) count_starts(r[q], rows + q * (kSmallT / 64) + w, kRows);
+    else if ((t & 63) < kLevels) rows[(t & 63) * kRows + q * (kSmallT / 64) + w] = 0;
+  }
   __syncthreads();
+  constexpr int kPer = (kLevels * kRows + kSmallT - 1) / kSmallT;
+  int mine[kPer], sum = 0, nc;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int e = t * kPer + k;
+    mine[k] = e < kLevels * kRows ? rows[e] : 0;
+    sum += mine[k];
+  }
+  int before = small_exclusive(sum, &nc, sh);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int e = t * kPer + k;
+    if (e < kLevels * kRows) rows[e] = before;
+    before += mine[k];
+  }
+  __syncthreads();
+  if (t <= kLevels) {
+    lbegs[t] = t < kLevels ? rows[t * kRows] : nc;
+    info->level[t] = lbegs[t];
+  }
+  if (nc > cap) return;  // uniform
+#pragma unroll
+  for (int q = 0; q < kHeld; ++q)
+    if (q * kSmallT < n)
+      write_cells(C, skey, n, q * kSmallT + t, r[q], n_leaf, cap, rows + q * (kSmallT / 64) + w,
+                  kRows);
+  __syncthreads();
+  int levels = 0;
+  while (levels < kLevels && lbegs[levels] < nc) ++levels;
 
   // Boxes and moments: the leaves, then level by level upwards (the deepest
   // level holds only leaves).
-  for (int c = t; c < nc; c += kSmallT) cell_moments<true>(C, part, c, box, mp64);
+  for (int c = t; c < nc; c += kSmallT) {
+    close_parent(C, c, nc);
+    cell_moments<true>(C, part, c, box, mp64);
+  }
   __syncthreads();
   for (int L = levels - 2; L >= 0; --L) {
     for (int c = lbegs[L] + t; c < lbegs[L + 1]; c += kSmallT) cell_moments<false>(C, part, c, box, mp64);
@@ -1205,6 +1068,10 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
                       int n_leaf, int n_group, HostTree& h, DevTree& dt, DeviceArrays& out,
                       DevAlloc& alloc, void* stream, std::string& err, BuildPools* pools) {
   hipStream_t s = (hipStream_t)stream;
+  if (n_leaf < 1 || n_leaf > kMaxLeaf) {  // (the callers have checked it)
+    err = "n_leaf out of range";
+    return -1;
+  }
   if (pools) {
     pools->outer.rewind();
     pools->cells.rewind();
@@ -1273,12 +1140,13 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   // Keys and the stable sort (ties keep the input order).
   uint64_t* key = S.get<uint64_t>(n);
   uint64_t* key2 = S.get<uint64_t>(n);
-  int32_t* idx = S.get<int32_t>(n);
   int32_t* perm = nullptr;
-  if (!key || !key2 || !idx || alloc.alloc((void**)&perm, (size_t)n * 4)) return fail("device allocation failed");
-  float4* packed = S.get<float4>(n);
-  if (!packed) return fail("device allocation failed");
+  float4* packed = nullptr;
+  if (!key || !key2 || alloc.alloc((void**)&perm, (size_t)n * 4)) return fail("device allocation failed");
   if (!small) {
+    int32_t* idx = S.get<int32_t>(n);
+    packed = S.get<float4>(n);
+    if (!idx || !packed) return fail("device allocation failed");
     keys_kernel<<<blocks(n), kT, 0, s>>>(pos, mass, n, info->cube, key, idx, packed);
     size_t sbytes = 0;
     if (hipcub::DeviceRadixSort::SortPairs(nullptr, sbytes, key, key2, idx, perm, (int)n, 0, 63,
@@ -1291,49 +1159,29 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
       return fail("sort failed");
   }
 
-  // Level-synchronous subdivision; cell arrays grow as needed.
+  // Cell arrays, for twice the particles at first; a tree of more cells has
+  // them written again into larger ones.
   int64_t cap = 2 * n + 64;
   Cells C{};
-  auto grow = [&](int64_t need) -> bool {
-    if (need <= cap && C.first) return true;
-    const int64_t nc2 = C.first ? std::max(need, cap + cap / 2) : need;
-    Cells D{CS.get<int32_t>(nc2), CS.get<int32_t>(nc2), CS.get<int32_t>(nc2),
-            CS.get<int32_t>(nc2), CS.get<int32_t>(nc2), CS.get<int32_t>(nc2)};
-    if (!D.first || !D.n || !D.depth || !D.parent || !D.fc || !D.nc) return false;
-    if (C.first) {
-      int32_t* src[6] = {C.first, C.n, C.depth, C.parent, C.fc, C.nc};
-      int32_t* dst[6] = {D.first, D.n, D.depth, D.parent, D.fc, D.nc};
-      for (int k = 0; k < 6; ++k)
-        if (hipMemcpyAsync(dst[k], src[k], (size_t)cap * 4, hipMemcpyDeviceToDevice, s) != hipSuccess)
-          return false;
-    }
-    C = D;
-    cap = nc2;
-    return true;
+  auto cell_arrays = [&]() {
+    C = Cells{CS.get<int32_t>(cap), CS.get<int32_t>(cap), CS.get<int32_t>(cap),
+              CS.get<int32_t>(cap), CS.get<int32_t>(cap), CS.get<int32_t>(cap)};
+    return C.first && C.n && C.depth && C.parent && C.fc && C.nc;
   };
-  if (!grow(cap)) return fail("device allocation failed");
-  std::vector<int64_t> level_beg{0};
-  int64_t lbeg = 0, lend = 1;
-  // The scalars of the levels, once fetched: the verdict on the inputs and the
-  // root cube; without an overflow also the level ranges (lbeg = lend = all
-  // cells then).
+  if (!cell_arrays()) return fail("device allocation failed");
+  // The scalars of the levels, once fetched: the verdict on the inputs, the
+  // root cube, and the level ranges.
+  int64_t nc = 0;
   auto read_levels = [&]() -> const char* {
     if (hinfo->bad & 1) return "positions must be finite with |x| < 2^60";
     if (hinfo->bad & 2) return "masses must be finite and > 0";
     for (int k = 0; k < 3; ++k) h.corner[k] = hinfo->cube[k];
     h.side = hinfo->cube[3];
-    bool over = false;
-    for (const Level& v : hinfo->lv) over = over || v.overflow;
-    if (over) return nullptr;
-    int levels = 0;
-    for (int L = 0; L <= kMaxDepth && hinfo->lv[L].end > hinfo->lv[L].beg; ++L) {
-      h.max_level_cells = std::max(h.max_level_cells, hinfo->lv[L].end - hinfo->lv[L].beg);
-      if (hinfo->lv[L].total > 0) h.max_depth = L + 1;
-      level_beg.push_back(hinfo->lv[L].end);
-      lbeg = lend = hinfo->lv[L].end;
-      levels = L + 1;
+    nc = hinfo->level[kLevels];
+    for (int L = 0; L < kLevels && hinfo->level[L] < nc; ++L) {
+      h.max_level_cells = std::max(h.max_level_cells, hinfo->level[L + 1] - hinfo->level[L]);
+      h.max_depth = L;
     }
-    if (pools) pools->last_levels = levels;
     return nullptr;
   };
 
@@ -1355,7 +1203,6 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
            A(&fcell, 2 * ncb) && A(&depth, ncb) && A(&groups, ngb) && A(&ginfo, ngb) &&
            A(&gbox, 2 * ngb) && A(&work, nwb) && A(&wwork, nwb);
   };
-  bool done = false;
   if (small) {
     const int64_t ngb = std::min(cap, n);
     int32_t* at = S.get<int32_t>(n);
@@ -1365,90 +1212,46 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
         pos, mass, (int)n, info, key);
     small_rank_kernel<<<((int)n + kRankKeys - 1) / kRankKeys, kSmallT, 0, s>>>(
         key, pos, mass, (int)n, key2, perm, part, iperm);
-    small_tree_kernel<<<1, kSmallT, 0, s>>>(
-        C, key2, part, (int)n, n_leaf, n_group, (int)cap, box, mp64,
-        Images{topo, geo_host, geo, wrec, mp, fcell, depth}, Groups{groups, ginfo, gbox}, at, nchunk,
-        work, wwork, info);
-    if (!fetch(0, sizeof(BuildInfo))) return fail("build failed");
-    if (const char* e = read_levels()) return fail(e);
-    done = lbeg == lend;
-  }
-  // All levels back to back with their ranges on the device (no host round
-  // trip per level); a tree that outgrows the cell arrays is redone below
-  // level by level, growing them.
-  if (!small) {
-    Level* lv = info->lv;
-    int32_t* bsum = S.get<int32_t>(kLB);
-    // The octant boundaries (eight per cell) go into the unsorted keys, dead
-    // after the sort: levels of up to n / 4 cells keep them, larger ones
-    // (only trees with very small leaves) are searched again.
-    int32_t* bnd = reinterpret_cast<int32_t*>(key);
-    const int64_t bcap = n / 4;
-    if (!bsum) return fail("device allocation failed");
-    level_init_kernel<<<1, 64, 0, s>>>(C, lv, (int32_t)n);
-    // A rebuild launches the levels its previous tree had plus two, then
-    // looks whether the next one is empty (an empty level still costs two
-    // launches); the rest follow only if the tree turned out deeper.  The
-    // copy also brings the input check and the root cube.
-    int L0 = 0, L1 = kMaxDepth;
-    if (pools && pools->last_levels > 0) L1 = std::min(kMaxDepth, pools->last_levels + 1);
     for (;;) {
-      for (int L = L0; L <= L1; ++L) {
-        split_level_kernel<<<kLB, kT, 0, s>>>(C, key2, lv, L, n_leaf, bsum, bnd, bcap);
-        emit_level_kernel<<<kLB, kT, 0, s>>>(C, key2, lv, L, n_leaf, bsum, bnd, bcap, cap);
-      }
-      if (!fetch(0, offsetof(BuildInfo, ng))) return fail("subdivision failed");
-      if (L1 == kMaxDepth || hinfo->lv[L1 + 1].end == hinfo->lv[L1 + 1].beg) break;
-      L0 = L1 + 1;
-      L1 = kMaxDepth;
+      small_tree_kernel<<<1, kSmallT, 0, s>>>(
+          C, key2, part, (int)n, n_leaf, n_group, (int)cap, box, mp64,
+          Images{topo, geo_host, geo, wrec, mp, fcell, depth}, Groups{groups, ginfo, gbox}, at,
+          nchunk, work, wwork, info);
+      if (!fetch(0, sizeof(BuildInfo))) return fail("build failed");
+      if (const char* e = read_levels()) return fail(e);
+      if (nc <= cap) break;
+      cap = nc;
+      const float4* ordered = part;
+      const int32_t* places = iperm;
+      if (!cell_arrays() || !persistent(cap, n)) return fail("device allocation failed");
+      if (hipMemcpyAsync(part, ordered, (size_t)n * 16, hipMemcpyDeviceToDevice, s) != hipSuccess ||
+          hipMemcpyAsync(iperm, places, (size_t)n * 4, hipMemcpyDeviceToDevice, s) != hipSuccess)
+        return fail("copy failed");
     }
+  } else {
+    // Cells of all levels.
+    const int nb = (int)((n + kST - 1) / kST);
+    uchar2* range = S.get<uchar2>(n);
+    int32_t* cnt = S.get<int32_t>((int64_t)kLevels * nb + 1);
+    int32_t* before = S.get<int32_t>((int64_t)kLevels * nb + 1);
+    if (!range || !cnt || !before) return fail("device allocation failed");
+    starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt);
+    if (exclusive_sum(cnt, before, (int64_t)kLevels * nb + 1, S, s)) return fail("scan failed");
+    cells_kernel<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, before, cap, info->level);
+    if (!fetch(0, offsetof(BuildInfo, ng))) return fail("subdivision failed");
     if (const char* e = read_levels()) return fail(e);
-  }
-  if (lbeg < lend) {  // the arrays overflowed: level by level with growth
-    const int32_t root[6] = {0, (int32_t)n, 0, -1, -1, 0};
-    int32_t* rdst[6] = {C.first, C.n, C.depth, C.parent, C.fc, C.nc};
-    for (int k = 0; k < 6; ++k)
-      if (hipMemcpyAsync(rdst[k], &root[k], 4, hipMemcpyHostToDevice, s) != hipSuccess)
-        return fail("root upload failed");
-    if (small) keys_kernel<<<blocks(n), kT, 0, s>>>(pos, mass, n, info->cube, key, idx, packed);
-  }
-  for (int L = 0; lbeg < lend; ++L) {
-    const int64_t m = lend - lbeg;
-    if (pools) pools->level.rewind();  // the previous level's scratch is dead
-    Scratch LS(pools ? &pools->level : nullptr);
-    int32_t* bd = LS.get<int32_t>(9 * m);
-    int32_t* nkid = LS.get<int32_t>(m + 1);
-    int32_t* pre = LS.get<int32_t>(m + 1);
-    if (!bd || !nkid || !pre) return fail("device allocation failed");
-    split_kernel<<<blocks(m), kT, 0, s>>>(C, key2, lbeg, m, L, n_leaf, bd, nkid);
-    if (hipMemsetAsync(nkid + m, 0, 4, s) != hipSuccess) return fail("memset failed");
-    if (exclusive_sum(nkid, pre, m + 1, LS, s)) return fail("scan failed");
-    int32_t total = 0;
-    if (hipMemcpyAsync(&total, pre + m, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return fail("level count failed");
-    if (total > 0) {
-      if (!grow(lend + total)) return fail("device allocation failed");
-      emit_kernel<<<blocks(m), kT, 0, s>>>(C, lbeg, lend, m, L, bd, nkid, pre);
+    if (nc > cap) {
+      cap = nc;
+      if (!cell_arrays()) return fail("device allocation failed");
+      cells_kernel<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, before, cap, info->level);
     }
-    h.max_level_cells = std::max(h.max_level_cells, m);
-    if (total > 0) h.max_depth = L + 1;
-    lbeg = lend;
-    lend += total;
-    level_beg.push_back(lbeg);  // level L spans [level_beg[L], level_beg[L + 1])
-    // Fresh level scratch is freed at the end of the iteration: let the level
-    // finish first (pool slots are reused in stream order instead).
-    if (!pools && hipStreamSynchronize(s) != hipSuccess) return fail("subdivision failed");
-  }
-  const int64_t nc = lend;
-  if (!done) {
     // Groups <= cells, so that the group and item counts come back in one copy at
     // the end.
     if (!persistent(nc, nc)) return fail("device allocation failed");
     gather_kernel<<<blocks(n), kT, 0, s>>>(packed, perm, n, part, iperm);
     moments_kernel<true><<<blocks(nc), kT, 0, s>>>(C, part, 0, nc, box, mp64);
     for (int L = h.max_depth - 1; L >= 0; --L) {  // the deepest level holds only leaves
-      const int64_t a = level_beg[L], b = level_beg[L + 1];
+      const int64_t a = hinfo->level[L], b = hinfo->level[L + 1];
       if (b > a) moments_kernel<false><<<blocks(b - a), kT, 0, s>>>(C, part, a, b, box, mp64);
     }
     const int64_t nbi = blocks(nc);

@@ -148,3 +148,24 @@ def test_one_block_build_keeps_the_order_of_ties(n):
     rng = np.random.default_rng(n)
     pos = (rng.integers(-1, 2, (n, 3)) * 0.5).astype(np.float32)
     _same_tree(pos, rng.uniform(0.5, 2.0, n).astype(np.float32), 16, 64)
+
+
+# The subdivision above the one-block limit: edges of its blocks of 1024 particles, the range of n_leaf,
+# deep ties.
+@pytest.mark.parametrize("n,n_leaf", [(8193, 1), (9216, 1), (9217, 2), (10240, 16), (20000, 3), (20000, 31),
+                                      (30721, 63), (70000, 64)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_subdivision_matches_host(n, n_leaf, ties):
+    _torch()
+    pos, m = W.plummer_clumps(n, n)
+    if ties:
+        pos = (np.round(pos * 4) / 4).astype(np.float32)
+    _same_tree(pos, m, n_leaf, 64)
+
+
+def test_large_build_outgrows_its_arrays():
+    """As above with more particles than one block takes: the cells are written again into larger arrays."""
+    _torch()
+    p = np.random.default_rng(4).uniform(-1, 1, (6000, 3))
+    H, D = _same_tree(np.concatenate([p, p]).astype(np.float32), np.full(12000, 1 / 12000, np.float32), 1, 4)
+    assert H.stats["n_cells"] > 2 * 12000 + 64
