@@ -190,7 +190,8 @@ struct Cells {
 // starts with it.  (Level by level, two launches each, this was 125 us of a
 // rebuild of 262144 particles; count, scan and write are 20, with fewer gaps.
 // Whole rebuild, before and now, us: 16384 263 / 173, 65536 297 / 214, 262144
-// 394 / 300, 1M 655 / 527.)
+// 394 / 300, 1M 655 / 527; with the moments of
+// inner_moments below 151, 202, 273, 475.)
 constexpr int kMaxLeaf = 64;            // largest n_leaf
 constexpr int kLevels = kMaxDepth + 1;  // levels 0 ... kMaxDepth
 constexpr int kST = 1024;               // particles, and threads, per block
@@ -238,7 +239,7 @@ __device__ __forceinline__ void count_starts(LevelRange r, int* row, int stride)
 // Writes the cells that start at the wave's particles (this lane's: i), as
 // far as they fit cap cells; row[L * stride]: the number of the wave's first
 // cell of level L.  Particle and child counts of split cells follow later
-// (close_parent, inner cell_moments).
+// (close_parent, inner_moments).
 __device__ __forceinline__ void write_cells(const Cells& C, const uint64_t* key, int32_t n,
                                             int32_t i, LevelRange r, int n_leaf, int64_t cap,
                                             const int* row, int stride) {
@@ -368,125 +369,57 @@ __global__ void gather_kernel(const float4* __restrict__ packed, const int32_t* 
 __device__ __forceinline__ double hmin(double a, double b) { return b < a ? b : a; }
 __device__ __forceinline__ double hmax(double a, double b) { return a < b ? b : a; }
 
-// Box and FP64 moments of one cell, as the host computes them.  The loads of
-// a leaf's particles (kMomChunk at a time) and of a cell's
-// children (four at a time) are issued before their sums, so a cell costs a
-// few memory round trips instead of one per particle or child.  The sums keep the
-// host's order; a slot past the end repeats the last particle or child with
-// weight +0, which leaves every sum and the box unchanged bit for bit (the
-// sums start at +0 and the inputs are finite).
+// Box and FP64 moments of leaf c (nothing if it has children), as the host
+// computes them.  The loads of its particles (kMomChunk at a time) are issued
+// before their sums, so a leaf costs a few memory round trips instead of one
+// per particle.  The sums keep the host's order; a slot past the end repeats
+// the last particle with weight +0, which leaves every sum and the box
+// unchanged bit for bit (the sums start at +0 and the inputs are finite).
 constexpr int kMomChunk = 16;
-// LEAVES: cell c if it is a leaf, else nothing; otherwise cell c if it has
-// children (whose moments are done), else nothing; then also its particle
-// count.
-template <bool LEAVES>
-__device__ __forceinline__ void cell_moments(const Cells& C, const float4* __restrict__ part,
+__device__ __forceinline__ void leaf_moments(const Cells& C, const float4* __restrict__ part,
                                              int64_t c, double* __restrict__ box,
                                              double* __restrict__ mp64) {
 #pragma clang fp contract(off)
+  if (C.fc[c] >= 0) return;
   double bx[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
   double M = 0, sx = 0, sy = 0, sz = 0;
   double Q[6] = {0, 0, 0, 0, 0, 0};
-  double com[3];
-  const bool leaf = C.fc[c] < 0;
-  if (leaf != LEAVES) return;
-  if (LEAVES) {
-    const int32_t f = C.first[c], e = f + C.n[c];
-    for (int32_t i0 = f; i0 < e; i0 += kMomChunk) {
-      float4 pb[kMomChunk];
+  const int32_t f = C.first[c], e = f + C.n[c];
+  for (int32_t i0 = f; i0 < e; i0 += kMomChunk) {
+    float4 pb[kMomChunk];
 #pragma unroll
-      for (int k = 0; k < kMomChunk; ++k) pb[k] = part[i0 + k < e ? i0 + k : e - 1];
+    for (int k = 0; k < kMomChunk; ++k) pb[k] = part[i0 + k < e ? i0 + k : e - 1];
 #pragma unroll
-      for (int k = 0; k < kMomChunk; ++k) {
-        const double x[3] = {pb[k].x, pb[k].y, pb[k].z};
-        for (int d = 0; d < 3; ++d) {
-          bx[d] = hmin(bx[d], x[d]);
-          bx[3 + d] = hmax(bx[3 + d], x[d]);
-        }
-        const double w = i0 + k < e ? (double)pb[k].w : 0.0;
-        M += w;
-        sx += w * x[0];
-        sy += w * x[1];
-        sz += w * x[2];
+    for (int k = 0; k < kMomChunk; ++k) {
+      const double x[3] = {pb[k].x, pb[k].y, pb[k].z};
+      for (int d = 0; d < 3; ++d) {
+        bx[d] = hmin(bx[d], x[d]);
+        bx[3 + d] = hmax(bx[3 + d], x[d]);
       }
+      const double w = i0 + k < e ? (double)pb[k].w : 0.0;
+      M += w;
+      sx += w * x[0];
+      sy += w * x[1];
+      sz += w * x[2];
     }
-    com[0] = sx / M;
-    com[1] = sy / M;
-    com[2] = sz / M;
-    for (int32_t i0 = f; i0 < e; i0 += kMomChunk) {
-      float4 pb[kMomChunk];
+  }
+  const double com[3] = {sx / M, sy / M, sz / M};
+  for (int32_t i0 = f; i0 < e; i0 += kMomChunk) {
+    float4 pb[kMomChunk];
 #pragma unroll
-      for (int k = 0; k < kMomChunk; ++k) pb[k] = part[i0 + k < e ? i0 + k : e - 1];
+    for (int k = 0; k < kMomChunk; ++k) pb[k] = part[i0 + k < e ? i0 + k : e - 1];
 #pragma unroll
-      for (int k = 0; k < kMomChunk; ++k) {
-        const float4 p = pb[k];
-        const double d0 = p.x - com[0], d1 = p.y - com[1], d2 = p.z - com[2];
-        const double w = i0 + k < e ? (double)p.w : 0.0;
-        const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-        Q[0] += w * (3 * d0 * d0 - r2);
-        Q[1] += w * (3 * d1 * d1 - r2);
-        Q[2] += w * (3 * d2 * d2 - r2);
-        Q[3] += w * 3 * d0 * d1;
-        Q[4] += w * 3 * d0 * d2;
-        Q[5] += w * 3 * d1 * d2;
-      }
-    }
-  } else {
-    // Children in two batches of four (a batch's loads first, then its sums
-    // in child order), which keeps the kernel at a few waves per SIMD.
-    const int32_t f = C.fc[c], nk = C.nc[c];  // 1 ... 8 children
-    C.n[c] = C.first[f + nk - 1] + C.n[f + nk - 1] - C.first[c];
-#pragma unroll 1
-    for (int h = 0; h < nk; h += 4) {
-      double cb[4][6], cm[4][4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int64_t ch = f + (h + k < nk ? h + k : nk - 1);
-#pragma unroll
-        for (int d = 0; d < 6; ++d) cb[k][d] = box[6 * ch + d];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) cm[k][d] = mp64[10 * ch + d];
-        if (h + k >= nk) cm[k][0] = 0.0;
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        for (int d = 0; d < 3; ++d) {
-          bx[d] = hmin(bx[d], cb[k][d]);
-          bx[3 + d] = hmax(bx[3 + d], cb[k][3 + d]);
-        }
-        M += cm[k][0];
-        sx += cm[k][0] * cm[k][1];
-        sy += cm[k][0] * cm[k][2];
-        sz += cm[k][0] * cm[k][3];
-      }
-    }
-    com[0] = sx / M;
-    com[1] = sy / M;
-    com[2] = sz / M;
-#pragma unroll 1
-    for (int h = 0; h < nk; h += 4) {
-      double cq[4][10];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int64_t ch = f + (h + k < nk ? h + k : nk - 1);
-#pragma unroll
-        for (int d = 0; d < 10; ++d) cq[k][d] = mp64[10 * ch + d];
-        if (h + k >= nk)
-          for (int d = 0; d < 10; ++d) cq[k][d] = d == 0 ? 0.0 : (d < 4 ? com[d - 1] : 0.0);
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const double* q = cq[k];
-        const double d0 = q[1] - com[0], d1 = q[2] - com[1], d2 = q[3] - com[2];
-        const double w = q[0];
-        const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-        Q[0] += q[4] + w * (3 * d0 * d0 - r2);
-        Q[1] += q[5] + w * (3 * d1 * d1 - r2);
-        Q[2] += q[6] + w * (3 * d2 * d2 - r2);
-        Q[3] += q[7] + w * 3 * d0 * d1;
-        Q[4] += q[8] + w * 3 * d0 * d2;
-        Q[5] += q[9] + w * 3 * d1 * d2;
-      }
+    for (int k = 0; k < kMomChunk; ++k) {
+      const float4 p = pb[k];
+      const double d0 = p.x - com[0], d1 = p.y - com[1], d2 = p.z - com[2];
+      const double w = i0 + k < e ? (double)p.w : 0.0;
+      const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+      Q[0] += w * (3 * d0 * d0 - r2);
+      Q[1] += w * (3 * d1 * d1 - r2);
+      Q[2] += w * (3 * d2 * d2 - r2);
+      Q[3] += w * 3 * d0 * d1;
+      Q[4] += w * 3 * d0 * d2;
+      Q[5] += w * 3 * d1 * d2;
     }
   }
   double* o = box + 6 * c;
@@ -497,19 +430,125 @@ __device__ __forceinline__ void cell_moments(const Cells& C, const float4* __res
   for (int k = 0; k < 6; ++k) q[4 + k] = Q[k];
 }
 
-// One thread per cell.  LEAVES: the leaves among all cells [a, b) (leaves need
-// only their particles), and every parent's number of children; otherwise the
-// cells with children among the cells [a, b) of one level, after the levels
-// below.
-template <bool LEAVES>
-__global__ __launch_bounds__(kT) void moments_kernel(Cells C, const float4* __restrict__ part,
-                                                     int64_t a, int64_t b,
-                                                     double* __restrict__ box,
-                                                     double* __restrict__ mp64) {
-  const int64_t c = a + (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (c >= b) return;
-  if (LEAVES) close_parent(C, c, b);
-  cell_moments<LEAVES>(C, part, c, box, mp64);
+// Every leaf (leaves need only their particles) and every parent's number of
+// children, one thread per cell.
+__global__ __launch_bounds__(kT) void leaf_moments_kernel(Cells C, const float4* __restrict__ part,
+                                                          int64_t nc, double* __restrict__ box,
+                                                          double* __restrict__ mp64) {
+  const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
+  if (c >= nc) return;
+  close_parent(C, c, nc);
+  leaf_moments(C, part, c, box, mp64);
+}
+
+// Lane K of each group of eight lanes (the LDS crossbar's bit-mask mode).
+template <int K>
+__device__ __forceinline__ double of_lane8(double v) {
+  constexpr int m = K << 5 | 0x18;
+  return __hiloint2double(__builtin_amdgcn_ds_swizzle(__double2hiint(v), m),
+                          __builtin_amdgcn_ds_swizzle(__double2loint(v), m));
+}
+
+// Box, FP64 moments and particle count of cell c from its children's (nothing
+// if it is a leaf, or !valid), by the eight lanes of a group, which all come
+// here with the same c.  Lane d loads child d, so the children arrive in one
+// memory latency, and forms its terms; the terms change places through LDS so
+// that lane d then folds quantity d over the children in their order, as the
+// host does (a box's upper side as the minimum of the negated sides, which
+// picks the same values).  A lane without a child has terms +0 and infinity,
+// which leave every sum and side unchanged bit for bit.  One thread per cell, four children at
+// a time, took four latencies and the serial chains of ten quantities: 6.9 us a
+// level of 262144 particles' tree, now 4.1, and 5003 particles in one block
+// 121 -> 106 us a rebuild.  (With the terms exchanged by ds_swizzle, 176 a
+// wave, the block was slower than one thread per cell.)
+constexpr int kFoldRow = 66;  // 64 terms a quantity; rows start four banks apart
+struct FoldBuf {
+  double t[8][kFoldRow];
+};
+__device__ __forceinline__ double fold8(const FoldBuf& F, bool sum) {
+#pragma clang fp contract(off)
+  const double* t = &F.t[threadIdx.x & 7][threadIdx.x & 56];
+  double v[8], s = sum ? 0.0 : (double)INFINITY;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = t[k];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const double a = s + v[k], m = v[k] < s ? v[k] : s;
+    s = sum ? a : m;
+  }
+  return s;
+}
+// The wave's LDS accesses before come before those after.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void inner_moments(const Cells& C, int64_t c, bool valid, FoldBuf& F,
+                                              double* __restrict__ box,
+                                              double* __restrict__ mp64) {
+#pragma clang fp contract(off)
+  const int d = threadIdx.x & 7, lane = threadIdx.x & 63;
+  const int32_t f = valid ? C.fc[c] : -1;
+  if (!__any(f >= 0)) return;
+  const int nk = f >= 0 ? C.nc[c] : 0;
+  const bool live = d < nk;
+  const int64_t ch = live ? (int64_t)f + d : 0;
+  double bx[6], q[10];
+  for (int k = 0; k < 6; ++k) bx[k] = box[6 * ch + k];
+  for (int k = 0; k < 10; ++k) q[k] = mp64[10 * ch + k];
+  if (d == nk - 1) C.n[c] = C.first[ch] + C.n[ch] - C.first[c];
+  const double w = live ? q[0] : 0.0;
+  for (int k = 0; k < 6; ++k) bx[k] = live ? (k < 3 ? bx[k] : -bx[k]) : (double)INFINITY;
+  F.t[0][lane] = w;
+  for (int k = 1; k < 4; ++k) F.t[k][lane] = live ? w * q[k] : 0.0;
+  for (int k = 0; k < 4; ++k) F.t[4 + k][lane] = bx[k];
+  wave_lds_order();
+  // M, the sums of m x, the lower sides and the first upper side
+  double s = fold8(F, d < 4);
+  const double M = of_lane8<0>(s);
+  if (d > 0 && d < 4) s = s / M;
+  const double com[3] = {of_lane8<1>(s), of_lane8<2>(s), of_lane8<3>(s)};
+  if (nk > 0) *(d < 4 ? mp64 + 10 * c + d : box + 6 * c + (d - 4)) = d == 7 ? -s : s;
+  const double d0 = q[1] - com[0], d1 = q[2] - com[1], d2 = q[3] - com[2];
+  const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+  const double Q[6] = {q[4] + w * (3 * d0 * d0 - r2), q[5] + w * (3 * d1 * d1 - r2),
+                       q[6] + w * (3 * d2 * d2 - r2), q[7] + w * 3 * d0 * d1,
+                       q[8] + w * 3 * d0 * d2,        q[9] + w * 3 * d1 * d2};
+  wave_lds_order();
+  for (int k = 0; k < 6; ++k) F.t[k][lane] = live ? Q[k] : 0.0;
+  for (int k = 6; k < 8; ++k) F.t[k][lane] = bx[k - 2];
+  wave_lds_order();
+  s = fold8(F, d < 6);
+  if (nk > 0) *(d < 6 ? mp64 + 10 * c + 4 + d : box + 6 * c + (d - 2)) = d < 6 ? s : -s;
+  wave_lds_order();
+}
+
+// Cells [a, b) of one level, after the levels below it.
+__global__ __launch_bounds__(kT) void inner_moments_kernel(Cells C, int64_t a, int64_t b,
+                                                           double* __restrict__ box,
+                                                           double* __restrict__ mp64) {
+  __shared__ FoldBuf F[kT / 64];
+  const int64_t c = a + ((int64_t)blockIdx.x * kT + threadIdx.x) / 8;
+  inner_moments(C, c, c < b, F[threadIdx.x >> 6], box, mp64);
+}
+
+// Levels L ... 0, of at most kTopCells cells each, by one block: B.at[L] ...
+// B.at[L + 1] are level L's cells.  (16384 and 262144 particles: 151 and 273 us
+// a rebuild, without it 157 and 281, with levels of up to 1024 cells 163 and 281.)
+constexpr int kTopCells = 128, kTopT = 1024;
+struct LevelBegin {
+  int32_t at[kLevels + 1];
+};
+__global__ __launch_bounds__(kTopT) void top_moments_kernel(Cells C, LevelBegin B, int L,
+                                                            double* box, double* mp64) {
+  __shared__ FoldBuf F[kTopT / 64];
+  for (; L >= 0; --L) {
+    for (int base = B.at[L]; base < B.at[L + 1]; base += kTopT / 8) {
+      const int c = base + (int)threadIdx.x / 8;
+      inner_moments(C, c, c < B.at[L + 1], F[threadIdx.x >> 6], box, mp64);
+    }
+    __syncthreads();
+  }
 }
 
 // Arrays of FP32 images per cell (images_kernel).
@@ -680,8 +719,8 @@ struct BuildInfo {
 // rest) do what the kernels above and below do in about 30, which for a few
 // thousand particles are all launch and latency.  The same functions and orders, so the
 // same tree.  Rebuild of a Plummer sphere, many launches against three, in us:
-//   300: 148 / 61    1000: 151 / 73    3000: 166 / 95    5003: 169 / 122
-//   8192: 170 / 159  12000: 183 / 232 (with this limit doubled)
+//   300: 130 / 52    1000: 133 / 60    3000: 147 / 83    5003: 149 / 106
+//   8192: 150 / 146
 constexpr int kSmallN = 8192;  // sorted keys in LDS: 64 KB
 constexpr int kSmallT = 1024;
 
@@ -839,8 +878,16 @@ __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
     int n_group, int cap, double* box, double* mp64, Images I, Groups G, int32_t* at, int4* nchunk,
     int2* __restrict__ work, int2* __restrict__ wwork, BuildInfo* __restrict__ info) {
   constexpr int kHeld = kSmallN / kSmallT, kRows = kSmallN / 64;
-  __shared__ uint64_t skey[kSmallN];
-  __shared__ int8_t sw[2][kSmallN + kMaxLeaf];
+  struct Split {
+    uint64_t key[kSmallN];
+    int8_t sw[2][kSmallN + kMaxLeaf];
+  };
+  __shared__ union {
+    Split split;
+    FoldBuf fold[kSmallT / 64];
+  } u;  // one after the other
+  uint64_t* skey = u.split.key;
+  auto& sw = u.split.sw;
   __shared__ int rows[kLevels * kRows];
   __shared__ int sh[kSmallT / 64];
   __shared__ int lbegs[kLevels + 1];
@@ -905,11 +952,14 @@ __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
   // level holds only leaves).
   for (int c = t; c < nc; c += kSmallT) {
     close_parent(C, c, nc);
-    cell_moments<true>(C, part, c, box, mp64);
+    leaf_moments(C, part, c, box, mp64);
   }
   __syncthreads();
   for (int L = levels - 2; L >= 0; --L) {
-    for (int c = lbegs[L] + t; c < lbegs[L + 1]; c += kSmallT) cell_moments<false>(C, part, c, box, mp64);
+    for (int base = lbegs[L]; base < lbegs[L + 1]; base += kSmallT / 8) {
+      const int c = base + t / 8;
+      inner_moments(C, c, c < lbegs[L + 1], u.fold[w], box, mp64);
+    }
     __syncthreads();
   }
 
@@ -1249,11 +1299,16 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     // the end.
     if (!persistent(nc, nc)) return fail("device allocation failed");
     gather_kernel<<<blocks(n), kT, 0, s>>>(packed, perm, n, part, iperm);
-    moments_kernel<true><<<blocks(nc), kT, 0, s>>>(C, part, 0, nc, box, mp64);
-    for (int L = h.max_depth - 1; L >= 0; --L) {  // the deepest level holds only leaves
+    leaf_moments_kernel<<<blocks(nc), kT, 0, s>>>(C, part, nc, box, mp64);
+    LevelBegin B{};
+    int top = 0;  // levels 0 ... top - 1 go to one block
+    while (top < h.max_depth && hinfo->level[top + 1] - hinfo->level[top] <= kTopCells) ++top;
+    for (int L = 0; L <= top; ++L) B.at[L] = (int32_t)hinfo->level[L];
+    for (int L = h.max_depth - 1; L >= top; --L) {  // the deepest level holds only leaves
       const int64_t a = hinfo->level[L], b = hinfo->level[L + 1];
-      if (b > a) moments_kernel<false><<<blocks(b - a), kT, 0, s>>>(C, part, a, b, box, mp64);
+      inner_moments_kernel<<<blocks(8 * (b - a)), kT, 0, s>>>(C, a, b, box, mp64);
     }
+    if (top > 0) top_moments_kernel<<<1, kTopT, 0, s>>>(C, B, top - 1, box, mp64);
     const int64_t nbi = blocks(nc);
     int32_t* nleaf = S.get<int32_t>(nbi);
     if (!nleaf) return fail("device allocation failed");
