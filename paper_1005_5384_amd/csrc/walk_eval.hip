@@ -21,7 +21,7 @@
 // eight lanes, one per child.  Evaluation: the wave splits into S = floor(64 / n)
 // slices of n lanes; every slice holds all n targets and takes every S-th
 // source of a tile; plain FP32 per tile is folded into compensated pairs;
-// slices are combined in slice order.
+// slices are added up pairwise in a fixed order.
 //
 // Bound: VALU issue.  Measured costs per wave instruction and SIMD with four
 // waves (cycles): 2.4 for FP32 and integer additions and FP32 multiplies on
@@ -69,11 +69,12 @@ constexpr int kRingW = 128;  // pending cells / leaves (two tiles)
 // ids < 2^29).
 template <int QCAP>
 struct WShared {
+  static constexpr int kRing = kRingW;
   int q[QCAP];
   int cring[kRingW];
   int2 lring[kRingW];  // (first particle, n particles) of opened leaves
   // Source tile: cells (com, M) [64], (Qxx, Qyy, Qzz, Qxy) [64], (Qxz, Qyz,
-  // -, -) [64], or particles [64]; the network's rows; the slices' sums.
+  // -, -) [64], or particles [64]; the network's rows; a wave's sums.
   float4 tile[3 * kTileW];
   int mark[kTileW];
 };
@@ -101,6 +102,21 @@ __device__ __forceinline__ float4 load_f4(const float4* p) {
   return make_float4(v[0], v[1], v[2], v[3]);
 }
 
+// Sums of the four values of lanes 0 ... 31 in a fixed order, stored by lanes 0
+// ... 3 (each step halves the values a lane carries: 12 word exchanges
+// instead of 40).
+__device__ __forceinline__ void store_item_sums(const double* d, int lane, double* out) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  double k0 = b0 ? d[2] : d[0], k1 = b0 ? d[3] : d[1];
+  k0 += __shfl_xor(b0 ? d[0] : d[2], 1);
+  k1 += __shfl_xor(b0 ? d[1] : d[3], 1);
+  double v = b1 ? k1 : k0;
+  v += __shfl_xor(b1 ? k0 : k1, 2);
+#pragma unroll
+  for (int o = 4; o < 32; o <<= 1) v += __shfl_xor(v, o);
+  if (lane < 4) out[((lane & 1) << 1) | (lane >> 1)] = v;
+}
+
 // The targets of one work item and their accumulators.  The wave splits into
 // S = floor(64 / n) slices of n lanes; a tile is T = S c sources (c =
 // floor(64 / S), T in [60, 64]) and slice s evaluates sources s, s + S, ...,
@@ -111,7 +127,7 @@ __device__ __forceinline__ float4 load_f4(const float4* p) {
 // and index arithmetic on scalar operands cost four slow instructions
 // per term before: compares and every instruction with a scalar-register
 // operand issue at half the rate of arithmetic on vector registers.
-template <bool PLAIN, int TEAM, typename SH>
+template <bool PLAIN, typename SH>
 struct WItem {
   const DevTree& T;
   SH& sh;
@@ -123,14 +139,20 @@ struct WItem {
   Sum4 acc4;
   int64_t nsrc = 0;
   int stamp;  // last value written to sh.mark (never reused by this wave)
-  int turn = 0;  // tiles until this wave evaluates one (teams)
 
-  // Whether the next tile is this wave's: the waves of a team take turns.
-  __device__ bool mine() {
-    if constexpr (TEAM == 1) return true;
-    const bool m = turn == 0;
-    turn = m ? TEAM - 1 : turn - 1;
-    return m;
+  // n targets from particle first on.
+  __device__ void targets(int lane_, int n, int first, bool do_eval_, int stamp_) {
+    lane = lane_;
+    nt = n;
+    S = kLanes / nt;
+    c = kLanes / S;
+    step = in_vgpr(16 * S);
+    stamp = stamp_;
+    slice = lane / nt;
+    active = slice < S;
+    do_eval = do_eval_;
+    xi = reinterpret_cast<const float4*>(T.part)[first + lane % nt];
+    acc4.zero();
   }
 
   __device__ int tile_size() const { return S * c; }
@@ -139,12 +161,12 @@ struct WItem {
   __device__ int terms(int cnt) const { return cnt == S * c ? c : uni((cnt + S - 1) / S); }
 
   __device__ void flush_cells(uint32_t start, int cnt) {
-    if (!do_eval || !mine()) return;
+    if (!do_eval) return;
     const float4* mp = reinterpret_cast<const float4*>(T.mp);
     const int k = terms(cnt);
     if (lane < S * k) {
       // The last entries of a partial tile repeat its last cell without mass.
-      const int64_t id = sh.cring[(start + min(lane, cnt - 1)) & (kRingW - 1)];
+      const int64_t id = sh.cring[(start + min(lane, cnt - 1)) & (SH::kRing - 1)];
       float4 a = mp[3 * id], b = mp[3 * id + 1];
       float2 d = *reinterpret_cast<const float2*>(mp + 3 * id + 2);
       if (lane >= cnt) {
@@ -178,13 +200,74 @@ struct WItem {
     wave_lds_sync();
   }
 
+  // Adds r + q to s + e.
+  __device__ static void add(float* s, float* e, const float* r, const float* q) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (PLAIN) {
+        s[k] += r[k];
+      } else {
+        neu_add(s[k], e[k], r[k]);
+        neu_add(s[k], e[k], q[k]);
+      }
+    }
+  }
+
+  // The slices of each target added up (in lane < nt), the upper half to the
+  // lower until one is left: six steps at most.  (One after the other in
+  // one lane, the 64 slices of a single target took 22 us, the eight of seven
+  // targets 3.5 us.)
+  __device__ void combine_slices(float* s, float* e) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      s[k] = acc4.s[k];
+      e[k] = PLAIN ? 0.f : acc4.c[k];
+    }
+    for (int n = S; n > 1;) {
+      const int h = (n + 1) >> 1, from = lane + h * nt;
+      float r[4], q[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        r[k] = __shfl(s[k], from);
+        q[k] = PLAIN ? 0.f : __shfl(e[k], from);
+      }
+      if (slice < n - h) add(s, e, r, q);
+      n = h;
+    }
+  }
+
+  // Results of the targets (lane < nt; o: its place in the input), and the item's
+  // diagnostic sums.
+  __device__ void store(const WalkBufs& B, int64_t w, int64_t o, float* s, float* e,
+                        float* __restrict__ acc, float* __restrict__ pot) {
+    double d[4] = {0.0, 0.0, 0.0, 0.0};  // m a, 1/2 m phi of this lane's target
+    if (lane < nt) {
+      // The target itself is in its own leaf: its self term added -m_i/eps to
+      // the potential and nothing to the acceleration; remove that same value.
+      const float self = self_term(xi.w, eps2);
+      if (PLAIN) s[3] += self;
+      else neu_add(s[3], e[3], self);
+      const float a[4] = {s[0] + e[0], s[1] + e[1], s[2] + e[2], s[3] + e[3]};
+      acc[3 * o + 0] = a[0];
+      acc[3 * o + 1] = a[1];
+      acc[3 * o + 2] = a[2];
+      const double m = xi.w;
+      for (int k = 0; k < 3; ++k) d[k] = m * (double)a[k];
+      if (pot) {
+        pot[o] = a[3];
+        d[3] = 0.5 * m * (double)a[3];
+      }
+    }
+    if (B.dpart) store_item_sums(d, lane, B.dpart + 4 * w);
+  }
+
   // The leaves [start, start + lc) of the ring: their particles, flattened in
   // list order, tile by tile.  A leaf marks the lane at which its particles
   // begin in the tile; a ballot of the marks gives every lane its leaf.
   __device__ void flush_leaves(uint32_t start, int lc) {
     int first = 0, ln = 0;
     if (lane < lc) {
-      const int2 fl = sh.lring[(start + lane) & (kRingW - 1)];
+      const int2 fl = sh.lring[(start + lane) & (SH::kRing - 1)];
       first = fl.x;
       ln = fl.y;
     }
@@ -195,7 +278,6 @@ struct WItem {
     const float4* part = reinterpret_cast<const float4*>(T.part);
     const int ex = incl - ln, rel = first - ex, tile = tile_size();
     for (int u0 = 0; u0 < total; u0 += tile) {
-      if (!mine()) continue;
       const int cnt = min(tile, total - u0);
       const int k = terms(cnt);
       ++stamp;
@@ -235,21 +317,6 @@ struct WItem {
   }
 };
 
-// Sums of the four values of lanes 0 ... 31 in a fixed order, stored by lanes 0
-// ... 3 (each step halves the values a lane carries: 12 word exchanges
-// instead of 40).
-__device__ __forceinline__ void store_item_sums(const double* d, int lane, double* out) {
-  const bool b0 = lane & 1, b1 = lane & 2;
-  double k0 = b0 ? d[2] : d[0], k1 = b0 ? d[3] : d[1];
-  k0 += __shfl_xor(b0 ? d[0] : d[2], 1);
-  k1 += __shfl_xor(b0 ? d[1] : d[3], 1);
-  double v = b1 ? k1 : k0;
-  v += __shfl_xor(b1 ? k0 : k1, 2);
-#pragma unroll
-  for (int o = 4; o < 32; o <<= 1) v += __shfl_xor(v, o);
-  if (lane < 4) out[((lane & 1) << 1) | (lane >> 1)] = v;
-}
-
 enum : int { kOverflow = 0, kDone = 1, kFallBack = 2 };
 
 // Walks and evaluates work item w with one wave.  Returns kOverflow
@@ -257,12 +324,8 @@ enum : int { kOverflow = 0, kDone = 1, kFallBack = 2 };
 // with LEARNED, kFallBack (nothing written but the trace) if the group's
 // budget is exceeded, *nband = band candidates visited.  cw is the value of
 // cnt[g].w written by a walk with the theta test.
-//
-// TEAM > 1: the block's TEAM waves all call it for the same item, walk the tree
-// alike and evaluate every TEAM-th tile each (sh[wave]: their LDS areas); the
-// first wave adds the partial sums in wave order.
-template <bool PLAIN, bool LEARNED, int TEAM, typename SH, typename Q>
-__device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH* shw, int64_t w,
+template <bool PLAIN, bool LEARNED, typename SH, typename Q>
+__device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64_t w,
                               float th2, float eps2, float* __restrict__ acc,
                               float* __restrict__ pot, Q q, uint32_t qmask, bool gmem_q,
                               bool do_eval, int cw, int* nband_out, int* stamp,
@@ -282,22 +345,9 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH* shw, int6
   const float4 gmin = U(gbox[2 * g]), gmax = U(gbox[2 * g + 1]);
   const float4* rec = reinterpret_cast<const float4*>(T.wrec);
 
-  const int wave = TEAM == 1 ? 0 : uni((int)threadIdx.x / kLanes);
-  SH& sh = shw[wave];
-  WItem<PLAIN, TEAM, SH> it{T, sh, in_vgpr(eps2)};
-  it.turn = wave;
-  it.lane = lane;
-  it.nt = uni(min(kChunk, gi.y - wk.y));
-  it.S = kLanes / it.nt;
-  it.c = kLanes / it.S;
-  it.step = in_vgpr(16 * it.S);
-  it.stamp = *stamp;
-  it.slice = lane / it.nt;
-  it.active = it.slice < it.S;
-  it.do_eval = do_eval;
+  WItem<PLAIN, SH> it{T, sh, in_vgpr(eps2)};
   const int first = gi.x + wk.y;
-  it.xi = reinterpret_cast<const float4*>(T.part)[first + lane % it.nt];
-  it.acc4.zero();
+  it.targets(lane, uni(min(kChunk, gi.y - wk.y)), first, do_eval, *stamp);
 
   const bool exp = B.export_lists && wk.y == 0;
   // learned criterion state
@@ -527,83 +577,27 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH* shw, int6
     }
     cw = 2 * nband;
   }
-  if (lane == 0 && wk.y == 0 && wave == 0)  // per-group counts; the totals are reduced afterwards
+  if (lane == 0 && wk.y == 0)  // per-group counts; the totals are reduced afterwards
     reinterpret_cast<int4*>(B.cnt)[g] = make_int4((int)ctail, (int)ltail, (int)it.nsrc, cw);
   if (!do_eval) return kDone;
 
-  // Combine the slices of each target in slice order.
-  float* red = reinterpret_cast<float*>(sh.tile);  // [64][8] floats
-  if (it.active) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      red[lane * 8 + k] = it.acc4.s[k];
-      red[lane * 8 + 4 + k] = it.acc4.c[k];
-    }
-  }
-  wave_lds_sync();
-  double d[4] = {0.0, 0.0, 0.0, 0.0};  // m a, 1/2 m phi of this lane's target
-  float s[4] = {0.f, 0.f, 0.f, 0.f}, cc[4] = {0.f, 0.f, 0.f, 0.f};
-  auto add = [&](const float* r) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (PLAIN) {
-        s[k] += r[k];
-      } else {
-        neu_add(s[k], cc[k], r[k]);
-        neu_add(s[k], cc[k], r[4 + k]);
-      }
-    }
-  };
-  if (lane < it.nt)
-    for (int sl = 0; sl < it.S; ++sl) add(red + (sl * it.nt + lane) * 8);
-  if constexpr (TEAM > 1) {
-    // behind the slices' sums in the tile: [32][8] floats per wave
-    float* own = reinterpret_cast<float*>(sh.tile + 2 * kTileW) + lane * 8;
-    if (lane < it.nt && wave != 0)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        own[k] = s[k];
-        own[4 + k] = cc[k];
-      }
-    __syncthreads();
-    if (wave != 0) return kDone;
-    if (lane < it.nt)
-      for (int k = 1; k < TEAM; ++k)
-        add(reinterpret_cast<const float*>(shw[k].tile + 2 * kTileW) + lane * 8);
-  }
-  if (lane < it.nt) {
-    // The target itself is in its own leaf: its self term added -m_i/eps to
-    // the potential and nothing to the acceleration; remove that same value.
-    const float self = self_term(it.xi.w, eps2);
-    if (PLAIN) s[3] += self;
-    else neu_add(s[3], cc[3], self);
-    const int64_t o = T.perm[first + lane];
-    const float a[4] = {s[0] + cc[0], s[1] + cc[1], s[2] + cc[2], s[3] + cc[3]};
-    acc[3 * o + 0] = a[0];
-    acc[3 * o + 1] = a[1];
-    acc[3 * o + 2] = a[2];
-    const double m = it.xi.w;
-    for (int k = 0; k < 3; ++k) d[k] = m * (double)a[k];
-    if (pot) {
-      pot[o] = a[3];
-      d[3] = 0.5 * m * (double)a[3];
-    }
-  }
-  if (B.dpart) store_item_sums(d, lane, B.dpart + 4 * w);
+  float v[4], e[4];
+  it.combine_slices(v, e);
+  it.store(B, w, T.perm[first + lane % it.nt], v, e, acc, pot);
   wave_lds_sync();
   return kDone;
 }
 
 // One work item, with the theta re-walk of a group over its budget.
 template <bool PLAIN, bool LEARNED, typename SH, typename Q>
-__device__ int walk_eval_one(const DevTree& T, const WalkBufs& B, SH* sh, int64_t w, float th2,
+__device__ int walk_eval_one(const DevTree& T, const WalkBufs& B, SH& sh, int64_t w, float th2,
                              float eps2, float* acc, float* pot, Q q, uint32_t qmask, bool gmem_q,
                              bool do_eval, int* stamp, const MlpView* mv) {
   int nb = 0;
-  const int st = walk_eval_item<PLAIN, LEARNED, 1>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q,
+  const int st = walk_eval_item<PLAIN, LEARNED>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q,
                                                 do_eval, 0, &nb, stamp, mv);
   if (!LEARNED || st != kFallBack) return st;
-  return walk_eval_item<PLAIN, false, 1>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q, do_eval,
+  return walk_eval_item<PLAIN, false>(T, B, sh, w, th2, eps2, acc, pot, q, qmask, gmem_q, do_eval,
                                       2 * nb + 1, &nb, stamp, mv);
 }
 
@@ -651,7 +645,7 @@ void walk_eval_persistent_kernel(
       const int k = take_work(B.wctr + 64 * 8, lane);
       if (k >= *src_n) break;
       const int32_t w = src[k];
-      if (walk_eval_one<PLAIN, LEARNED>(T, B, shw + wv, w, th2, eps2, acc, pot, q, qmask, false,
+      if (walk_eval_one<PLAIN, LEARNED>(T, B, shw[wv], w, th2, eps2, acc, pot, q, qmask, false,
                                         do_eval != 0, &stamp, &V) == kOverflow &&
           lane == 0)
         ovl[atomicAdd(ovn, 1)] = w;
@@ -687,7 +681,7 @@ void walk_eval_persistent_kernel(
         }
         const int64_t w = ((int64_t)(k / kDeal) * 8 + x) * kDeal + k % kDeal;
         if (w >= T.nw) continue;
-        if (walk_eval_one<PLAIN, LEARNED>(T, B, shw + wv, w, th2, eps2, acc, pot, q, qmask, false,
+        if (walk_eval_one<PLAIN, LEARNED>(T, B, shw[wv], w, th2, eps2, acc, pot, q, qmask, false,
                                           do_eval != 0, &stamp, &V) == kOverflow &&
             lane == 0)
           ovl[atomicAdd(ovn, 1)] = (int32_t)w;
@@ -697,25 +691,154 @@ void walk_eval_persistent_kernel(
 }
 
 // One block of NW waves per work item, for trees with too few items to fill
-// the chip with a wave each: the item's latency is its walk plus 1 / NW of its
-// tiles, and no wave waits for a work counter.  (The walk itself, about a
-// microsecond per dependent gather, is repeated by every wave: the chip would
-// be idle otherwise.)  Blocks go to the XCDs in turn, so consecutive items,
-// which cost alike, do too (contiguous ranges per XCD: 10 % longer).
+// the chip with a wave each: the item's latency is what counts.  The waves walk
+// the tree together, NW windows of eight entries a step from one queue: a step
+// takes about a microsecond (a dependent gather and two barriers) whatever
+// its width, and a level of a small tree is one or two steps.  Every wave
+// counts what its window appends and, after a barrier, writes it behind that of the
+// waves before it, so the lists keep the order of the one-wave walk.  The waves
+// then evaluate a tile of cells or 64 leaves each whenever all have one, and
+// share the rest evenly at the end; the first wave adds the partial sums in
+// wave order.  At 1000 bodies an item takes 13 us, of which 4.4 are seven steps
+// and 4 its sources; with every wave walking alone and evaluating every NW-th
+// tile, calls took 54 us for 5003 bodies (now 46), 75 for 16384 (67).
+// Blocks go to the XCDs in turn, so consecutive items, which cost alike, do
+// too (contiguous ranges per XCD: 10 % longer).
+template <int QCAP, int NW>
+struct TeamShared {
+  int q[QCAP];
+  int cring[128 * NW];  // before a step fewer than 64 NW are pending; it adds up to 64 NW
+  int2 lring[128 * NW];
+  float4 tile[NW][3 * kTileW];
+  int mark[NW][kTileW];
+  int count[NW];
+  int nsrc[NW];
+};
+// A wave's part of it, as WItem reads it.
+template <int NW>
+struct TeamView {
+  static constexpr int kRing = 128 * NW;
+  int* cring;
+  int2* lring;
+  float4* tile;
+  int* mark;
+};
 template <bool PLAIN, int QCAP, int NW>
 __global__ __launch_bounds__(NW * kLanes) void walk_eval_team_kernel(DevTree T, WalkBufs B, float th2,
-                                                                     float eps2, float* acc,
-                                                                     float* pot) {
-  __shared__ WShared<QCAP> shw[NW];
+                                                                     float eps2,
+                                                                     float* __restrict__ acc,
+                                                                     float* __restrict__ pot) {
+  static_assert(NW <= 8, "counts of a step in ten bits each");
+  __shared__ TeamShared<QCAP, NW> sh;
   const int64_t w = blockIdx.x;
-  const int wv = uni((int)threadIdx.x / kLanes);
+  const int lane = threadIdx.x & (kLanes - 1), wave = uni((int)threadIdx.x / kLanes);
   const uint32_t qmask = (uint32_t)min(B.lds_qcap / 8, QCAP) - 1;
-  shw[wv].mark[threadIdx.x & (kLanes - 1)] = 0;
-  int stamp = 0, nb = 0;
-  if (walk_eval_item<PLAIN, false, NW>(T, B, shw, w, th2, eps2, acc, pot, LQueue{shw[wv].q}, qmask,
-                                       false, true, 0, &nb, &stamp, nullptr) == kOverflow &&
-      threadIdx.x == 0)
-    B.ovf_list[atomicAdd(B.ovf_count, 1)] = (int32_t)w;
+  const int2 wk = reinterpret_cast<const int2*>(T.wwork)[w];
+  const int64_t g = wk.x;
+  const int4 gi = reinterpret_cast<const int4*>(T.ginfo)[g];
+  const float4* gbox = reinterpret_cast<const float4*>(T.gbox);
+  const float4 gmin = gbox[2 * g], gmax = gbox[2 * g + 1];
+  const float4* rec = reinterpret_cast<const float4*>(T.wrec);
+  TeamView<NW> view{sh.cring, sh.lring, sh.tile[wave], sh.mark[wave]};
+  view.mark[lane] = 0;
+  WItem<PLAIN, TeamView<NW>> it{T, view, in_vgpr(eps2)};
+  const int first = gi.x + wk.y;
+  it.targets(lane, uni(min(kChunk, gi.y - wk.y)), first, true, 0);
+  const int64_t place = T.perm[first + lane % it.nt];
+
+  uint32_t rhead = 0, rtail = 0, chead = 0, ctail = 0, lhead = 0, ltail = 0;
+  const int4 root = reinterpret_cast<const int4*>(rec)[1];
+  if (root.y == 0) {  // the root is a leaf: its particles are the whole list
+    if (threadIdx.x == 0) sh.lring[0] = make_int2(root.z, root.w);
+    ltail = 1;
+  } else {
+    if (threadIdx.x == 0) sh.q[0] = (root.x << 3) | (root.y - 1);
+    rtail = 1;
+  }
+  __syncthreads();
+  const uint32_t ent = 8 * wave + (lane >> 3);
+  const int child = lane & 7;
+  const uint32_t tile = (uint32_t)it.tile_size();
+  const float th2v = in_vgpr(th2);
+  for (;;) {
+    // (every condition is the same in all waves)
+    while (rhead != rtail && ctail - chead < NW * tile && ltail - lhead < (uint32_t)(NW * kTileW)) {
+      const uint32_t avail = rtail - rhead;
+      uint64_t mC = 0, mL = 0, mQ = 0;
+      int c = 0;
+      int4 tp = make_int4(0, 0, 0, 0);
+      if (8u * wave < avail) {
+        const int e = sh.q[(rhead + ent) & qmask];
+        c = ent < avail && child <= (e & 7) ? (int)((uint32_t)e >> 3) + child : 0;
+        tp = reinterpret_cast<const int4*>(rec)[2 * (int64_t)c + 1];
+        const float4 ge = rec[2 * (int64_t)c];
+        const uint64_t mV = __ballot(c != 0);
+        const uint64_t mOp = mV & open_mask(gmin, gmax, ge, th2v), mLeaf = __ballot(tp.y == 0);
+        mC = mV & ~mOp;
+        mL = mOp & mLeaf;
+        mQ = mOp & ~mLeaf;
+      }
+      rhead += min(8u * NW, avail);
+      if (lane == 0) sh.count[wave] = __popcll(mC) | __popcll(mL) << 10 | __popcll(mQ) << 20;
+      __syncthreads();
+      const int incl = wave_inclusive_sum(lane < NW ? sh.count[lane] : 0);
+      const uint32_t all = (uint32_t)__builtin_amdgcn_readlane(incl, NW - 1);
+      const uint32_t own = wave == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane(incl, max(wave - 1, 0));
+      if ((rtail + (all >> 20)) - rhead > qmask + 1) {
+        if (threadIdx.x == 0) B.ovf_list[atomicAdd(B.ovf_count, 1)] = (int32_t)w;
+        return;
+      }
+      if (__builtin_amdgcn_inverse_ballot_w64(mC))
+        sh.cring[(ctail + (own & 1023) + rank_below(mC)) & (128 * NW - 1)] = c;
+      if (__builtin_amdgcn_inverse_ballot_w64(mL))
+        sh.lring[(ltail + (own >> 10 & 1023) + rank_below(mL)) & (128 * NW - 1)] = make_int2(tp.z, tp.w);
+      if (__builtin_amdgcn_inverse_ballot_w64(mQ))
+        sh.q[(rtail + (own >> 20) + rank_below(mQ)) & qmask] = (tp.x << 3) | (tp.y - 1);
+      ctail += all & 1023;
+      ltail += all >> 10 & 1023;
+      rtail += all >> 20;
+      __syncthreads();
+    }
+    const bool last = rhead == rtail;
+    const uint32_t pc = ctail - chead, pl = ltail - lhead;
+    if (pc >= NW * tile || (last && pc != 0)) {
+      const uint32_t per = min(tile, (pc + NW - 1) / NW), from = min(pc, per * wave);
+      const uint32_t n = min(per, pc - from);
+      if (n != 0) it.flush_cells(chead + from, (int)n);
+      chead += min(pc, per * NW);
+    } else if (pl >= (uint32_t)(NW * kTileW) || (last && pl != 0)) {
+      const uint32_t per = min((uint32_t)kTileW, (pl + NW - 1) / NW), from = min(pl, per * wave);
+      const uint32_t n = min(per, pl - from);
+      if (n != 0) it.flush_leaves(lhead + from, (int)n);
+      lhead += min(pl, per * NW);
+    } else {
+      break;
+    }
+  }
+
+  // The waves' sums, in their tiles: [32][8] floats.
+  float v[4], e[4];
+  it.combine_slices(v, e);
+  auto sums = [&](int k) { return reinterpret_cast<float*>(sh.tile[k]) + lane * 8; };
+  float* own = sums(wave);
+  if (lane < it.nt && wave != 0)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      own[k] = v[k];
+      own[4 + k] = e[k];
+    }
+  if (lane == 0) sh.nsrc[wave] = (int)it.nsrc;
+  __syncthreads();
+  if (wave != 0) return;
+  if (lane < it.nt)
+    for (int k = 1; k < NW; ++k)
+      it.add(v, e, sums(k), sums(k) + 4);
+  if (lane == 0 && wk.y == 0) {
+    int n = 0;
+    for (int k = 0; k < NW; ++k) n += sh.nsrc[k];
+    reinterpret_cast<int4*>(B.cnt)[g] = make_int4((int)ctail, (int)ltail, n, 0);
+  }
+  it.store(B, w, place, v, e, acc, pot);
 }
 
 // Global-memory queues: written and read by different lanes of one wave, so
@@ -751,7 +874,7 @@ __global__ __launch_bounds__(kLanes) void walk_eval_fallback_kernel(DevTree T, W
   sh.mark[threadIdx.x] = 0;
   int stamp = 0;
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    const int st = walk_eval_one<PLAIN, LEARNED>(T, B, &sh, src[i], th2, eps2, acc, pot, q,
+    const int st = walk_eval_one<PLAIN, LEARNED>(T, B, sh, src[i], th2, eps2, acc, pot, q,
                                                  (uint32_t)(B.gq_cap - 1), true, do_eval != 0, &stamp, &V);
     if (st == kOverflow && threadIdx.x == 0)
       atomicOr(reinterpret_cast<unsigned long long*>(&B.tot[5]), 1ull);
@@ -928,13 +1051,14 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
   // Waves per work item.  With fewer than about 11000 items (two for each of the
   // 5120 waves the chip holds) one wave per item leaves a long tail, or most of
   // the chip idle; measured with 1 / 2 / 4 / 8 waves per item, in us: 79 items (1000
-  // bodies) 106 / 47 / 42 / 40, 368 items 159 / 79 / 61 / 56, 655 items 180 / 93 / 71 / 84,
-  // 1198 items 227 / 130 / 97 / 127, 2590 items 213 / 130 / 156 / 218, 5008 items 261 / 214 /
-  // 252 / 395, 7580 items 180 / 163 / 205 / 328, 12641 items 237 / 244 / 318 / 530.  (Not
+  // bodies) 100 / 43 / 38 / 37, 368 items 154 / 74 / 53 / 46, 655 items 173 / 89 / 61 / 55,
+  // 1042 items 186 / 98 / 67 / 69, 1198 items 216 / 120 / 79 / 81, 2590 items 201 / 121 / 110 /
+  // 129 and 125 / 76 / 77 / 102, 5008 items 248 / 198 / 186 / 230 and 137 / 113 / 119 / 173, 7580
+  // items 165 / 150 / 164 / 253, 12641 items 219 / 229 / 258 / 406.  (Not
   // with the learned criterion: every wave would run the network.)
   int team = 1;
   if (!learned && do_eval && !B.export_lists)
-    team = T.nw <= 512 ? 8 : T.nw <= 2000 ? 4 : T.nw <= 11000 ? 2 : 1;
+    team = T.nw <= 1000 ? 8 : T.nw <= 3500 ? 4 : T.nw <= 11000 ? 2 : 1;
   auto go = [&](auto plain_tag, auto learned_tag) {
     constexpr bool P = decltype(plain_tag)::value, L = decltype(learned_tag)::value;
     if (parts & kWalkFirst) {

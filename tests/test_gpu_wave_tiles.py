@@ -102,3 +102,17 @@ def test_waves_per_item(n, cap, monkeypatch):
     again = T.forces(0.6, 0.01)
     assert (again[0] == acc).all() and (again[1] == pot).all()
     assert T.diagnostics()[1] == w and (T.diagnostics()[0] == mom).all()
+
+
+@pytest.mark.parametrize("n,n_leaf,n_group,theta", [(1500, 1, 64, 0.1), (3000, 1, 8, 0.3), (9000, 2, 64, 0.25),
+                                                    (4000, 64, 64, 0.2), (24000, 1, 32, 0.35)])
+def test_long_lists_of_few_items(n, n_leaf, n_group, theta):
+    """Several rounds of cell tiles and of leaves for the waves of one item, and shared remainders."""
+    pos, m = W.plummer_clumps(n, n)
+    _check(pos, m, n_leaf, n_group, theta, 0.01, acc_gate=False)
+    T = og.Tree(pos, m, n_leaf, n_group)
+    O = oracle.Tree(pos, m, n_leaf, n_group)
+    T.forces(theta, 0.01)
+    co, _, lo, _ = O.lists(theta)
+    g = T.group_counts()
+    assert np.array_equal(g[:, 0], np.diff(co)) and np.array_equal(g[:, 1], np.diff(lo))
