@@ -711,7 +711,8 @@ __global__ void work_kernel(const int4* __restrict__ pre, const int4* __restrict
 struct BuildInfo {
   int64_t level[kLevels + 1];  // where each level's cells begin; all cells
   double cube[6];  // root_kernel
-  int32_t bad;     // input check (bbox_kernel)
+  int32_t bad;       // input check (bbox_kernel)
+  int32_t unsorted;  // a bucket was too large (bucket_sort_kernel)
   int32_t ng, nw, leaves;
 };
 
@@ -805,19 +806,15 @@ __global__ __launch_bounds__(kSmallT) void small_keys_kernel(const float* __rest
 }
 
 // The stable sort by counting: a key's place is the number of keys before it
-// in (key, index) order.  A block places kRankKeys keys: its threads hold all
-// keys between them and each compare's lane mask is counted by the scalar
-// unit.  n^2 compares over the whole device take 12 us for 5003 keys (16 for
-// 8000), where rocPRIM's block sort and merge passes took 35 in six launches.  Also writes
-// the particles in key order.
+// in (key, index) order.  A block places kRankKeys of the n keys at(0) ...
+// at(n - 1), n <= kSmallN: its threads hold all keys between them and each compare's lane
+// mask is counted by the scalar unit.  n^2 compares over the whole device take 12 us for
+// 5003 keys (16 for 8000), where rocPRIM's block sort and merge passes took 35
+// in six launches.  Returns the place of key kRankKeys * block + t in thread t <
+// kRankKeys, -1 in others.
 constexpr int kRankKeys = 32;
-__global__ __launch_bounds__(kSmallT) void small_rank_kernel(const uint64_t* __restrict__ key,
-                                                             const float* __restrict__ pos,
-                                                             const float* __restrict__ mass, int n,
-                                                             uint64_t* __restrict__ sorted,
-                                                             int32_t* __restrict__ perm,
-                                                             float4* __restrict__ part,
-                                                             int32_t* __restrict__ iperm) {
+template <typename At>
+__device__ __forceinline__ int rank_by_counting(const At& at, int n) {
   constexpr int kHeld = kSmallN / kSmallT;
   static_assert(64 % kRankKeys == 0, "a block's keys lie in one run of 64");
   __shared__ int cnt[kSmallT / 64][kRankKeys];
@@ -827,13 +824,13 @@ __global__ __launch_bounds__(kSmallT) void small_rank_kernel(const uint64_t* __r
 #pragma unroll
   for (int q = 0; q < kHeld; ++q) {
     const int j = q * kSmallT + t;
-    kj[q] = j < n ? key[j] : ~0ull;
+    kj[q] = j < n ? at(j) : ~0ull;
   }
   const int jw = __builtin_amdgcn_readfirstlane(w) * 64;
   const int run = e0 & ~63;  // the block's keys lie in run ... run + 63
   // (the block's keys from a lane each: loaded one by one they cost a memory
   // latency per key)
-  const uint64_t ke = key[min(e0 + (lane & (kRankKeys - 1)), n - 1)];
+  const uint64_t ke = at(min(e0 + (lane & (kRankKeys - 1)), n - 1));
   constexpr int kU = 8;
 #pragma unroll 1
   for (int g = 0; g < kRankKeys; g += kU) {
@@ -860,14 +857,168 @@ __global__ __launch_bounds__(kSmallT) void small_rank_kernel(const uint64_t* __r
       if (lane == u) cnt[w][g + u] = c[u];
   }
   __syncthreads();
-  const int i = e0 + t;
-  if (t >= kRankKeys || i >= n) return;
+  if (t >= kRankKeys || e0 + t >= n) return -1;
   int r = 0;
   for (int k = 0; k < kSmallT / 64; ++k) r += cnt[k][t];
+  return r;
+}
+
+// The order of all particles, and the particles in it.
+__global__ __launch_bounds__(kSmallT) void small_rank_kernel(const uint64_t* __restrict__ key,
+                                                             const float* __restrict__ pos,
+                                                             const float* __restrict__ mass, int n,
+                                                             uint64_t* __restrict__ sorted,
+                                                             int32_t* __restrict__ perm,
+                                                             float4* __restrict__ part,
+                                                             int32_t* __restrict__ iperm) {
+  const int r = rank_by_counting([&](int j) { return key[j]; }, n);
+  if (r < 0) return;
+  const int i = blockIdx.x * kRankKeys + threadIdx.x;
   sorted[r] = key[i];
   perm[r] = i;
   iperm[i] = r;
   part[r] = make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]);
+}
+
+// ---- the sort of up to kSampleMax particles, by (key, index): buckets of
+// about kBucket particles between splitters taken from a sorted sample, each
+// sorted by one block in LDS.  262144 particles: sample 13 us, count 7, scan 8,
+// scatter 10, buckets 23, where rocPRIM's block sort and sixteen launches of
+// merge passes took 115.  Whole rebuild with the library's sort and with this, in us:
+// 16384 176 / 174, 65536 200 / 187, 262144 268 / 222, 2^20 474 / 412.  A bucket of more than kBucketMax
+// particles (input whose keys at regular places tell nothing of the others)
+// is reported, and the host sorts with the library.
+constexpr int kSampleMax = 1 << 20;
+constexpr int kBucket = 1024, kBucketMax = 4096, kBuckets = kSampleMax / kBucket;
+constexpr int kSplitN = 4096;  // particles per block of the count and the scatter
+// Buckets: a block for each compute unit, of up to kBucket particles on average.
+inline int bucket_count(int64_t n) { return (int)std::max<int64_t>(256, (n + kBucket - 1) / kBucket); }
+// Samples: 8 per bucket while kBucketMax is at least 16 times the mean, 16 up
+// to 2^18 particles, 8 to 16 up to 2^20 (a bucket of four times the mean is then less
+// likely than one in 10^4 trees).
+inline int sample_size(int64_t n) { return n <= (1 << 16) ? 2048 : n <= (1 << 18) ? 4096 : 8192; }
+
+// Splitter q (1 ... nb - 1) is the sample of rank floor(q S / nb).
+__global__ __launch_bounds__(kSmallT) void splitters_kernel(const uint64_t* __restrict__ key,
+                                                            int64_t n, int S, int nb,
+                                                            uint64_t* __restrict__ skey,
+                                                            int32_t* __restrict__ sidx) {
+  auto index = [&](int j) { return (int64_t)j * n / S; };
+  const int r = rank_by_counting([&](int j) { return key[index(j)]; }, S);
+  if (r < 0) return;
+  const int q = (r * nb + S - 1) / S;
+  if (q < 1 || q >= nb || q * S / nb != r) return;
+  const int64_t i = index(blockIdx.x * kRankKeys + threadIdx.x);
+  skey[q - 1] = key[i];
+  sidx[q - 1] = (int32_t)i;
+}
+
+// Bucket of every particle (splitters at or before it) and each block's
+// particles per bucket, cnt[bucket * gridDim.x + block]; a 0 behind the last.
+__global__ __launch_bounds__(kSmallT) void bucket_count_kernel(const uint64_t* __restrict__ key,
+                                                               int64_t n, int nb,
+                                                               const uint64_t* __restrict__ skey,
+                                                               const int32_t* __restrict__ sidx,
+                                                               uint16_t* __restrict__ bucket,
+                                                               int32_t* __restrict__ cnt) {
+  __shared__ uint64_t sk[kBuckets];
+  __shared__ int32_t si[kBuckets], hist[kBuckets];
+  const int t = threadIdx.x;
+  if (t < nb) hist[t] = 0;
+  if (t < nb - 1) {
+    sk[t] = skey[t];
+    si[t] = sidx[t];
+  }
+  __syncthreads();
+  static_assert(kBuckets <= kSmallT, "one bucket per thread");
+  for (int u = 0; u < kSplitN / kSmallT; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kSplitN + u * kSmallT + t;
+    if (i >= n) break;
+    const uint64_t k = key[i];
+    int l = 0, h = nb - 1;
+    while (l < h) {
+      const int mid = (l + h) >> 1;
+      if (sk[mid] < k || (sk[mid] == k && si[mid] <= (int32_t)i)) l = mid + 1;
+      else h = mid;
+    }
+    bucket[i] = (uint16_t)l;
+    atomicAdd(&hist[l], 1);
+  }
+  __syncthreads();
+  if (t < nb) cnt[(int64_t)t * gridDim.x + blockIdx.x] = hist[t];
+  if (t == 0 && blockIdx.x == 0) cnt[(int64_t)nb * gridDim.x] = 0;
+}
+
+// Particles to their buckets, in any order within one.
+__global__ __launch_bounds__(kSmallT) void bucket_scatter_kernel(const uint64_t* __restrict__ key,
+                                                                 int64_t n, int nb,
+                                                                 const uint16_t* __restrict__ bucket,
+                                                                 const int32_t* __restrict__ before,
+                                                                 uint64_t* __restrict__ key_out,
+                                                                 int32_t* __restrict__ idx_out) {
+  __shared__ int32_t next[kBuckets];
+  const int t = threadIdx.x;
+  if (t < nb) next[t] = before[(int64_t)t * gridDim.x + blockIdx.x];
+  __syncthreads();
+  for (int u = 0; u < kSplitN / kSmallT; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kSplitN + u * kSmallT + t;
+    if (i >= n) break;
+    const int32_t p = atomicAdd(&next[bucket[i]], 1);
+    key_out[p] = key[i];
+    idx_out[p] = (int32_t)i;
+  }
+}
+
+// Bucket blockIdx.x (of nblk counts each): a merge sort in LDS in which every
+// element finds its place by a binary search in the run its own is merged with
+// (keys first, indices only between equal keys; every step lies within the
+// two runs).  (A bitonic network of the next power of two: 26 us at 16384
+// particles in 16 buckets, this 23 at 262144 in 256.)
+__global__ __launch_bounds__(kSmallT) void bucket_sort_kernel(const int32_t* __restrict__ before,
+                                                              int nblk,
+                                                              const uint64_t* __restrict__ key_in,
+                                                              const int32_t* __restrict__ idx_in,
+                                                              uint64_t* __restrict__ sorted,
+                                                              int32_t* __restrict__ perm,
+                                                              int32_t* __restrict__ unsorted) {
+  __shared__ uint64_t key[2][kBucketMax];
+  __shared__ int32_t idx[2][kBucketMax];
+  const int t = threadIdx.x;
+  const int32_t lo = before[(int64_t)blockIdx.x * nblk];
+  const int m = before[(int64_t)(blockIdx.x + 1) * nblk] - lo;
+  if (m > kBucketMax) {  // uniform
+    if (t == 0) *unsorted = 1;
+    return;
+  }
+  for (int i = t; i < m; i += kSmallT) {
+    key[0][i] = key_in[lo + i];
+    idx[0][i] = idx_in[lo + i];
+  }
+  __syncthreads();
+  int cur = 0;
+  for (int run = 1; run < m; run *= 2, cur ^= 1) {
+    for (int i = t; i < m; i += kSmallT) {
+      const uint64_t k = key[cur][i];
+      const int32_t v = idx[cur][i];
+      const int mine = i & ~(run - 1), other = mine ^ run;
+      int l = min(m, other), h = min(m, other + run);
+      const int from = l;
+      while (l < h) {
+        const int mid = (l + h) >> 1;
+        const uint64_t km = key[cur][mid];
+        if (km < k || (km == k && idx[cur][mid] < v)) l = mid + 1;
+        else h = mid;
+      }
+      const int to = min(mine, other) + (i - mine) + (l - from);
+      key[cur ^ 1][to] = k;
+      idx[cur ^ 1][to] = v;
+    }
+    __syncthreads();
+  }
+  for (int i = t; i < m; i += kSmallT) {
+    sorted[lo + i] = key[cur][i];
+    perm[lo + i] = idx[cur][i];
+  }
 }
 
 // Everything after the sort.  Cell, image, group and item arrays hold cap
@@ -1179,7 +1330,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
 
   // Root cube (the host's rule on the device's bounding box).
   if (!small) {
-    if (hipMemsetAsync(&info->bad, 0, 4, s) != hipSuccess) return fail("memset failed");
+    if (hipMemsetAsync(&info->bad, 0, 8, s) != hipSuccess) return fail("memset failed");
     const int nbb = (int)std::min<int64_t>(1024, blocks(n));
     float* bbp = S.get<float>(6 * nbb);
     if (!bbp) return fail("device allocation failed");
@@ -1191,22 +1342,45 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   uint64_t* key = S.get<uint64_t>(n);
   uint64_t* key2 = S.get<uint64_t>(n);
   int32_t* perm = nullptr;
+  int32_t* idx = nullptr;
   float4* packed = nullptr;
   if (!key || !key2 || alloc.alloc((void**)&perm, (size_t)n * 4)) return fail("device allocation failed");
-  if (!small) {
-    int32_t* idx = S.get<int32_t>(n);
-    packed = S.get<float4>(n);
-    if (!idx || !packed) return fail("device allocation failed");
-    keys_kernel<<<blocks(n), kT, 0, s>>>(pos, mass, n, info->cube, key, idx, packed);
+  auto library_sort = [&]() {
     size_t sbytes = 0;
     if (hipcub::DeviceRadixSort::SortPairs(nullptr, sbytes, key, key2, idx, perm, (int)n, 0, 63,
                                            s) != hipSuccess)
-      return fail("sort failed");
+      return false;
     void* stmp = S.get<char>((int64_t)sbytes);
-    if (!stmp) return fail("device allocation failed");
-    if (hipcub::DeviceRadixSort::SortPairs(stmp, sbytes, key, key2, idx, perm, (int)n, 0, 63, s) !=
-        hipSuccess)
-      return fail("sort failed");
+    return stmp && hipcub::DeviceRadixSort::SortPairs(stmp, sbytes, key, key2, idx, perm, (int)n, 0,
+                                                      63, s) == hipSuccess;
+  };
+  const bool sampled = !small && n <= kSampleMax;
+  if (!small) {
+    idx = S.get<int32_t>(n);
+    packed = S.get<float4>(n);
+    if (!idx || !packed) return fail("device allocation failed");
+    keys_kernel<<<blocks(n), kT, 0, s>>>(pos, mass, n, info->cube, key, idx, packed);
+  }
+  if (sampled) {
+    const int ns = sample_size(n), nb = bucket_count(n);
+    const int nblk = (int)((n + kSplitN - 1) / kSplitN);
+    const int64_t nc = (int64_t)nb * nblk + 1;
+    uint64_t* skey = S.get<uint64_t>(kBuckets);
+    int32_t* sidx = S.get<int32_t>(kBuckets);
+    uint16_t* bucket = S.get<uint16_t>(n);
+    int32_t* cnt = S.get<int32_t>(nc);
+    int32_t* before = S.get<int32_t>(nc);
+    uint64_t* bkey = S.get<uint64_t>(n);
+    int32_t* bidx = S.get<int32_t>(n);
+    if (!skey || !sidx || !bucket || !cnt || !before || !bkey || !bidx)
+      return fail("device allocation failed");
+    splitters_kernel<<<ns / kRankKeys, kSmallT, 0, s>>>(key, n, ns, nb, skey, sidx);
+    bucket_count_kernel<<<nblk, kSmallT, 0, s>>>(key, n, nb, skey, sidx, bucket, cnt);
+    if (exclusive_sum(cnt, before, nc, S, s)) return fail("scan failed");
+    bucket_scatter_kernel<<<nblk, kSmallT, 0, s>>>(key, n, nb, bucket, before, bkey, bidx);
+    bucket_sort_kernel<<<nb, kSmallT, 0, s>>>(before, nblk, bkey, bidx, key2, perm, &info->unsorted);
+  } else if (!small && !library_sort()) {
+    return fail("sort failed");
   }
 
   // Cell arrays, for twice the particles at first; a tree of more cells has
@@ -1228,6 +1402,8 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     for (int k = 0; k < 3; ++k) h.corner[k] = hinfo->cube[k];
     h.side = hinfo->cube[3];
     nc = hinfo->level[kLevels];
+    h.max_level_cells = 0;
+    h.max_depth = 0;
     for (int L = 0; L < kLevels && hinfo->level[L] < nc; ++L) {
       h.max_level_cells = std::max(h.max_level_cells, hinfo->level[L + 1] - hinfo->level[L]);
       h.max_depth = L;
@@ -1285,11 +1461,16 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     int32_t* cnt = S.get<int32_t>((int64_t)kLevels * nb + 1);
     int32_t* before = S.get<int32_t>((int64_t)kLevels * nb + 1);
     if (!range || !cnt || !before) return fail("device allocation failed");
-    starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt);
-    if (exclusive_sum(cnt, before, (int64_t)kLevels * nb + 1, S, s)) return fail("scan failed");
-    cells_kernel<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, before, cap, info->level);
-    if (!fetch(0, offsetof(BuildInfo, ng))) return fail("subdivision failed");
-    if (const char* e = read_levels()) return fail(e);
+    for (bool sorted = !sampled;; sorted = true) {
+      starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt);
+      if (exclusive_sum(cnt, before, (int64_t)kLevels * nb + 1, S, s)) return fail("scan failed");
+      cells_kernel<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, before, cap, info->level);
+      if (!fetch(0, offsetof(BuildInfo, ng))) return fail("subdivision failed");
+      if (const char* e = read_levels()) return fail(e);
+      if (sorted || !hinfo->unsorted) break;
+      // (what was made of the unsorted keys stays within its arrays)
+      if (!library_sort()) return fail("sort failed");
+    }
     if (nc > cap) {
       cap = nc;
       if (!cell_arrays()) return fail("device allocation failed");

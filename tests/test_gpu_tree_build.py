@@ -169,3 +169,23 @@ def test_large_build_outgrows_its_arrays():
     p = np.random.default_rng(4).uniform(-1, 1, (6000, 3))
     H, D = _same_tree(np.concatenate([p, p]).astype(np.float32), np.full(12000, 1 / 12000, np.float32), 1, 4)
     assert H.stats["n_cells"] > 2 * 12000 + 64
+
+
+# The sort of 8193 ... 2^20 particles in buckets: counts that leave a partial last block, powers of two,
+# many ties, input already in order, and input whose regular places (those the sample is taken from) tell
+# nothing of the others, so that one bucket is too large.
+@pytest.mark.parametrize("n", [8193, 12288, 50001, 262144, 262145])
+@pytest.mark.parametrize("kind", ["random", "ties", "ordered", "misleading"])
+def test_bucket_sort_matches_host(n, kind):
+    _torch()
+    rng = np.random.default_rng(n)
+    pos, m = W.plummer(n, n)
+    if kind == "ties":
+        pos = (rng.integers(-3, 4, (n, 3)) * 0.25).astype(np.float32)
+    elif kind == "ordered":
+        pos = pos[np.lexsort(pos.T)]
+    elif kind == "misleading":
+        s = 2048 if n <= 1 << 16 else 4096 if n <= 1 << 18 else 8192
+        pos = rng.normal(0.9, 1e-3, (n, 3)).astype(np.float32)
+        pos[np.arange(s) * n // s] = rng.uniform(-1, 0, (s, 3)).astype(np.float32)
+    _same_tree(pos, rng.uniform(0.5, 2.0, n).astype(np.float32), 16, 64)
