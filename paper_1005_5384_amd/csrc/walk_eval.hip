@@ -127,7 +127,7 @@ __device__ __forceinline__ void store_item_sums(const double* d, int lane, doubl
 // and index arithmetic on scalar operands cost four slow instructions
 // per term before: compares and every instruction with a scalar-register
 // operand issue at half the rate of arithmetic on vector registers.
-template <bool PLAIN, typename SH>
+template <bool PLAIN, int TEAM, typename SH>
 struct WItem {
   const DevTree& T;
   SH& sh;
@@ -139,6 +139,15 @@ struct WItem {
   Sum4 acc4;
   int64_t nsrc = 0;
   int stamp;  // last value written to sh.mark (never reused by this wave)
+  int turn = 0;  // tiles of leaves until this wave evaluates one (teams)
+
+  // Whether the next tile of leaves is this wave's: the waves of a team take turns.
+  __device__ bool mine() {
+    if constexpr (TEAM == 1) return true;
+    const bool m = turn == 0;
+    turn = m ? TEAM - 1 : turn - 1;
+    return m;
+  }
 
   // n targets from particle first on.
   __device__ void targets(int lane_, int n, int first, bool do_eval_, int stamp_) {
@@ -278,6 +287,7 @@ struct WItem {
     const float4* part = reinterpret_cast<const float4*>(T.part);
     const int ex = incl - ln, rel = first - ex, tile = tile_size();
     for (int u0 = 0; u0 < total; u0 += tile) {
+      if (!mine()) continue;
       const int cnt = min(tile, total - u0);
       const int k = terms(cnt);
       ++stamp;
@@ -345,7 +355,7 @@ __device__ int walk_eval_item(const DevTree& T, const WalkBufs& B, SH& sh, int64
   const float4 gmin = U(gbox[2 * g]), gmax = U(gbox[2 * g + 1]);
   const float4* rec = reinterpret_cast<const float4*>(T.wrec);
 
-  WItem<PLAIN, SH> it{T, sh, in_vgpr(eps2)};
+  WItem<PLAIN, 1, SH> it{T, sh, in_vgpr(eps2)};
   const int first = gi.x + wk.y;
   it.targets(lane, uni(min(kChunk, gi.y - wk.y)), first, do_eval, *stamp);
 
@@ -696,12 +706,14 @@ void walk_eval_persistent_kernel(
 // takes about a microsecond (a dependent gather and two barriers) whatever
 // its width, and a level of a small tree is one or two steps.  Every wave
 // counts what its window appends and, after a barrier, writes it behind that of the
-// waves before it, so the lists keep the order of the one-wave walk.  The waves
-// then evaluate a tile of cells or 64 leaves each whenever all have one, and
-// share the rest evenly at the end; the first wave adds the partial sums in
-// wave order.  At 1000 bodies an item takes 13 us, of which 4.4 are seven steps
+// waves before it, so the lists keep the order of the one-wave walk.  The tiles
+// are its tiles too, so that the compensated sums round to the same results:
+// of cells one per wave whenever all have one, and what there is at the end; of each
+// 64 leaves in turns.  The first wave adds the partial sums in wave order.  At 1000 bodies an item takes 13 us, of which 4.4 are seven steps
 // and 4 its sources; with every wave walking alone and evaluating every NW-th
-// tile, calls took 54 us for 5003 bodies (now 46), 75 for 16384 (67).
+// tile, calls took 54 us for 5003 bodies (now 47), 75 for 16384 (67).
+// (Remainders shared evenly by the waves were 1 to 2 us faster, but are other
+// tiles, with other roundings.)
 // Blocks go to the XCDs in turn, so consecutive items, which cost alike, do
 // too (contiguous ranges per XCD: 10 % longer).
 template <int QCAP, int NW>
@@ -712,7 +724,6 @@ struct TeamShared {
   float4 tile[NW][3 * kTileW];
   int mark[NW][kTileW];
   int count[NW];
-  int nsrc[NW];
 };
 // A wave's part of it, as WItem reads it.
 template <int NW>
@@ -741,7 +752,8 @@ __global__ __launch_bounds__(NW * kLanes) void walk_eval_team_kernel(DevTree T, 
   const float4* rec = reinterpret_cast<const float4*>(T.wrec);
   TeamView<NW> view{sh.cring, sh.lring, sh.tile[wave], sh.mark[wave]};
   view.mark[lane] = 0;
-  WItem<PLAIN, TeamView<NW>> it{T, view, in_vgpr(eps2)};
+  WItem<PLAIN, NW, TeamView<NW>> it{T, view, in_vgpr(eps2)};
+  it.turn = wave;
   const int first = gi.x + wk.y;
   it.targets(lane, uni(min(kChunk, gi.y - wk.y)), first, true, 0);
   const int64_t place = T.perm[first + lane % it.nt];
@@ -802,15 +814,17 @@ __global__ __launch_bounds__(NW * kLanes) void walk_eval_team_kernel(DevTree T, 
     const bool last = rhead == rtail;
     const uint32_t pc = ctail - chead, pl = ltail - lhead;
     if (pc >= NW * tile || (last && pc != 0)) {
-      const uint32_t per = min(tile, (pc + NW - 1) / NW), from = min(pc, per * wave);
-      const uint32_t n = min(per, pc - from);
+      const uint32_t from = min(pc, tile * wave);
+      const uint32_t n = min(tile, pc - from);
       if (n != 0) it.flush_cells(chead + from, (int)n);
-      chead += min(pc, per * NW);
+      // the leaves' turns go on after the last tile (a full round leaves them)
+      const int used = uni((int)((min(pc, tile * NW) + tile - 1) / tile));
+      it.turn = it.turn >= used ? it.turn - used : it.turn - used + NW;
+      chead += min(pc, tile * NW);
     } else if (pl >= (uint32_t)(NW * kTileW) || (last && pl != 0)) {
-      const uint32_t per = min((uint32_t)kTileW, (pl + NW - 1) / NW), from = min(pl, per * wave);
-      const uint32_t n = min(per, pl - from);
-      if (n != 0) it.flush_leaves(lhead + from, (int)n);
-      lhead += min(pl, per * NW);
+      const uint32_t n = min((uint32_t)kTileW, pl);
+      it.flush_leaves(lhead, (int)n);
+      lhead += n;
     } else {
       break;
     }
@@ -827,17 +841,13 @@ __global__ __launch_bounds__(NW * kLanes) void walk_eval_team_kernel(DevTree T, 
       own[k] = v[k];
       own[4 + k] = e[k];
     }
-  if (lane == 0) sh.nsrc[wave] = (int)it.nsrc;
   __syncthreads();
   if (wave != 0) return;
   if (lane < it.nt)
     for (int k = 1; k < NW; ++k)
       it.add(v, e, sums(k), sums(k) + 4);
-  if (lane == 0 && wk.y == 0) {
-    int n = 0;
-    for (int k = 0; k < NW; ++k) n += sh.nsrc[k];
-    reinterpret_cast<int4*>(B.cnt)[g] = make_int4((int)ctail, (int)ltail, n, 0);
-  }
+  if (lane == 0 && wk.y == 0)
+    reinterpret_cast<int4*>(B.cnt)[g] = make_int4((int)ctail, (int)ltail, (int)it.nsrc, 0);
   it.store(B, w, place, v, e, acc, pot);
 }
 
@@ -1051,10 +1061,10 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
   // Waves per work item.  With fewer than about 11000 items (two for each of the
   // 5120 waves the chip holds) one wave per item leaves a long tail, or most of
   // the chip idle; measured with 1 / 2 / 4 / 8 waves per item, in us: 79 items (1000
-  // bodies) 100 / 43 / 38 / 37, 368 items 154 / 74 / 53 / 46, 655 items 173 / 89 / 61 / 55,
-  // 1042 items 186 / 98 / 67 / 69, 1198 items 216 / 120 / 79 / 81, 2590 items 201 / 121 / 110 /
-  // 129 and 125 / 76 / 77 / 102, 5008 items 248 / 198 / 186 / 230 and 137 / 113 / 119 / 173, 7580
-  // items 165 / 150 / 164 / 253, 12641 items 219 / 229 / 258 / 406.  (Not
+  // bodies) 100 / 44 / 39 / 37, 368 items 154 / 74 / 54 / 47, 655 items 173 / 88 / 61 / 55,
+  // 1042 items 186 / 98 / 68 / 71, 1198 items 216 / 121 / 80 / 81, 2590 items 201 / 123 / 111 /
+  // 131 and 125 / 76 / 77 / 101, 5008 items 248 / 201 / 189 / 235 and 137 / 112 / 119 / 172, 7580
+  // items 165 / 149 / 164 / 250, 12641 items 219 / 233 / 259 / 402.  (Not
   // with the learned criterion: every wave would run the network.)
   int team = 1;
   if (!learned && do_eval && !B.export_lists)
