@@ -21,6 +21,7 @@
 #include <cstring>
 #include <vector>
 
+#include "device_common.h"
 #include "octgrav_internal.h"
 
 namespace octgrav {
@@ -190,8 +191,7 @@ struct Cells {
 // starts with it.  (Level by level, two launches each, this was 125 us of a
 // rebuild of 262144 particles; count, scan and write are 20, with fewer gaps.
 // Whole rebuild, before and now, us: 16384 263 / 173, 65536 297 / 214, 262144
-// 394 / 300, 1M 655 / 527; with the moments of
-// inner_moments below 151, 202, 273, 475.)
+// 394 / 300, 1M 655 / 527.)
 constexpr int kMaxLeaf = 64;            // largest n_leaf
 constexpr int kLevels = kMaxDepth + 1;  // levels 0 ... kMaxDepth
 constexpr int kST = 1024;               // particles, and threads, per block
@@ -283,10 +283,11 @@ __device__ __forceinline__ void close_parent(const Cells& C, int64_t c, int64_t 
 }
 
 // Level ranges of the particles and each block's starts per level (cnt[L *
-// gridDim.x + block]; a 0 behind the last).
+// gridDim.x + block]; a 0 behind the last).  Also clears the group marks.
 __global__ __launch_bounds__(kST) void starts_kernel(const uint64_t* __restrict__ key, int64_t n,
                                                      int n_leaf, uchar2* __restrict__ range,
-                                                     int32_t* __restrict__ cnt) {
+                                                     int32_t* __restrict__ cnt,
+                                                     int32_t* __restrict__ group_at) {
   __shared__ int8_t sw[2][kST + kMaxLeaf];
   __shared__ int rows[kLevels][kSW];
   const int t = threadIdx.x;
@@ -304,6 +305,7 @@ __global__ __launch_bounds__(kST) void starts_kernel(const uint64_t* __restrict_
   if (i < n) {
     r = level_range(key, i, D);
     range[i] = make_uchar2((unsigned char)r.lo, (unsigned char)r.hi);
+    group_at[i] = -1;
   }
   count_starts(r, &rows[0][t >> 6], kSW);
   __syncthreads();
@@ -315,32 +317,62 @@ __global__ __launch_bounds__(kST) void starts_kernel(const uint64_t* __restrict_
   if (t == 0 && blockIdx.x == 0) cnt[(int64_t)kLevels * gridDim.x] = 0;
 }
 
-// The cells, numbered by the scan of the counts; block 0 records where each
-// level begins.
+// The cells, numbered by the counts; block 0 records where each level begins.
+// SCANNED: sums holds the scan of the counts; otherwise the counts, of which
+// every block adds up those before its own, a wave per level (at most kOwnScan
+// blocks: two launches less, rebuilds of 16384 and 262144 particles 153 -> 136 and
+// 222 -> 193 us together with the groups' two launches below).
+constexpr int kOwnScan = 1024;
+template <bool SCANNED>
 __global__ __launch_bounds__(kST) void cells_kernel(Cells C, const uint64_t* __restrict__ key,
                                                     int32_t n, int n_leaf,
                                                     const uchar2* __restrict__ range,
-                                                    const int32_t* __restrict__ before,
+                                                    const int32_t* __restrict__ sums,
                                                     int64_t cap, int64_t* __restrict__ level) {
   __shared__ int rows[kLevels][kSW];
-  const int t = threadIdx.x;
-  const int64_t i = (int64_t)blockIdx.x * kST + t;
+  __shared__ int all[kLevels + 1], before[kLevels];
+  const int t = threadIdx.x, nb = (int)gridDim.x, blk = (int)blockIdx.x;
+  const int64_t i = (int64_t)blk * kST + t;
   LevelRange r{1, 0};
   if (i < n) {
     const uchar2 v = range[i];
     r = LevelRange{v.x, v.y};
   }
   count_starts(r, &rows[0][t >> 6], kSW);
-  __syncthreads();
-  if (t < kLevels) {
-    int at = before[(int64_t)t * gridDim.x + blockIdx.x];
-    for (int v = 0; v < kSW; ++v) {
-      const int k = rows[t][v];
-      rows[t][v] = at;
-      at += k;
+  if (!SCANNED) {
+    for (int L = t >> 6; L < kLevels; L += kSW) {
+      int a = 0, b = 0;
+      for (int k = t & 63; k < nb; k += 64) {
+        const int v = sums[L * nb + k];
+        a += v;
+        b += k < blk ? v : 0;
+      }
+      for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
+      }
+      if ((t & 63) == 0) {
+        all[L] = a;
+        before[L] = b;
+      }
     }
   }
-  if (t <= kLevels && blockIdx.x == 0) level[t] = before[(int64_t)t * gridDim.x];
+  __syncthreads();
+  if (t <= kLevels) {
+    int begin = 0;  // the level's first cell
+    if (SCANNED) begin = sums[(int64_t)t * nb];
+    else
+      for (int L = 0; L < t; ++L) begin += all[L];
+    if (blk == 0) level[t] = begin;
+    if (t < kLevels) {
+      int at = SCANNED ? sums[(int64_t)t * nb + blk] : begin + before[t];
+      for (int v = 0; v < kSW; ++v) {
+        const int k = rows[t][v];
+        rows[t][v] = at;
+        at += k;
+      }
+    }
+  }
   __syncthreads();
   write_cells(C, key, n, (int32_t)i, r, n_leaf, cap, &rows[0][t >> 6], kSW);
 }
@@ -604,23 +636,30 @@ __device__ __forceinline__ void cell_image(const Cells& C, int64_t c, const doub
                                    log2f(1.0f + (float)dc) / log2f(22.0f), sqrtf(s2) / lf, 0.0f);
 }
 
-// cell_image of every cell, and the leaves of each block's cells.
+__device__ __forceinline__ bool is_group(const Cells& C, int64_t c, int n_group) {
+  const bool cand = C.n[c] <= n_group || C.nc[c] == 0;
+  const bool top = c == 0 || C.n[C.parent[c]] > n_group;
+  return cand && top;
+}
+
+// cell_image of every cell, the leaves of each block's cells, and the groups
+// (the maximal cells with at most n_group particles, or leaves): their
+// particle ranges partition the particles, so each is marked at its first
+// particle, which orders them.
 __global__ void images_kernel(Cells C, int64_t nc, const double* __restrict__ box,
                               const double* __restrict__ mp64, Images I,
-                              int32_t* __restrict__ leaf_part) {
+                              int32_t* __restrict__ leaf_part, int n_group,
+                              int32_t* __restrict__ group_at) {
   __shared__ int sh[kT / 64];
   const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
   // the block's leaf count (one store per block: same-address atomics
   // from every wave serialise)
   const int nl = block_sum(c < nc && C.nc[c < nc ? c : 0] == 0 ? 1 : 0, sh);
   if (threadIdx.x == 0) leaf_part[blockIdx.x] = nl;
-  if (c < nc) cell_image(C, c, box, mp64, I);
-}
-
-__device__ __forceinline__ bool is_group(const Cells& C, int64_t c, int n_group) {
-  const bool cand = C.n[c] <= n_group || C.nc[c] == 0;
-  const bool top = c == 0 || C.n[C.parent[c]] > n_group;
-  return cand && top;
+  if (c < nc) {
+    cell_image(C, c, box, mp64, I);
+    if (is_group(C, c, n_group)) group_at[C.first[c]] = (int32_t)c;
+  }
 }
 
 // Arrays per group.
@@ -630,6 +669,15 @@ struct Groups {
   float4* box;
 };
 
+// Chunks of each item class of a group of n particles.
+__device__ __forceinline__ int4 group_chunks(int32_t n) {
+  const int32_t rest = n % kChunk;
+  int32_t k[kItemClasses] = {0, 0, 0, 0};
+  k[item_class(kChunk)] = n / kChunk;
+  for (int q = 0; q < kItemClasses; ++q) k[q] += rest > 0 && item_class(rest) == q;
+  return make_int4(k[0], k[1], k[2], k[3]);
+}
+
 // Writes group g, cell c; returns its chunks per item class.
 __device__ __forceinline__ int4 write_group(const Cells& C, int64_t g, int32_t c,
                                             const double* __restrict__ box, const Groups& G) {
@@ -638,11 +686,7 @@ __device__ __forceinline__ int4 write_group(const Cells& C, int64_t g, int32_t c
   const double* bx = box + 6 * (int64_t)c;
   G.box[2 * g] = make_float4((float)bx[0], (float)bx[1], (float)bx[2], 0.0f);
   G.box[2 * g + 1] = make_float4((float)bx[3], (float)bx[4], (float)bx[5], 0.0f);
-  const int32_t rest = C.n[c] % kChunk;
-  int32_t k[kItemClasses] = {0, 0, 0, 0};
-  k[item_class(kChunk)] = C.n[c] / kChunk;
-  for (int q = 0; q < kItemClasses; ++q) k[q] += rest > 0 && item_class(rest) == q;
-  return make_int4(k[0], k[1], k[2], k[3]);
+  return group_chunks(C.n[c]);
 }
 
 // Work items of group g of n particles, in group order (work) and class by
@@ -661,50 +705,11 @@ __device__ __forceinline__ void write_items(int64_t g, int32_t n, int4 p, int4 t
   }
 }
 
-// Groups: the maximal cells with at most n_group particles, or leaves; their
-// particle ranges partition the particles, so marking each group at its first
-// particle and compacting orders them by first particle.
-// (Also clears the nc + 1 per-group chunk counts that group_fill_kernel
-// fills and the chunk scan reads: chunks of each item class.)
-__global__ void group_mark_kernel(Cells C, int64_t nc, int n_group, int32_t* __restrict__ at,
-                                  int4* __restrict__ nchunk) {
-  const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (c > nc) return;
-  nchunk[c] = make_int4(0, 0, 0, 0);
-  if (c == nc) return;
-  if (is_group(C, c, n_group)) at[C.first[c]] = (int32_t)c;
-}
-
-// Group-start flags of the n particles, and a 0 at f[n] for the scan.
-__global__ void flag_kernel(const int32_t* __restrict__ at, int64_t n, int32_t* __restrict__ f) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i < n) f[i] = at[i] >= 0;
-  else if (i == n) f[n] = 0;
-}
-
-__global__ void group_fill_kernel(const int32_t* __restrict__ at, const int32_t* __restrict__ f,
-                                  const int32_t* __restrict__ pre, int64_t n, Cells C,
-                                  const double* __restrict__ box, Groups G,
-                                  int4* __restrict__ nchunk) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i >= n || !f[i]) return;
-  nchunk[pre[i]] = write_group(C, pre[i], at[i], box, G);
-}
-
 struct Int4Sum {
   __host__ __device__ int4 operator()(const int4& a, const int4& b) const {
     return make_int4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
   }
 };
-
-// Work items of every group; pre and all: chunks of each class in the groups
-// before, and in all groups.
-__global__ void work_kernel(const int4* __restrict__ pre, const int4* __restrict__ all,
-                            const int4* __restrict__ ginfo, const int32_t* __restrict__ ngp,
-                            int2* __restrict__ work, int2* __restrict__ wwork) {
-  const int64_t g = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (g < *ngp) write_items(g, ginfo[g].y, pre[g], *all, work, wwork);
-}
 
 // The build's scalars the host needs, gathered in one place on the device so
 // that one copy fetches them.
@@ -717,32 +722,35 @@ struct BuildInfo {
 };
 
 // ---- small trees: three launches (keys, order, and one block for all the
-// rest) do what the kernels above and below do in about 30, which for a few
+// rest) do what the kernels above and below do in about 25, which for a few
 // thousand particles are all launch and latency.  The same functions and orders, so the
 // same tree.  Rebuild of a Plummer sphere, many launches against three, in us:
-//   300: 130 / 52    1000: 133 / 60    3000: 147 / 83    5003: 149 / 106
-//   8192: 150 / 146
-constexpr int kSmallN = 8192;  // sorted keys in LDS: 64 KB
+//   300: 94 / 49    1000: 102 / 57    3000: 117 / 79    5003: 136 / 102
+//   8192: 129 / 140
+constexpr int kOneBlock = 7168;  // particles up to which these are used
+constexpr int kSmallN = 8192;    // what they hold (sorted keys in LDS: 64 KB)
 constexpr int kSmallT = 1024;
 
-// Exclusive prefix of v over the block in thread order, and the block total.
-__device__ int small_exclusive(int v, int* total, int* sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int incl = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
-  }
-  if (lane == 63) sh[w] = incl;
-  __syncthreads();
-  int base = 0, tot = 0;
-  for (int k = 0; k < kSmallT / 64; ++k) {
-    base += k < w ? sh[k] : 0;
-    tot += sh[k];
+// Exclusive prefixes of the N values over the block in thread order, and the
+// block totals.
+template <int N>
+__device__ __forceinline__ void block_exclusives(int (&v)[N], int (&total)[N], int (*sh)[N]) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int kW = kSmallT / 64;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int incl = dev::wave_inclusive_sum(v[k]);
+    if (lane == 63) sh[w][k] = incl;
+    v[k] = incl - v[k];
   }
   __syncthreads();
-  *total = tot;
-  return base + incl - v;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int incl = dev::wave_inclusive_sum(lane < kW ? sh[lane][k] : 0);
+    total[k] = __builtin_amdgcn_readlane(incl, kW - 1);
+    v[k] += w == 0 ? 0 : __builtin_amdgcn_readlane(incl, max(w - 1, 0));
+  }
+  __syncthreads();
 }
 
 // Input check, root cube and keys: kSmallKeys keys a block, each block after a
@@ -1040,7 +1048,8 @@ __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
   uint64_t* skey = u.split.key;
   auto& sw = u.split.sw;
   __shared__ int rows[kLevels * kRows];
-  __shared__ int sh[kSmallT / 64];
+  __shared__ int sh[kSmallT / 64][4];
+  auto* sh1 = reinterpret_cast<int(*)[1]>(&sh[0][0]);
   __shared__ int lbegs[kLevels + 1];
   const int t = threadIdx.x, w = t >> 6;
   for (int i = t; i < n; i += kSmallT) {
@@ -1070,14 +1079,16 @@ __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
   }
   __syncthreads();
   constexpr int kPer = (kLevels * kRows + kSmallT - 1) / kSmallT;
-  int mine[kPer], sum = 0, nc;
+  int mine[kPer], sum[1] = {0}, cells[1];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     const int e = t * kPer + k;
     mine[k] = e < kLevels * kRows ? rows[e] : 0;
-    sum += mine[k];
+    sum[0] += mine[k];
   }
-  int before = small_exclusive(sum, &nc, sh);
+  block_exclusives(sum, cells, sh1);
+  const int nc = cells[0];
+  int before = sum[0];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     const int e = t * kPer + k;
@@ -1115,21 +1126,22 @@ __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
   }
 
   // Images, leaves and group marks.
-  int nl = 0;
+  int nl[1] = {0}, leaves[1];
   for (int c = t; c < nc; c += kSmallT) {
     cell_image(C, c, box, mp64, I);
-    nl += C.nc[c] == 0;
+    nl[0] += C.nc[c] == 0;
     if (is_group(C, c, n_group)) at[C.first[c]] = c;
   }
-  int leaves;
-  small_exclusive(nl, &leaves, sh);  // (its barriers also order the marks)
+  block_exclusives(nl, leaves, sh1);  // (its barriers also order the marks)
 
   // Groups in particle order, then their work items.
   const int per = (n + kSmallT - 1) / kSmallT;
   const int i0 = min(n, t * per), i1 = min(n, i0 + per);
-  int k = 0, ng;
-  for (int i = i0; i < i1; ++i) k += at[i] >= 0;
-  int g = small_exclusive(k, &ng, sh);
+  int k[1] = {0}, groups[1];
+  for (int i = i0; i < i1; ++i) k[0] += at[i] >= 0;
+  block_exclusives(k, groups, sh1);
+  const int ng = groups[0];
+  int g = k[0];
   for (int i = i0; i < i1; ++i)
     if (at[i] >= 0) {
       nchunk[g] = write_group(C, g, at[i], box, G);
@@ -1141,10 +1153,10 @@ __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
   int4 s = make_int4(0, 0, 0, 0), p, tot;
   const Int4Sum add;
   for (int i = g0; i < g1; ++i) s = add(s, nchunk[i]);
-  p.x = small_exclusive(s.x, &tot.x, sh);
-  p.y = small_exclusive(s.y, &tot.y, sh);
-  p.z = small_exclusive(s.z, &tot.z, sh);
-  p.w = small_exclusive(s.w, &tot.w, sh);
+  int v[4] = {s.x, s.y, s.z, s.w}, all[4];
+  block_exclusives(v, all, sh);
+  p = make_int4(v[0], v[1], v[2], v[3]);
+  tot = make_int4(all[0], all[1], all[2], all[3]);
   for (int i = g0; i < g1; ++i) {
     write_items(i, G.info[i].y, p, tot, work, wwork);
     p = add(p, nchunk[i]);
@@ -1152,24 +1164,94 @@ __global__ __launch_bounds__(kSmallT) void small_tree_kernel(
   if (t == 0) {
     info->ng = ng;
     info->nw = tot.x + tot.y + tot.z + tot.w;
-    info->leaves = leaves;
+    info->leaves = leaves[0];
   }
 }
 
-// The group and work-item counts and the leaf count (sum of the images
-// kernel's nb per-block counts).
-__global__ __launch_bounds__(kT) void counts_kernel(const int32_t* __restrict__ ngp,
-                                                    const int4* __restrict__ nwp,
-                                                    const int32_t* __restrict__ leaf_part,
-                                                    int64_t nb, BuildInfo* __restrict__ info) {
-  __shared__ int sh[kT / 64];
-  int t = 0;
-  for (int64_t i = threadIdx.x; i < nb; i += kT) t += leaf_part[i];
-  t = block_sum(t, sh);
-  if (threadIdx.x == 0) {
-    info->ng = *ngp;
-    info->nw = nwp->x + nwp->y + nwp->z + nwp->w;
-    info->leaves = t;
+// ---- groups and work items from the marks, in two launches: the groups and
+// chunks of each block's per particles, then every block adds up those of the
+// blocks before it and writes its own.  (Marks, flags, two library scans, groups, items and
+// counts were ten launches, 43 us at 262144 particles; these two are 10.)
+constexpr int kGroupBlocks = 1024;  // at most
+
+constexpr int kGroupSums = 5;       // chunks of each class, groups
+
+__global__ __launch_bounds__(kSmallT) void group_count_kernel(Cells C,
+                                                              const int32_t* __restrict__ at,
+                                                              int64_t n, int64_t per,
+                                                              int32_t* __restrict__ sums) {
+  __shared__ int sh[kSmallT / 64][kGroupSums];
+  const int64_t i0 = blockIdx.x * per, i1 = i0 + per < n ? i0 + per : n;
+  int v[kGroupSums] = {0, 0, 0, 0, 0}, total[kGroupSums];
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += kSmallT) {
+    const int32_t c = at[i];
+    if (c < 0) continue;
+    const int4 k = group_chunks(C.n[c]);
+    v[0] += k.x;
+    v[1] += k.y;
+    v[2] += k.z;
+    v[3] += k.w;
+    ++v[4];
+  }
+  block_exclusives(v, total, sh);
+  if (threadIdx.x == 0)
+    for (int k = 0; k < kGroupSums; ++k) sums[k * gridDim.x + blockIdx.x] = total[k];
+}
+
+// Block 0 also records the counts, with the leaves (nl counts of the images kernel).
+__global__ __launch_bounds__(kSmallT) void group_write_kernel(
+    Cells C, const int32_t* __restrict__ at, int64_t n, int64_t per,
+    const int32_t* __restrict__ sums, const double* __restrict__ box, Groups G,
+    int2* __restrict__ work, int2* __restrict__ wwork, const int32_t* __restrict__ leaf_part,
+    int64_t nl, BuildInfo* __restrict__ info) {
+  __shared__ int all[kGroupSums + 1], before[kGroupSums];
+  __shared__ int sh[kSmallT / 64][3];
+  const int t = threadIdx.x, blk = (int)blockIdx.x, nb = (int)gridDim.x, w = t >> 6;
+  // a wave per quantity; one wave of block 0 adds up the leaves
+  if (w < kGroupSums || (w == kGroupSums && blk == 0)) {
+    int a = 0, b = 0;
+    if (w < kGroupSums) {
+      for (int k = t & 63; k < nb; k += 64) {
+        const int v = sums[w * nb + k];
+        a += v;
+        b += k < blk ? v : 0;
+      }
+    } else {
+      for (int64_t k = t & 63; k < nl; k += 64) a += leaf_part[k];
+    }
+    a = dev::wave_inclusive_sum(a);
+    b = dev::wave_inclusive_sum(b);
+    if ((t & 63) == 63) {
+      all[w] = a;
+      if (w < kGroupSums) before[w] = b;
+    }
+  }
+  __syncthreads();
+  const int4 tot = make_int4(all[0], all[1], all[2], all[3]);
+  int4 p = make_int4(before[0], before[1], before[2], before[3]);
+  int g = before[4];
+  const Int4Sum add;
+  const int64_t i0 = blk * per, i1 = i0 + per < n ? i0 + per : n;
+  for (int64_t base = i0; base < i1; base += kSmallT) {
+    const int64_t i = base + t;
+    const int32_t c = i < i1 ? at[i] : -1;
+    const int4 k = c >= 0 ? group_chunks(C.n[c]) : make_int4(0, 0, 0, 0);
+    // a group has at most one chunk of the classes after the first
+    int v[3] = {(c >= 0) | k.y << 16, k.z | k.w << 16, k.x}, all3[3];
+    block_exclusives(v, all3, sh);
+    if (c >= 0) {
+      const int64_t q = g + (v[0] & 0xffff);
+      write_group(C, q, c, box, G);
+      write_items(q, C.n[c], add(p, make_int4(v[2], v[0] >> 16, v[1] & 0xffff, v[1] >> 16)), tot,
+                  work, wwork);
+    }
+    g += all3[0] & 0xffff;
+    p = add(p, make_int4(all3[2], all3[0] >> 16, all3[1] & 0xffff, all3[1] >> 16));
+  }
+  if (blk == 0 && t == 0) {
+    info->ng = all[4];
+    info->nw = tot.x + tot.y + tot.z + tot.w;
+    info->leaves = all[kGroupSums];
   }
 }
 
@@ -1193,15 +1275,6 @@ int exclusive_sum(const T* in, T* out, int64_t n, Scratch& S, hipStream_t s) {
   void* tmp = S.get<char>((int64_t)bytes);
   if (!tmp) return -2;
   return hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, (int)n, s) == hipSuccess ? 0 : -1;
-}
-
-template <typename T, typename Op>
-int exclusive_scan(const T* in, T* out, int64_t n, T init, Op op, Scratch& S, hipStream_t s) {
-  size_t bytes = 0;
-  if (hipcub::DeviceScan::ExclusiveScan(nullptr, bytes, in, out, op, init, (int)n, s) != hipSuccess) return -1;
-  void* tmp = S.get<char>((int64_t)bytes);
-  if (!tmp) return -2;
-  return hipcub::DeviceScan::ExclusiveScan(tmp, bytes, in, out, op, init, (int)n, s) == hipSuccess ? 0 : -1;
 }
 
 }  // namespace
@@ -1326,7 +1399,8 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     mass = q;
   }
   const bool check = inputs_on_device;  // then bbox_kernel checks them
-  const bool small = n <= kSmallN;
+  static_assert(kOneBlock <= kSmallN, "the one block's arrays");
+  const bool small = n <= kOneBlock;
 
   // Root cube (the host's rule on the device's bounding box).
   if (!small) {
@@ -1460,11 +1534,17 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     uchar2* range = S.get<uchar2>(n);
     int32_t* cnt = S.get<int32_t>((int64_t)kLevels * nb + 1);
     int32_t* before = S.get<int32_t>((int64_t)kLevels * nb + 1);
-    if (!range || !cnt || !before) return fail("device allocation failed");
+    int32_t* at = S.get<int32_t>(n);
+    if (!range || !cnt || !before || !at) return fail("device allocation failed");
+    const bool scan = nb > kOwnScan;
+    auto write = [&]() {
+      auto* k = scan ? cells_kernel<true> : cells_kernel<false>;
+      k<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, scan ? before : cnt, cap, info->level);
+    };
     for (bool sorted = !sampled;; sorted = true) {
-      starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt);
-      if (exclusive_sum(cnt, before, (int64_t)kLevels * nb + 1, S, s)) return fail("scan failed");
-      cells_kernel<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, before, cap, info->level);
+      starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt, at);
+      if (scan && exclusive_sum(cnt, before, (int64_t)kLevels * nb + 1, S, s)) return fail("scan failed");
+      write();
       if (!fetch(0, offsetof(BuildInfo, ng))) return fail("subdivision failed");
       if (const char* e = read_levels()) return fail(e);
       if (sorted || !hinfo->unsorted) break;
@@ -1474,7 +1554,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     if (nc > cap) {
       cap = nc;
       if (!cell_arrays()) return fail("device allocation failed");
-      cells_kernel<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, before, cap, info->level);
+      write();
     }
     // Groups <= cells, so that the group and item counts come back in one copy at
     // the end.
@@ -1494,25 +1574,17 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     int32_t* nleaf = S.get<int32_t>(nbi);
     if (!nleaf) return fail("device allocation failed");
     images_kernel<<<blocks(nc), kT, 0, s>>>(
-        C, nc, box, mp64, Images{topo, geo_host, geo, wrec, mp, fcell, depth}, nleaf);
+        C, nc, box, mp64, Images{topo, geo_host, geo, wrec, mp, fcell, depth}, nleaf, n_group, at);
 
     // Groups and work chunks.
-    const int64_t ngcap = nc;
-    int32_t* at = S.get<int32_t>(n);
-    int32_t* f = S.get<int32_t>(n + 1);
-    int32_t* fpre = S.get<int32_t>(n + 1);
-    int4* nchunk = S.get<int4>(ngcap + 1);
-    int4* cpre = S.get<int4>(ngcap + 1);
-    if (!at || !f || !fpre || !nchunk || !cpre) return fail("device allocation failed");
-    if (hipMemsetAsync(at, 0xff, (size_t)n * 4, s) != hipSuccess) return fail("memset failed");
-    group_mark_kernel<<<blocks(nc + 1), kT, 0, s>>>(C, nc, n_group, at, nchunk);
-    flag_kernel<<<blocks(n + 1), kT, 0, s>>>(at, n, f);
-    if (exclusive_sum(f, fpre, n + 1, S, s)) return fail("scan failed");
-    group_fill_kernel<<<blocks(n), kT, 0, s>>>(at, f, fpre, n, C, box, Groups{groups, ginfo, gbox}, nchunk);
-    if (exclusive_scan(nchunk, cpre, ngcap + 1, make_int4(0, 0, 0, 0), Int4Sum(), S, s))
-      return fail("scan failed");
-    work_kernel<<<blocks(ngcap), kT, 0, s>>>(cpre, cpre + ngcap, ginfo, fpre + n, work, wwork);
-    counts_kernel<<<1, kT, 0, s>>>(fpre + n, cpre + ngcap, nleaf, nbi, info);
+    const int64_t per = (n + (int64_t)kGroupBlocks * kSmallT - 1) / ((int64_t)kGroupBlocks * kSmallT) * kSmallT;
+    const int gb = (int)((n + per - 1) / per);
+    int32_t* gsum = S.get<int32_t>(kGroupSums * gb);
+    if (!gsum) return fail("device allocation failed");
+    group_count_kernel<<<gb, kSmallT, 0, s>>>(C, at, n, per, gsum);
+    group_write_kernel<<<gb, kSmallT, 0, s>>>(C, at, n, per, gsum, box,
+                                              Groups{groups, ginfo, gbox}, work, wwork, nleaf, nbi,
+                                              info);
     if (!fetch(offsetof(BuildInfo, ng), sizeof(BuildInfo) - offsetof(BuildInfo, ng)))
       return fail("group and work counts failed");
   }

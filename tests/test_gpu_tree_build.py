@@ -189,3 +189,16 @@ def test_bucket_sort_matches_host(n, kind):
         pos = rng.normal(0.9, 1e-3, (n, 3)).astype(np.float32)
         pos[np.arange(s) * n // s] = rng.uniform(-1, 0, (s, 3)).astype(np.float32)
     _same_tree(pos, rng.uniform(0.5, 2.0, n).astype(np.float32), 16, 64)
+
+
+# The line between one block and many launches; a last group block of few particles; groups of one
+# particle and of one leaf, of every item class, and with several chunks of one group.
+@pytest.mark.parametrize("n,n_leaf,n_group", [(7168, 16, 64), (7169, 16, 64), (7169, 1, 1), (9217, 64, 200),
+                                              (30000, 16, 24), (40961, 8, 500)])
+def test_groups_and_items_match_host(n, n_leaf, n_group):
+    _torch()
+    pos, m = W.milky_way(n, n)
+    H, D = _same_tree(pos, m, n_leaf, n_group)
+    import torch
+    a, b = H.forces(0.6, 0.01), D.forces(0.6, 0.01)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
