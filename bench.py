@@ -20,10 +20,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = ("particles/s and % FP32 VALU peak at N=2^20, learned vs θ-MAC at p99 err 1e-3")
-PEAK_FP32_TFLOPS = 157.3   # MI355X FP32 vector peak (spec sheet; reached only with packed FP32)
+PEAK_FP32_TFLOPS = 157.3   # MI355X FP32 vector peak (spec sheet)
 # Non-packed FP32 (the instructions the force kernels are built with): one
-# wave64 FMA per SIMD per 4 cycles, 256 CUs x 4 SIMDs x 16 lanes x 2 FLOP x 2.4 GHz.
-PEAK_FP32_NONPACKED_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
+# wave64 FMA on vector registers per SIMD per 2 cycles, 256 CUs x 4 SIMDs x 32
+# lanes x 2 FLOP x 2.4 GHz (csrc/valu_rate.hip reaches 104 at the clock FMA leaves).
+PEAK_FP32_NONPACKED_TFLOPS = 256 * 4 * 32 * 2 * 2.4e9 / 1e12
 FLOP_PP, FLOP_PC = 38, 70  # the paper's per-interaction convention (Sec. 3.3)
 
 

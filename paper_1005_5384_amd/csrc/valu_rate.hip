@@ -4,7 +4,9 @@
 // Prints one JSON object: per kind, wave64 instructions per compute unit per
 // cycle of the nominal clock, and for FMA the FP32 rate (2 FLOP per lane).
 // This is the ceiling of the force kernels' arithmetic, which is built
-// without packed FP32 instructions.
+// without packed FP32 instructions.  All operands are vector registers: an
+// instruction with a scalar-register operand (which uniform kernel arguments
+// would be) issues at about half the rate.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -13,6 +15,8 @@ namespace {
 
 template <int KIND>
 __global__ __launch_bounds__(256) void chains_kernel(float* out, int iters, float a, float b) {
+  int bi = (int)b;
+  asm volatile("" : "+v"(a), "+v"(b), "+v"(bi));  // out of the scalar registers
   float x[8];
   int ix[8];
 #pragma unroll
@@ -27,7 +31,7 @@ __global__ __launch_bounds__(256) void chains_kernel(float* out, int iters, floa
       if constexpr (KIND == 1) x[k] = x[k] * a;
       if constexpr (KIND == 2) x[k] = x[k] + a;
       if constexpr (KIND == 3) x[k] = __builtin_amdgcn_rsqf(x[k]);
-      if constexpr (KIND == 4) ix[k] = ix[k] + (int)b;
+      if constexpr (KIND == 4) ix[k] = ix[k] + bi;
     }
   }
   float s = 0.f;
