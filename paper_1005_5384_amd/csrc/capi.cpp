@@ -1676,10 +1676,12 @@ int octgrav_sim_run(octgrav_sim* s, float theta, float eps, float dt, int32_t st
     for (int32_t k = 0; k < steps; ++k) {
       // From the first half-kick on, a failure leaves the step half done.
       s->broken = true;
-      if (launch_kick(s->vel, s->acc, s->n, 0.5f * dt, s->stream) ||
-          launch_drift(s->pos, s->vel, s->n, dt, s->stream))
+      // (The half-kick that ends a step goes into the next one's first launch.)
+      if (launch_kick_drift(s->pos, s->vel, s->acc, s->n, 0.5f * dt, dt, k > 0, s->stream))
         return fail(OCTGRAV_EHIP, "leapfrog launch failed");
       if (int rc = s->rebuild_and_force(&tb, &tf)) return rc;
+    }
+    if (steps > 0) {
       if (launch_kick(s->vel, s->acc, s->n, 0.5f * dt, s->stream))
         return fail(OCTGRAV_EHIP, "leapfrog launch failed");
       s->broken = false;

@@ -260,7 +260,9 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
 
 // Leapfrog pieces: v += h a, x += dt v, and FP64 (1/2 sum m v^2, sum m v).
 int launch_kick(float* vel, const float* acc, int64_t n, float h, void* stream);
-int launch_drift(float* pos, const float* vel, int64_t n, float dt, void* stream);
+// v += h a (twice with both), x += dt v
+int launch_kick_drift(float* pos, float* vel, const float* acc, int64_t n, float h, float dt,
+                      bool both, void* stream);
 int launch_kinetic(const float* mass, const float* vel, int64_t n, double* part, double* out4,
                    void* stream);
 int64_t kinetic_scratch_entries();
