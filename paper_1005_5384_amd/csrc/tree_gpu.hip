@@ -981,13 +981,17 @@ __global__ __launch_bounds__(kSmallT) void bucket_scatter_kernel(const uint64_t*
 // element finds its place by a binary search in the run its own is merged with
 // (keys first, indices only between equal keys; every step lies within the
 // two runs).  (A bitonic network of the next power of two: 26 us at 16384
-// particles in 16 buckets, this 23 at 262144 in 256.)
+// particles in 16 buckets, this 23 at 262144 in 256.)  Also writes the particles
+// in order (a launch of 8 us of its own before, 5 more here).
 __global__ __launch_bounds__(kSmallT) void bucket_sort_kernel(const int32_t* __restrict__ before,
                                                               int nblk,
                                                               const uint64_t* __restrict__ key_in,
                                                               const int32_t* __restrict__ idx_in,
+                                                              const float4* __restrict__ packed,
                                                               uint64_t* __restrict__ sorted,
                                                               int32_t* __restrict__ perm,
+                                                              float4* __restrict__ part,
+                                                              int32_t* __restrict__ iperm,
                                                               int32_t* __restrict__ unsorted) {
   __shared__ uint64_t key[2][kBucketMax];
   __shared__ int32_t idx[2][kBucketMax];
@@ -1024,8 +1028,11 @@ __global__ __launch_bounds__(kSmallT) void bucket_sort_kernel(const int32_t* __r
     __syncthreads();
   }
   for (int i = t; i < m; i += kSmallT) {
+    const int32_t v = idx[cur][i];
     sorted[lo + i] = key[cur][i];
-    perm[lo + i] = idx[cur][i];
+    perm[lo + i] = v;
+    part[lo + i] = packed[v];
+    iperm[v] = lo + i;
   }
 }
 
@@ -1415,10 +1422,15 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   // Keys and the stable sort (ties keep the input order).
   uint64_t* key = S.get<uint64_t>(n);
   uint64_t* key2 = S.get<uint64_t>(n);
-  int32_t* perm = nullptr;
-  int32_t* idx = nullptr;
+  float4* part = nullptr;
+  int32_t *perm = nullptr, *iperm = nullptr, *idx = nullptr;
   float4* packed = nullptr;
-  if (!key || !key2 || alloc.alloc((void**)&perm, (size_t)n * 4)) return fail("device allocation failed");
+  auto A = [&](auto** p, int64_t count) {
+    return alloc.alloc((void**)p, (size_t)count * sizeof(**p)) == 0;
+  };
+  alloc.expect((size_t)n * 24 + 3 * 256);
+  if (!key || !key2 || !A(&perm, n) || !A(&part, n) || !A(&iperm, n))
+    return fail("device allocation failed");
   auto library_sort = [&]() {
     size_t sbytes = 0;
     if (hipcub::DeviceRadixSort::SortPairs(nullptr, sbytes, key, key2, idx, perm, (int)n, 0, 63,
@@ -1452,7 +1464,8 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     bucket_count_kernel<<<nblk, kSmallT, 0, s>>>(key, n, nb, skey, sidx, bucket, cnt);
     if (exclusive_sum(cnt, before, nc, S, s)) return fail("scan failed");
     bucket_scatter_kernel<<<nblk, kSmallT, 0, s>>>(key, n, nb, bucket, before, bkey, bidx);
-    bucket_sort_kernel<<<nb, kSmallT, 0, s>>>(before, nblk, bkey, bidx, key2, perm, &info->unsorted);
+    bucket_sort_kernel<<<nb, kSmallT, 0, s>>>(before, nblk, bkey, bidx, packed, key2, perm, part, iperm,
+                                              &info->unsorted);
   } else if (!small && !library_sort()) {
     return fail("sort failed");
   }
@@ -1486,19 +1499,16 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   };
 
   // Persistent device arrays of the tree, for up to ncb cells and ngb groups.
-  float4 *part = nullptr, *geo_host = nullptr, *geo = nullptr, *wrec = nullptr, *mp = nullptr,
+  float4 *geo_host = nullptr, *geo = nullptr, *wrec = nullptr, *mp = nullptr,
          *fcell = nullptr, *gbox = nullptr;
-  int32_t *iperm = nullptr, *depth = nullptr, *groups = nullptr;
+  int32_t *depth = nullptr, *groups = nullptr;
   double *box = nullptr, *mp64 = nullptr;
   int4 *topo = nullptr, *ginfo = nullptr;
   int2 *work = nullptr, *wwork = nullptr;
-  auto A = [&](auto** p, int64_t count) {
-    return alloc.alloc((void**)p, (size_t)count * sizeof(**p)) == 0;
-  };
   auto persistent = [&](int64_t ncb, int64_t ngb) {
     const int64_t nwb = ngb + n / kChunk + 1;  // a rest per group and the full chunks
-    alloc.expect((size_t)n * 20 + (size_t)ncb * 308 + (size_t)ngb * 52 + (size_t)nwb * 16 + 16 * 256);
-    return A(&part, n) && A(&iperm, n) && A(&box, 6 * ncb) && A(&mp64, 10 * ncb) && A(&topo, ncb) &&
+    alloc.expect((size_t)ncb * 308 + (size_t)ngb * 52 + (size_t)nwb * 16 + 14 * 256);
+    return A(&box, 6 * ncb) && A(&mp64, 10 * ncb) && A(&topo, ncb) &&
            A(&geo_host, ncb) && A(&geo, ncb) && A(&wrec, 2 * ncb) && A(&mp, 3 * ncb) &&
            A(&fcell, 2 * ncb) && A(&depth, ncb) && A(&groups, ngb) && A(&ginfo, ngb) &&
            A(&gbox, 2 * ngb) && A(&work, nwb) && A(&wwork, nwb);
@@ -1521,12 +1531,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
       if (const char* e = read_levels()) return fail(e);
       if (nc <= cap) break;
       cap = nc;
-      const float4* ordered = part;
-      const int32_t* places = iperm;
       if (!cell_arrays() || !persistent(cap, n)) return fail("device allocation failed");
-      if (hipMemcpyAsync(part, ordered, (size_t)n * 16, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-          hipMemcpyAsync(iperm, places, (size_t)n * 4, hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return fail("copy failed");
     }
   } else {
     // Cells of all levels.
@@ -1541,6 +1546,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
       auto* k = scan ? cells_kernel<true> : cells_kernel<false>;
       k<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, scan ? before : cnt, cap, info->level);
     };
+    bool gathered = sampled;
     for (bool sorted = !sampled;; sorted = true) {
       starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt, at);
       if (scan && exclusive_sum(cnt, before, (int64_t)kLevels * nb + 1, S, s)) return fail("scan failed");
@@ -1550,6 +1556,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
       if (sorted || !hinfo->unsorted) break;
       // (what was made of the unsorted keys stays within its arrays)
       if (!library_sort()) return fail("sort failed");
+      gathered = false;
     }
     if (nc > cap) {
       cap = nc;
@@ -1559,7 +1566,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     // Groups <= cells, so that the group and item counts come back in one copy at
     // the end.
     if (!persistent(nc, nc)) return fail("device allocation failed");
-    gather_kernel<<<blocks(n), kT, 0, s>>>(packed, perm, n, part, iperm);
+    if (!gathered) gather_kernel<<<blocks(n), kT, 0, s>>>(packed, perm, n, part, iperm);
     leaf_moments_kernel<<<blocks(nc), kT, 0, s>>>(C, part, nc, box, mp64);
     LevelBegin B{};
     int top = 0;  // levels 0 ... top - 1 go to one block
