@@ -202,3 +202,11 @@ def test_groups_and_items_match_host(n, n_leaf, n_group):
     import torch
     a, b = H.forces(0.6, 0.01), D.forces(0.6, 0.01)
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("n", [(1 << 20) + 1, 1300000])
+def test_build_above_the_bucket_sort_matches_host(n):
+    """More than 2^20 particles: the library's sort and a scan of the cell counts."""
+    _torch()
+    pos, m = W.plummer_clumps(n, 8)
+    _same_tree(pos, m, 16, 64)
