@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "cell_numbers.h"
 #include "octgrav.h"
 #include "octgrav_internal.h"
 
@@ -22,6 +23,18 @@ using namespace octgrav;
 
 namespace octgrav {
 int fallback_waves();
+
+// OCTGRAV_MAX_CELLS=<count> (test-only) lowers the limit.
+int64_t max_cells() {
+  const char* v = std::getenv("OCTGRAV_MAX_CELLS");
+  const long long x = v ? std::atoll(v) : 0;
+  return x > 0 && x < kMaxCells ? x : kMaxCells;
+}
+
+std::string too_many_cells(int64_t nc) {
+  return "tree has " + std::to_string(nc) + " cells; the walks address at most " +
+         std::to_string(max_cells());
+}
 }
 
 namespace {
@@ -375,10 +388,9 @@ struct octgrav_tree : DevAlloc {
     direct_cap = 0;
     dev = false;
     std::string err;
-    if (build_device_tree(pos, mass, true, n, n_leaf, n_group, h, dt, darr, *this, stream, err,
-                          build_pools.get()) != 0)
-      return fail(err.find("must be") != std::string::npos ? OCTGRAV_EINVAL : OCTGRAV_EHIP,
-                  g_err.empty() ? err : g_err);
+    if (int rc = build_device_tree(pos, mass, true, n, n_leaf, n_group, h, dt, darr, *this, stream,
+                                   err, build_pools.get()))
+      return fail(rc == kBuildRefused ? OCTGRAV_EINVAL : OCTGRAV_EHIP, g_err.empty() ? err : g_err);
     host_partial = true;
     return alloc_walk_buffers();
   }
@@ -387,9 +399,7 @@ struct octgrav_tree : DevAlloc {
   // device, from either build).
   int alloc_walk_buffers() {
     const int64_t n = h.n, ng = h.n_groups(), nw = h.n_work();
-    if (dt.nc >= (int64_t(1) << 29))  // the walks' queue entries hold cell id << 3
-      return fail(OCTGRAV_EINVAL, "tree has " + std::to_string(dt.nc) +
-                                      " cells; the walks address at most 2^29 - 1");
+    if (dt.nc > max_cells()) return fail(OCTGRAV_EINVAL, too_many_cells(dt.nc));
     int rc;
     void* p;
     expect((size_t)(ng + 1) * 32 + (size_t)scan_scratch_entries(ng) * 8 +

@@ -251,8 +251,13 @@ struct DeviceArrays {
   const int32_t* depth = nullptr;  // [nc]
   const int32_t* groups = nullptr; // [ng]
 };
+// Most cells of a tree (kMaxCells), and what is said of one with more.
+int64_t max_cells();
+std::string too_many_cells(int64_t nc);
 // Inputs are host arrays (copied) or, with inputs_on_device, device arrays
-// (checked on the device).
+// (checked on the device).  0, kBuildRefused (err: what is wrong with the input,
+// or the tree's size) or another error.
+constexpr int kBuildRefused = -2;
 int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_device, int64_t n,
                       int n_leaf, int n_group, HostTree& h, DevTree& dt, DeviceArrays& out,
                       DevAlloc& alloc, void* stream, std::string& err,

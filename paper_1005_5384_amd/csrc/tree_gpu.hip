@@ -19,8 +19,10 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
+#include "cell_numbers.h"
 #include "device_common.h"
 #include "octgrav_internal.h"
 
@@ -237,8 +239,8 @@ __device__ __forceinline__ void count_starts(LevelRange r, int* row, int stride)
 }
 
 // Writes the cells that start at the wave's particles (this lane's: i), as
-// far as they fit cap cells; row[L * stride]: the number of the wave's first
-// cell of level L.  Particle and child counts of split cells follow later
+// far as they fit cap <= kMaxCells cells; row[L * stride]: the number of the
+// wave's first cell of level L.  Particle and child counts of split cells follow later
 // (close_parent, inner_moments).
 __device__ __forceinline__ void write_cells(const Cells& C, const uint64_t* key, int32_t n,
                                             int32_t i, LevelRange r, int n_leaf, int64_t cap,
@@ -284,9 +286,10 @@ __device__ __forceinline__ void close_parent(const Cells& C, int64_t c, int64_t 
 
 // Level ranges of the particles and each block's starts per level (cnt[L *
 // gridDim.x + block]; a 0 behind the last).  Also clears the group marks.
+template <typename Count>
 __global__ __launch_bounds__(kST) void starts_kernel(const uint64_t* __restrict__ key, int64_t n,
                                                      int n_leaf, uchar2* __restrict__ range,
-                                                     int32_t* __restrict__ cnt,
+                                                     Count* __restrict__ cnt,
                                                      int32_t* __restrict__ group_at) {
   __shared__ int8_t sw[2][kST + kMaxLeaf];
   __shared__ int rows[kLevels][kSW];
@@ -318,16 +321,19 @@ __global__ __launch_bounds__(kST) void starts_kernel(const uint64_t* __restrict_
 }
 
 // The cells, numbered by the counts; block 0 records where each level begins.
-// SCANNED: sums holds the scan of the counts; otherwise the counts, of which
-// every block adds up those before its own, a wave per level (at most kOwnScan
-// blocks: two launches less, rebuilds of 16384 and 262144 particles 153 -> 136 and
-// 222 -> 193 us together with the groups' two launches below).
+// SCANNED: sums holds the scan of the counts (CellSum); otherwise the counts, of
+// which every block adds up those before its own, a wave per level (at most
+// kOwnScan blocks, so 22 * 2^20 cells: two launches less, rebuilds of 16384 and
+// 262144 particles 153 -> 136 and 222 -> 193 us together with the groups' two
+// launches below).
 constexpr int kOwnScan = 1024;
+template <bool SCANNED>
+using StartCount = std::conditional_t<SCANNED, CellSum, int32_t>;
 template <bool SCANNED>
 __global__ __launch_bounds__(kST) void cells_kernel(Cells C, const uint64_t* __restrict__ key,
                                                     int32_t n, int n_leaf,
                                                     const uchar2* __restrict__ range,
-                                                    const int32_t* __restrict__ sums,
+                                                    const StartCount<SCANNED>* __restrict__ sums,
                                                     int64_t cap, int64_t* __restrict__ level) {
   __shared__ int rows[kLevels][kSW];
   __shared__ int all[kLevels + 1], before[kLevels];
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(kST) void cells_kernel(Cells C, const uint64_t* __r
     r = LevelRange{v.x, v.y};
   }
   count_starts(r, &rows[0][t >> 6], kSW);
-  if (!SCANNED) {
+  if constexpr (!SCANNED) {
     for (int L = t >> 6; L < kLevels; L += kSW) {
       int a = 0, b = 0;
       for (int k = t & 63; k < nb; k += 64) {
@@ -359,13 +365,15 @@ __global__ __launch_bounds__(kST) void cells_kernel(Cells C, const uint64_t* __r
   }
   __syncthreads();
   if (t <= kLevels) {
-    int begin = 0;  // the level's first cell
-    if (SCANNED) begin = sums[(int64_t)t * nb];
+    CellSum begin = 0;  // the level's first cell
+    if constexpr (SCANNED) begin = sums[(int64_t)t * nb];
     else
       for (int L = 0; L < t; ++L) begin += all[L];
     if (blk == 0) level[t] = begin;
     if (t < kLevels) {
-      int at = SCANNED ? sums[(int64_t)t * nb + blk] : begin + before[t];
+      int at;
+      if constexpr (SCANNED) at = cell_number(sums[(int64_t)t * nb + blk]);
+      else at = (int)begin + before[t];
       for (int v = 0; v < kSW; ++v) {
         const int k = rows[t][v];
         rows[t][v] = at;
@@ -1472,7 +1480,8 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
 
   // Cell arrays, for twice the particles at first; a tree of more cells has
   // them written again into larger ones.
-  int64_t cap = 2 * n + 64;
+  const int64_t most = max_cells();
+  int64_t cap = std::min(2 * n + 64, most);
   Cells C{};
   auto cell_arrays = [&]() {
     C = Cells{CS.get<int32_t>(cap), CS.get<int32_t>(cap), CS.get<int32_t>(cap),
@@ -1481,11 +1490,13 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   };
   if (!cell_arrays()) return fail("device allocation failed");
   // The scalars of the levels, once fetched: the verdict on the inputs, the
-  // root cube, and the level ranges.
+  // root cube, and the level ranges.  False, with err, where the call is refused.
   int64_t nc = 0;
-  auto read_levels = [&]() -> const char* {
-    if (hinfo->bad & 1) return "positions must be finite with |x| < 2^60";
-    if (hinfo->bad & 2) return "masses must be finite and > 0";
+  auto read_levels = [&]() {
+    if (hinfo->bad) {
+      err = hinfo->bad & 1 ? "positions must be finite with |x| < 2^60" : "masses must be finite and > 0";
+      return false;
+    }
     for (int k = 0; k < 3; ++k) h.corner[k] = hinfo->cube[k];
     h.side = hinfo->cube[3];
     nc = hinfo->level[kLevels];
@@ -1495,7 +1506,12 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
       h.max_level_cells = std::max(h.max_level_cells, hinfo->level[L + 1] - hinfo->level[L]);
       h.max_depth = L;
     }
-    return nullptr;
+    return true;
+  };
+  auto too_many = [&]() {  // (not of keys that are still to be sorted)
+    if (nc <= most) return false;
+    err = too_many_cells(nc);
+    return true;
   };
 
   // Persistent device arrays of the tree, for up to ncb cells and ngb groups.
@@ -1528,7 +1544,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
           Images{topo, geo_host, geo, wrec, mp, fcell, depth}, Groups{groups, ginfo, gbox}, at,
           nchunk, work, wwork, info);
       if (!fetch(0, sizeof(BuildInfo))) return fail("build failed");
-      if (const char* e = read_levels()) return fail(e);
+      if (!read_levels() || too_many()) return kBuildRefused;
       if (nc <= cap) break;
       cap = nc;
       if (!cell_arrays() || !persistent(cap, n)) return fail("device allocation failed");
@@ -1537,27 +1553,36 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     // Cells of all levels.
     const int nb = (int)((n + kST - 1) / kST);
     uchar2* range = S.get<uchar2>(n);
-    int32_t* cnt = S.get<int32_t>((int64_t)kLevels * nb + 1);
-    int32_t* before = S.get<int32_t>((int64_t)kLevels * nb + 1);
-    int32_t* at = S.get<int32_t>(n);
-    if (!range || !cnt || !before || !at) return fail("device allocation failed");
     const bool scan = nb > kOwnScan;
+    const int64_t ncnt = (int64_t)kLevels * nb + 1;
+    int32_t* cnt = scan ? nullptr : S.get<int32_t>(ncnt);
+    CellSum* cnt64 = scan ? S.get<CellSum>(ncnt) : nullptr;
+    CellSum* before = scan ? S.get<CellSum>(ncnt) : nullptr;
+    int32_t* at = S.get<int32_t>(n);
+    if (!range || (scan ? !cnt64 || !before : !cnt) || !at) return fail("device allocation failed");
     auto write = [&]() {
-      auto* k = scan ? cells_kernel<true> : cells_kernel<false>;
-      k<<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, scan ? before : cnt, cap, info->level);
+      if (scan)
+        cells_kernel<true><<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, before, cap, info->level);
+      else
+        cells_kernel<false><<<nb, kST, 0, s>>>(C, key2, (int32_t)n, n_leaf, range, cnt, cap, info->level);
     };
     bool gathered = sampled;
     for (bool sorted = !sampled;; sorted = true) {
-      starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt, at);
-      if (scan && exclusive_sum(cnt, before, (int64_t)kLevels * nb + 1, S, s)) return fail("scan failed");
+      if (scan) {
+        starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt64, at);
+        if (exclusive_sum(cnt64, before, ncnt, S, s)) return fail("scan failed");
+      } else {
+        starts_kernel<<<nb, kST, 0, s>>>(key2, n, n_leaf, range, cnt, at);
+      }
       write();
       if (!fetch(0, offsetof(BuildInfo, ng))) return fail("subdivision failed");
-      if (const char* e = read_levels()) return fail(e);
+      if (!read_levels()) return kBuildRefused;
       if (sorted || !hinfo->unsorted) break;
       // (what was made of the unsorted keys stays within its arrays)
       if (!library_sort()) return fail("sort failed");
       gathered = false;
     }
+    if (too_many()) return kBuildRefused;
     if (nc > cap) {
       cap = nc;
       if (!cell_arrays()) return fail("device allocation failed");
