@@ -53,6 +53,22 @@ bool alloc_fault() {
   return v && v[0] == '1';
 }
 
+// OCTGRAV_FAIL_ALLOC=2: the allocations of page-locked memory fail, which the
+// library does without.
+hipError_t pinned_malloc(void** p, size_t bytes) {
+  const char* v = std::getenv("OCTGRAV_FAIL_ALLOC");
+  if (v && v[0] == '2') return hipErrorOutOfMemory;
+  return hipHostMalloc(p, bytes);
+}
+
+// OCTGRAV_FALLBACK_QUEUE=<power of two> (test-only): caps the global-memory
+// queues of the last walk tier, which then overflow too.
+int64_t fallback_queue_entries(int64_t need) {
+  const char* v = std::getenv("OCTGRAV_FALLBACK_QUEUE");
+  const long long q = v ? std::atoll(v) : 0;
+  return q >= 64 && !(q & (q - 1)) ? std::min<int64_t>(need, q) : need;
+}
+
 // OCTGRAV_DEBUG=1 traces each force call's path decisions on stderr.
 bool debug_trace() {
   static const bool on = [] {
@@ -112,7 +128,7 @@ struct octgrav_mlp {
   MlpHost* host_buffer() {
     if (!host_tried) {
       host_tried = true;
-      if (hipHostMalloc((void**)&host, sizeof(MlpHost)) != hipSuccess) {
+      if (pinned_malloc((void**)&host, sizeof(MlpHost)) != hipSuccess) {
         (void)hipGetLastError();
         host = nullptr;
       } else if (hipHostGetDevicePointer((void**)&host_dev, host, 0) != hipSuccess) {
@@ -420,7 +436,7 @@ struct octgrav_tree : DevAlloc {
     }
     set_ctl(wb, ctl);
     if (!tot_host) {
-      if (hipHostMalloc((void**)&tot_host, kFinishHost * 8) != hipSuccess) {
+      if (pinned_malloc((void**)&tot_host, kFinishHost * 8) != hipSuccess) {
         (void)hipGetLastError();  // read_tot then copies into pageable memory
         tot_host = nullptr;
       } else if (hipHostGetDevicePointer((void**)&tot_host_dev, tot_host, 0) != hipSuccess) {
@@ -440,6 +456,7 @@ struct octgrav_tree : DevAlloc {
     // two consecutive levels, hence at most twice the widest level.
     int64_t cap = 64;
     while (cap < 2 * h.max_level_cells + 64) cap <<= 1;
+    cap = fallback_queue_entries(cap);
     wb.gq_cap = cap;
     wb.gq_waves = fallback_waves();
     // At most 4 GiB of queues.
@@ -766,7 +783,7 @@ static int fused_wave_forces(octgrav_tree* t, WalkBufs b, double* scratch, bool*
     if (last || t->tot_host[8] == 0) break;
     parts = kWalkRest;
   }
-  *clean = true;
+  *clean = tot8[5] == 0;
   return OCTGRAV_OK;
 }
 

@@ -159,7 +159,8 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
 // diagnostics (diag[4]) from the per-item and per-group records, copied to
 // host (device pointer of page-locked memory, kFinishHost entries: the totals,
 // then the number of items the first tier left over; or NULL).  Unless items
-// were left over and !last, it also resets the counters as kWalkInit does.
+// were left over and !last, it also resets the counters as kWalkInit does, but
+// for B.tot[5]: a call that reports it is followed by kWalkInit.
 constexpr int kFinishHost = 9;
 int launch_finish(const DevTree& T, const WalkBufs& B, double* scratch, double* diag, int64_t* host,
                   bool last, void* stream);

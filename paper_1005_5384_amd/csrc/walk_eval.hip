@@ -891,14 +891,14 @@ __global__ __launch_bounds__(kLanes) void walk_eval_fallback_kernel(DevTree T, W
   }
 }
 
-// The counters a call starts from, by threads [0, 64) of one block.
+// The counters a call starts from, by threads [0, 64) of one block.  (Not the
+// last tier's overflow, B.tot[5], which the host may read after them.)
 __device__ __forceinline__ void reset_counters(const WalkBufs& B, int t) {
   if (t < 9) B.wctr[64 * t] = 0;
   if (t == 0) {
     *B.ovf_count = 0;
     *B.ovf_count2 = 0;
     *B.ticket = 0;
-    B.tot[5] = 0;
     B.c_off[0] = 0;  // base of an offsets scan of the counts the walk writes
     B.l_off[0] = 0;
   }
