@@ -123,10 +123,11 @@ __global__ __launch_bounds__(256) void mlp_train_kernel(const uint8_t* __restric
   for (int i = 0; i < 16; ++i) sb1[i] = sb2[i] = sw3[i] = 0.f;
 
   for (int64_t base = (int64_t)blockIdx.x * 64; base < B; base += (int64_t)gridDim.x * 64) {
-    // inputs, rounded once; samples past the batch are zero
+    // inputs, rounded once (by the conversion of the forward pass, which keeps
+    // every NaN one); samples past the batch are zero
     for (int i = tid; i < 64 * kMlpIn; i += 256) {
       const int sm = i / kMlpIn, k = i % kMlpIn;
-      const uint16_t v = base + sm < B ? (uint16_t)bf16_bits(x[base * kMlpIn + i]) : (uint16_t)0;
+      const uint16_t v = base + sm < B ? (uint16_t)pk_bf16(x[base * kMlpIn + i], 0.f) : (uint16_t)0;
       L.xs[sm * kXsLd + k] = v;
       L.xr[k * kTrLd + sm] = v;
     }
@@ -157,8 +158,9 @@ __global__ __launch_bounds__(256) void mlp_train_kernel(const uint8_t* __restric
         sw3[4 * mb + r] += dy * bf16_round(fmaxf(a2[mb][r], 0.f));
       }
       p2[mb] = make_uint2(pk_bf16(d[0], d[1]), pk_bf16(d[2], d[3]));
-      const uint2 h = make_uint2(relu_pk(pk_bf16(a1[mb][0], a1[mb][1])),
-                                 relu_pk(pk_bf16(a1[mb][2], a1[mb][3])));
+      // (a NaN activation counts as inactive here, as in dh1 and dh2)
+      const uint2 h = make_uint2(pk_bf16(fmaxf(a1[mb][0], 0.f), fmaxf(a1[mb][1], 0.f)),
+                                 pk_bf16(fmaxf(a1[mb][2], 0.f), fmaxf(a1[mb][3], 0.f)));
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         L.d2[(k0 + r) * kTrLd + sm] = (uint16_t)((r & 2 ? p2[mb].y : p2[mb].x) >> (16 * (r & 1)));
