@@ -47,10 +47,13 @@ int fail(int code, const std::string& msg) {
 }
 
 // Set by the environment variable OCTGRAV_FAIL_ALLOC=1 (test-only fault
-// injection): every device allocation of the library fails.
-bool alloc_fault() {
+// injection): every device allocation of the library fails; by
+// OCTGRAV_ALLOC_LIMIT=<bytes>: a tree's allocations of more than this.
+bool alloc_fault(size_t bytes = 0) {
   const char* v = std::getenv("OCTGRAV_FAIL_ALLOC");
-  return v && v[0] == '1';
+  if (v && v[0] == '1') return true;
+  const char* m = std::getenv("OCTGRAV_ALLOC_LIMIT");
+  return m && (long long)bytes > std::atoll(m);
 }
 
 // OCTGRAV_FAIL_ALLOC=2: the allocations of page-locked memory fail, which the
@@ -220,7 +223,7 @@ struct octgrav_tree : DevAlloc {
   Arena arena;
   int alloc(void** p, size_t bytes) override {
     if (pool) return dalloc(p, bytes);
-    if (alloc_fault()) return fail(OCTGRAV_ENOMEM, "device allocation failed (injected)");
+    if (alloc_fault(bytes)) return fail(OCTGRAV_ENOMEM, "device allocation failed (injected)");
     *p = arena.take(bytes);
     if (!*p) return fail(OCTGRAV_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
     return OCTGRAV_OK;
@@ -261,7 +264,7 @@ struct octgrav_tree : DevAlloc {
   }
 
   int dalloc(void** p, size_t bytes) {
-    if (alloc_fault()) return fail(OCTGRAV_ENOMEM, "device allocation failed (injected)");
+    if (alloc_fault(bytes)) return fail(OCTGRAV_ENOMEM, "device allocation failed (injected)");
     if (pool) {
       *p = pool->take(bytes);
       if (!*p) return fail(OCTGRAV_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
@@ -478,11 +481,17 @@ struct octgrav_tree : DevAlloc {
   }
 
   // The queues of the last walk tier, up to 4 GiB that most handles never use:
-  // allocated before its first launch.
+  // allocated before its first launch.  That may be in the middle of a program
+  // that has filled the device since the handle was made, so where they don't fit
+  // there are fewer queues (and waves to walk with them), one at least.
   int fallback_queues() {
     if (wb.gq) return OCTGRAV_OK;
     void* p = nullptr;
-    if (int rc = dalloc(&p, (size_t)wb.gq_waves * wb.gq_cap * 4)) return rc;
+    while (int rc = dalloc(&p, (size_t)wb.gq_waves * wb.gq_cap * 4)) {
+      if (wb.gq_waves <= 1) return rc;
+      wb.gq_waves /= 2;
+      g_err.clear();
+    }
     wb.gq = (int32_t*)p;
     return OCTGRAV_OK;
   }
@@ -762,6 +771,7 @@ static int fused_wave_forces(octgrav_tree* t, WalkBufs b, double* scratch, bool*
     if ((parts & kWalkRest) && !b.gq) {
       if (int rc = t->fallback_queues()) return rc;
       b.gq = t->wb.gq;
+      b.gq_waves = t->wb.gq_waves;
     }
     if (launch_walk_eval(t->dt, b, theta, eps, plain, true, acc, pot, t->stream, parts))
       return fail(OCTGRAV_EHIP, "walk+evaluation launch failed");

@@ -1,0 +1,50 @@
+"""Calls whose walks outgrow the first tier's queues: what the later tiers need is
+made inside the call."""
+import numpy as np
+import pytest
+
+from paper_1005_5384_amd import octgrav as og
+from paper_1005_5384_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("path", ["fused_wave", "fused_block", "two_pass"])
+@pytest.mark.parametrize("n", [3000, 40000])
+def test_little_memory_left_for_the_queues(n, path, monkeypatch):
+    """The device refuses the queues of all waves: fewer waves walk, with the same results; it refuses a
+    single queue: the call says so, and works once there is memory."""
+    import torch
+    pos, m = W.plummer(n, 5)
+    monkeypatch.setenv("OCTGRAV_LDS_QUEUE", "64")
+    ref = og.Tree(pos, m, 1, 64).forces(0.5, 0.01, path=path)
+    T = og.Tree(pos, m, 1, 64)
+    acc = torch.empty((n, 3), dtype=torch.float32, device="cuda")
+    monkeypatch.setenv("OCTGRAV_ALLOC_LIMIT", "1000")
+    with pytest.raises(og.OctgravError) as e:
+        T.forces(0.5, 0.01, acc=acc, path=path)
+    assert e.value.code == og.ENOMEM
+    queue = 4  # bytes of a queue: 2 x the widest level + 64 entries of 4, up to a power of two
+    while queue < 4 * (2 * T.stats["max_level_cells"] + 64):
+        queue *= 2
+    # the two-pass path also allocates its lists: all that is needed but the queues of more than 3 waves
+    lists = 0 if path != "two_pass" else 64 << 20
+    monkeypatch.setenv("OCTGRAV_ALLOC_LIMIT", str(max(3 * queue, lists)))
+    a = T.forces(0.5, 0.01, path=path)
+    assert torch.equal(a[0], ref[0]) and torch.equal(a[1], ref[1])
+
+
+def test_little_memory_left_in_a_rebuilt_handle(monkeypatch):
+    pos, vel, m = W.plummer_with_velocities(6000, 5)
+    monkeypatch.setenv("OCTGRAV_LDS_QUEUE", "64")
+    S = og.Sim(pos, vel, m, 1, 64)
+    S.run(0.5, 0.01, 1.0 / 64, 3)
+    F = og.Sim(pos, vel, m, 1, 64)
+    F.run(1.0, 0.01, 0.0, 1)  # the arrays of the tree are in place, with headroom
+    cells = og.Tree(pos, m, 1, 64, device_build=True).stats["n_cells"]
+    # every array of the tree (80 bytes per cell the largest), not the 2048 waves' queues
+    monkeypatch.setenv("OCTGRAV_ALLOC_LIMIT", str(100 * (2 * 6000 + 64)))
+    assert 2048 * 4 * 4096 > 100 * (2 * 6000 + 64) > 80 * cells
+    F.run(0.5, 0.01, 1.0 / 64, 3)
+    for a, b in zip(S.state(), F.state()):
+        assert np.array_equal(a, b)
