@@ -207,6 +207,10 @@ struct octgrav_tree : DevAlloc {
   // the last call left reset (ctl_clean) stay so when the tree is rebuilt.
   void* ctl = nullptr;
   bool ctl_clean = false;
+  // Whether the last fused wave call left items to the later tiers: the next
+  // one, most often with the same angle on much the same tree, launches them
+  // with the first (fused_wave_forces).
+  bool later_tiers = false;
 
   ~octgrav_tree() {
     if (tot_host) hipHostFree(tot_host);
@@ -758,14 +762,17 @@ static int launch_fused(octgrav_tree* t, Path p, float theta, float eps, bool pl
 // tot8: the first tier and the finishing kernel, whose totals come back through
 // page-locked memory.  The later tiers run only when that reports items left
 // over (no work item of the benchmark sets, from theta 0.3 up), followed by the
-// finishing kernel again; without page-locked memory they always run.
+// finishing kernel again; without page-locked memory they always run, and so they
+// do after a call that left items over: waiting for the host before them costs
+// 18 us (5003 single particles as groups, theta 0.1: 387 -> 368), the two launches
+// with nothing to do 9.
 // *clean: the counters of b are reset.  Events (timed): ev[4] after the
 // evaluation, ev[5] at the end.
 static int fused_wave_forces(octgrav_tree* t, WalkBufs b, double* scratch, bool* clean,
                              float theta, float eps, bool plain, float* acc, float* pot, bool timed,
                              int64_t* tot8) {
   int64_t* host = t->tot_host_dev;
-  int parts = (*clean ? 0 : kWalkInit) | kWalkFirst | (host ? 0 : kWalkRest);
+  int parts = (*clean ? 0 : kWalkInit) | kWalkFirst | (host && !t->later_tiers ? 0 : kWalkRest);
   *clean = false;
   for (;;) {
     if ((parts & kWalkRest) && !b.gq) {
@@ -790,6 +797,7 @@ static int fused_wave_forces(octgrav_tree* t, WalkBufs b, double* scratch, bool*
     if (debug_trace())
       std::fprintf(stderr, "octgrav: fused wave, items %lld, left to the later tiers %lld%s\n",
                    (long long)t->dt.nw, host ? (long long)t->tot_host[8] : -1ll, last ? " (run)" : "");
+    if (host) t->later_tiers = t->tot_host[8] != 0;
     if (last || t->tot_host[8] == 0) break;
     parts = kWalkRest;
   }

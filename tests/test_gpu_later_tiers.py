@@ -1,5 +1,9 @@
 """Calls whose walks outgrow the first tier's queues: what the later tiers need is
 made inside the call."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -7,6 +11,8 @@ from paper_1005_5384_amd import octgrav as og
 from paper_1005_5384_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.parametrize("path", ["fused_wave", "fused_block", "two_pass"])
@@ -48,3 +54,29 @@ def test_little_memory_left_in_a_rebuilt_handle(monkeypatch):
     F.run(0.5, 0.01, 1.0 / 64, 3)
     for a, b in zip(S.state(), F.state()):
         assert np.array_equal(a, b)
+
+
+TIERS = """
+import sys, torch
+from paper_1005_5384_amd import octgrav as og, workloads as W
+pos, m = W.plummer(16384, 3)
+T = og.Tree(pos, m, 1, 1)
+for theta in (0.5, 0.1, 0.1, 0.5, 0.5):
+    print("#", file=sys.stderr, flush=True)
+    a = T.forces(theta, 0.01)
+    print("# fresh", file=sys.stderr, flush=True)
+    b = og.Tree(pos, m, 1, 1).forces(theta, 0.01)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+"""
+
+
+def test_tiers_follow_the_calls():
+    """After a call that left items to the later tiers the next one launches them at once, until one
+    leaves none; the results are a fresh handle's."""
+    r = subprocess.run([sys.executable, "-c", TIERS], cwd=ROOT, env=dict(os.environ, OCTGRAV_DEBUG="1"),
+                       capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stderr
+    ran = [["(run)" in l for l in c.splitlines() if "items" in l] for c in r.stderr.split("#")[1:]]
+    # the first tier alone; the others after it; with it; with it once more, for nothing; alone again
+    assert ran[::2] == [[False], [False, True], [True], [True], [False]], r.stderr
+    assert ran[1::2] == [[False], [False, True], [False, True], [False], [False]], r.stderr
