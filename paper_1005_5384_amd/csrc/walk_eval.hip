@@ -1053,10 +1053,12 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
   if (parts & kWalkInit) fused_init_kernel<<<1, 64, 0, s>>>(B);
   // The breadth-first FIFO holds about two tree levels of the group's walk,
   // which grow like theta^-3, as entries of up to eight children: 512 entries
-  // (4 KB) held every walk of the 2^20 Plummer sphere and the 4M clumps at
+  // (2 KB) held every walk of the 2^20 Plummer sphere and the 4M clumps at
   // theta 0.3 ... 0.5.  Tiers: 512-entry LDS queues (20 waves per CU), then
-  // the overflows with 2048-entry LDS queues (one wave per block, 7 per CU),
-  // then global-memory queues.
+  // the overflows with 2048-entry LDS queues (one wave per block, 10 per CU, all
+  // that its LDS holds: with 7, calls of 16384 single particles as groups took
+  // 2330 us at theta 0.1, now 1847, and of 2^20 particles 38.0 ms at theta 0.2,
+  // now 30.0), then global-memory queues.
   const bool learned = B.mlp != nullptr;
   // Waves per work item.  With fewer than about 11000 items (two for each of the
   // 5120 waves the chip holds) one wave per item leaves a long tail, or most of
@@ -1087,7 +1089,7 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
             T, B, th2, eps2, acc, pot, do_eval, nullptr, nullptr, B.ovf_list, B.ovf_count);
     }
     if (parts & kWalkRest) {
-      walk_eval_persistent_kernel<P, 2048, L, 1, true><<<8 * 224, kLanes, 0, s>>>(
+      walk_eval_persistent_kernel<P, 2048, L, 1, true><<<8 * 320, kLanes, 0, s>>>(
           T, B, th2, eps2, acc, pot, do_eval, B.ovf_list, B.ovf_count, B.ovf_list2, B.ovf_count2);
       walk_eval_fallback_kernel<P, L><<<B.gq_waves, kLanes, 0, s>>>(
           T, B, th2, eps2, acc, pot, do_eval, B.ovf_list2, B.ovf_count2);

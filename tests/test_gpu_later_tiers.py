@@ -80,3 +80,28 @@ def test_tiers_follow_the_calls():
     # the first tier alone; the others after it; with it; with it once more, for nothing; alone again
     assert ran[::2] == [[False], [False, True], [True], [True], [False]], r.stderr
     assert ran[1::2] == [[False], [False, True], [False, True], [False], [False]], r.stderr
+
+
+@pytest.mark.parametrize("n,theta", [(16384, 0.1), (5003, 0.1), (70000, 0.12)])
+@pytest.mark.parametrize("learned", [False, True])
+def test_more_items_than_the_later_tiers_hold(n, theta, learned):
+    """Several items for each wave of the second tier, with its own queues: lists of the two-pass walk's
+    lengths, forces within the gates of the oracle's."""
+    import oracle
+    from paper_1005_5384_amd import learned as L
+    pos, m = W.plummer(n, 3)
+    T = og.Tree(pos, m, 1, 1 if n < 20000 else 32)
+    if learned:  # never accepted: the lists of theta
+        T.set_mac(og.Mlp(L.init_params(1)), theta, 1.0, 0.0, float("inf"))
+    acc, pot = T.forces(theta, 0.01)
+    g = T.group_counts()
+    T.set_mac(None)
+    co, _, lo, _ = T.lists(theta, path="two_pass")
+    assert np.array_equal(g[:, 0], np.diff(co)) and np.array_equal(g[:, 1], np.diff(lo))
+    O = oracle.Tree(pos, m, 1, 1 if n < 20000 else 32)
+    sel = np.random.default_rng(1).choice(O.n_groups, 100, replace=False)
+    ar, pr = O.forces(theta, 0.01, groups=sel)
+    k = ~np.isnan(pr)
+    ea = oracle.rel_err(acc.double().cpu().numpy()[k], ar[k])
+    ep = oracle.rel_err(pot.double().cpu().numpy()[k], pr[k])
+    assert np.median(ea) <= 1e-5 and ea.max() <= 1e-4 and ep.max() <= 1e-4
