@@ -1068,6 +1068,12 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
   // 131 and 125 / 76 / 77 / 101, 5008 items 248 / 201 / 189 / 235 and 137 / 112 / 119 / 172, 7580
   // items 165 / 149 / 164 / 250, 12641 items 219 / 233 / 259 / 402.  (Not
   // with the learned criterion: every wave would run the network.)
+  // Below theta 0.3, where the frontiers outgrow 512 entries, a team of two has a
+  // queue of 1024: calls of 5003 and 10000 single particles as groups took 387 and
+  // 1149 us at theta 0.1 without, with the second tier redoing a quarter and
+  // more of their items, and 241 and 629 with it.  From 0.3 up the two blocks per CU
+  // less that its LDS then holds cost 1 to 2 % (5003 74.1 / 75.3 us at theta 0.5,
+  // 9644 items 168 / 171 at 0.75).
   int team = 1;
   if (!learned && do_eval && !B.export_lists)
     team = T.nw <= 1000 ? 8 : T.nw <= 3500 ? 4 : T.nw <= 11000 ? 2 : 1;
@@ -1082,6 +1088,8 @@ int launch_walk_eval(const DevTree& T, const WalkBufs& B, float theta, float eps
         walk_eval_team_kernel<P, 512, 8><<<(unsigned)T.nw, 8 * kLanes, 0, s>>>(T, B, th2, eps2, acc, pot);
       else if (team == 4)
         walk_eval_team_kernel<P, 512, 4><<<(unsigned)T.nw, 4 * kLanes, 0, s>>>(T, B, th2, eps2, acc, pot);
+      else if (team == 2 && theta < 0.3f)
+        walk_eval_team_kernel<P, 1024, 2><<<(unsigned)T.nw, 2 * kLanes, 0, s>>>(T, B, th2, eps2, acc, pot);
       else if (team == 2)
         walk_eval_team_kernel<P, 512, 2><<<(unsigned)T.nw, 2 * kLanes, 0, s>>>(T, B, th2, eps2, acc, pot);
       else  // 5 blocks of 4 waves per CU (four: 2.36 against 2.32 ms at 2^20)

@@ -105,3 +105,23 @@ def test_more_items_than_the_later_tiers_hold(n, theta, learned):
     ea = oracle.rel_err(acc.double().cpu().numpy()[k], ar[k])
     ep = oracle.rel_err(pot.double().cpu().numpy()[k], pr[k])
     assert np.median(ea) <= 1e-5 and ea.max() <= 1e-4 and ep.max() <= 1e-4
+
+
+@pytest.mark.parametrize("n,n_group", [(5003, 1), (10000, 1), (60000, 64)])
+@pytest.mark.parametrize("theta", [0.1, float(np.nextafter(np.float32(0.3), np.float32(0))), 0.3])
+def test_two_waves_with_the_larger_queue(n, n_group, theta):
+    """Either side of the angle below which teams of two have it; some items outgrow it."""
+    import oracle
+    pos, m = W.plummer(n, 3)
+    T = og.Tree(pos, m, 1, n_group)
+    acc, pot = T.forces(theta, 0.01)
+    g = T.group_counts()
+    co, _, lo, _ = T.lists(theta, path="two_pass")
+    assert np.array_equal(g[:, 0], np.diff(co)) and np.array_equal(g[:, 1], np.diff(lo))
+    O = oracle.Tree(pos, m, 1, n_group)
+    sel = np.random.default_rng(1).choice(O.n_groups, 100, replace=False)
+    ar, pr = O.forces(theta, 0.01, groups=sel)
+    k = ~np.isnan(pr)
+    ea = oracle.rel_err(acc.double().cpu().numpy()[k], ar[k])
+    ep = oracle.rel_err(pot.double().cpu().numpy()[k], pr[k])
+    assert np.median(ea) <= 1e-5 and ea.max() <= 1e-4 and ep.max() <= 1e-4
