@@ -732,10 +732,19 @@ struct BuildInfo {
 // ---- small trees: three launches (keys, order, and one block for all the
 // rest) do what the kernels above and below do in about 25, which for a few
 // thousand particles are all launch and latency.  The same functions and orders, so the
-// same tree.  Rebuild of a Plummer sphere, many launches against three, in us:
-//   300: 94 / 49    1000: 102 / 57    3000: 117 / 79    5003: 136 / 102
-//   8192: 129 / 140
-constexpr int kOneBlock = 7168;  // particles up to which these are used
+// same tree.  The one block's time goes with its cells, hence with the particles
+// per leaf as well.  Rebuild of a Plummer sphere, many launches / three, in us:
+//   particles  n_leaf 1    2          4          8          16
+//   1000       120 / 95    110 / 79   103 / 67   99 / 59    95 / 57
+//   2000       140 / 149   124 / 113  110 / 89   110 / 77   106 / 69
+//   3000       136 / 196   134 / 144  121 / 113  116 / 91   113 / 78
+//   5003       137 / 291   130 / 209  125 / 156  126 / 124  128 / 102
+//   7168       143 / 389   136 / 276  136 / 200  134 / 155  130 / 124
+// The line runs through the crossings; at 8192 and n_leaf 16 it is 129 / 140.
+constexpr int kOneBlock = 7168;  // particles above which it is never one block
+constexpr bool one_block(int64_t n, int n_leaf) {
+  return n <= std::min<int64_t>(kOneBlock, 1400 + 470 * (int64_t)n_leaf);
+}
 constexpr int kSmallN = 8192;    // what they hold (sorted keys in LDS: 64 KB)
 constexpr int kSmallT = 1024;
 
@@ -1415,7 +1424,7 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
   }
   const bool check = inputs_on_device;  // then bbox_kernel checks them
   static_assert(kOneBlock <= kSmallN, "the one block's arrays");
-  const bool small = n <= kOneBlock;
+  const bool small = one_block(n, n_leaf);
 
   // Root cube (the host's rule on the device's bounding box).
   if (!small) {

@@ -29,3 +29,26 @@ def test_too_many_cells_are_refused(n, monkeypatch):
     F.run(0.6, 0.01, 0.0, 1)
     for a, b in zip(before, F.state()):
         assert np.array_equal(a, b)
+
+
+def _same_tree(pos, m, n_leaf, n_group):
+    H = og.Tree(pos, m, n_leaf, n_group)
+    D = og.Tree(pos, m, n_leaf, n_group, device_build=True)
+    assert D.stats == H.stats
+    eh, ed = H.export(), D.export()
+    for k in eh:
+        assert np.array_equal(eh[k].view(np.uint8), ed[k].view(np.uint8)), k
+    return H, D
+
+
+# Either side of the line between the one-block build and the general one, 1400 + 470 n_leaf particles up to
+# 7168, at the ends and in the middle of its range: bit for bit the host's tree, and the same forces.
+@pytest.mark.parametrize("n_leaf,n_group", [(1, 1), (1, 64), (2, 17), (8, 64), (12, 200), (13, 64), (16, 64), (64, 1024)])
+@pytest.mark.parametrize("past", [0, 1])
+def test_line_of_the_one_block_build(n_leaf, n_group, past):
+    import torch
+    n = min(7168, 1400 + 470 * n_leaf) + past
+    pos, m = W.milky_way(n, n_leaf)
+    H, D = _same_tree(pos, m * np.random.default_rng(n).uniform(0.5, 2, n).astype(np.float32), n_leaf, n_group)
+    a, b = H.forces(0.6, 0.01), D.forces(0.6, 0.01)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
