@@ -291,8 +291,8 @@ struct octgrav_tree : DevAlloc {
     }
   }
 
-  // Scratch of a direct sum over nt targets (at most about 33 MB, see
-  // direct_scratch_bytes), kept for the next call; NULL where none is needed
+  // Scratch of a direct sum over nt targets (at most 67 MB: two ranges of just
+  // below 2^20 targets; see direct_plan), kept for the next call; NULL where none is needed
   // or the device has no memory for it (the sum then runs in one range).
   void* d_direct = nullptr;
   int64_t direct_cap = 0;

@@ -17,8 +17,8 @@ using namespace dev;
 constexpr int kThreads = 256;
 constexpr int kDTile = 256;
 
-// Direct sum.  One wave per block takes 64 * kDTpl targets, kDTpl per lane, and
-// one of `splits` contiguous ranges of the particles, streamed through LDS in
+// Direct sum.  One wave per block takes 64 * TPL targets, TPL per lane, and
+// one of the contiguous ranges of the particles, streamed through LDS in
 // tiles of kDTile; plain FP32 per tile folded into compensated pairs.  The
 // target itself contributes -m_i/eps to the potential and nothing to the
 // acceleration; that same FP32 value is removed at the end.
@@ -27,12 +27,11 @@ constexpr int kDTile = 256;
 // issue costs (cycles per wave instruction and SIMD): 2.4 for FP32 arithmetic on
 // vector registers or constants, 4.2 as soon as one operand is a scalar
 // register, 8.3 for v_rsq_f32.  So eps^2 sits in a vector register, one LDS
-// read serves two targets, and the tile loop is unrolled with the reads at
-// constant offsets.  The ranges fill the chip for any number of targets: 4096
-// targets of 2^20 particles made 16 blocks of four waves before (39.6 ms).
-constexpr int kDTpl = 2;
-constexpr int kDTargets = kDTpl * 64;
-
+// read serves two targets (TPL = 2; one where the chip is idle anyway, see
+// direct_plan), and the tile loop is unrolled with the reads at constant
+// offsets.  The ranges fill the chip for any number of targets: 4096 targets of
+// 2^20 particles made 16 blocks of four waves before (39.6 ms, now 1.4).
+template <int TPL>
 __global__ __launch_bounds__(64) void direct_kernel(DevTree T, const int32_t* __restrict__ targets,
                                                     int64_t nt, float eps2, int64_t range,
                                                     float4* __restrict__ part_out,
@@ -41,12 +40,12 @@ __global__ __launch_bounds__(64) void direct_kernel(DevTree T, const int32_t* __
   __shared__ float4 src[kDTile];
   const float4* part = reinterpret_cast<const float4*>(T.part);
   const int lane = threadIdx.x;
-  const int64_t u0 = (int64_t)blockIdx.x * kDTargets + lane;
+  const int64_t u0 = (int64_t)blockIdx.x * (TPL * 64) + lane;
   const int64_t beg = (int64_t)blockIdx.y * range, end = min(T.n, beg + range);
-  float4 xi[kDTpl];
-  Sum4 s[kDTpl];
+  float4 xi[TPL];
+  Sum4 s[TPL];
 #pragma unroll
-  for (int q = 0; q < kDTpl; ++q) {
+  for (int q = 0; q < TPL; ++q) {
     const int64_t u = min(u0 + 64 * q, nt - 1);  // lanes past the end repeat the last target
     xi[q] = part[T.iperm[targets ? targets[u] : u]];
     s[q].zero();
@@ -61,23 +60,23 @@ __global__ __launch_bounds__(64) void direct_kernel(DevTree T, const int32_t* __
     }
     __syncthreads();
     const int cnt = ((int)min((int64_t)kDTile, end - base) + 3) & ~3;
-    float a[kDTpl][4];
+    float a[TPL][4];
 #pragma unroll
-    for (int q = 0; q < kDTpl; ++q) a[q][0] = a[q][1] = a[q][2] = a[q][3] = 0.f;
+    for (int q = 0; q < TPL; ++q) a[q][0] = a[q][1] = a[q][2] = a[q][3] = 0.f;
     for (int j = 0; j < cnt; j += 4) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float4 sj = src[j + k];
 #pragma unroll
-        for (int q = 0; q < kDTpl; ++q) pp_term(xi[q], sj, e2, a[q][0], a[q][1], a[q][2], a[q][3]);
+        for (int q = 0; q < TPL; ++q) pp_term(xi[q], sj, e2, a[q][0], a[q][1], a[q][2], a[q][3]);
       }
     }
 #pragma unroll
-    for (int q = 0; q < kDTpl; ++q) s[q].fold<false>(a[q][0], a[q][1], a[q][2], a[q][3]);
+    for (int q = 0; q < TPL; ++q) s[q].template fold<false>(a[q][0], a[q][1], a[q][2], a[q][3]);
     __syncthreads();
   }
 #pragma unroll
-  for (int q = 0; q < kDTpl; ++q) {
+  for (int q = 0; q < TPL; ++q) {
     const int64_t u = u0 + 64 * q;
     if (u >= nt) continue;
     if (part_out) {
@@ -247,17 +246,32 @@ int launch_com_records(const DevTree& T, float theta, float* out, void* stream) 
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Source ranges of a direct sum: enough waves for eight per SIMD (256 CUs x 4
-// SIMDs; below about four the issue rate falls), each over at least two tiles.
-// The cost of a range is 32 bytes per target written and read again.
-int direct_splits(int64_t n, int64_t nt) {
-  const int64_t tb = (nt + kDTargets - 1) / kDTargets;
-  const int64_t want = (8 * 1024 + tb - 1) / tb, most = (n + 2 * kDTile - 1) / (2 * kDTile);
-  return (int)std::max<int64_t>(1, std::min<int64_t>({want, most, 1024}));
+// Split of a direct sum: targets per lane, and the particle ranges, whole tiles.
+// Ranges: enough waves for eight per SIMD (256 CUs x 4 SIMDs; below about four the
+// issue rate falls).  The cost of a range is 32 bytes per target written and
+// read again.  A sum too small for four waves per SIMD even so is bound by the
+// chain of pairs in a wave, and has one target per lane: us for all of 256 / 512 /
+// 1000 / 8000 particles with one target per lane 32 / 37 / 38 / 61, with two and
+// ranges of two tiles 38 / 55 / 60 / 70, in one range by waves of one target per
+// lane 32 / 42 / 60 / 322.  (Ranges of 128: 33 / 33 / 33 / 65, but 32 instead of 30
+// at 200, where the second launch costs what they save.)
+struct DirectPlan {
+  int tpl, splits;
+  int64_t range;
+};
+static DirectPlan direct_plan(int64_t n, int64_t nt) {
+  auto blocks = [&](int tpl) { return (nt + 64 * tpl - 1) / (64 * tpl); };
+  const int64_t tiles = (n + kDTile - 1) / kDTile;
+  const int tpl = blocks(2) * tiles >= 4 * 1024 ? 2 : 1;
+  const int64_t want = (8 * 1024 + blocks(tpl) - 1) / blocks(tpl);
+  const int64_t k = std::max<int64_t>(1, std::min<int64_t>({want, tiles, 1024}));
+  const int64_t per = (tiles + k - 1) / k;
+  return {tpl, (int)((tiles + per - 1) / per), per * kDTile};  // no empty range
 }
 
 int64_t direct_scratch_bytes(int64_t n, int64_t nt) {
-  const int splits = direct_splits(n, nt);
+  if (nt <= 0) return 0;
+  const int splits = direct_plan(n, nt).splits;
   return splits > 1 ? 32 * (int64_t)splits * nt : 0;
 }
 
@@ -265,15 +279,15 @@ int launch_direct(const DevTree& T, const int32_t* targets, int64_t nt, float ep
                   float* pot, void* scratch, void* stream) {
   if (nt <= 0) return 0;
   hipStream_t s = (hipStream_t)stream;
-  int splits = scratch ? direct_splits(T.n, nt) : 1;
-  const int64_t tiles = (T.n + kDTile - 1) / kDTile, per = (tiles + splits - 1) / splits;
-  splits = (int)((tiles + per - 1) / per);  // no empty range
-  const dim3 grid((nt + kDTargets - 1) / kDTargets, splits);
-  float4* p = splits > 1 ? (float4*)scratch : nullptr;
-  direct_kernel<<<grid, 64, 0, s>>>(T, targets, nt, eps * eps, per * kDTile, p, acc, pot);
+  DirectPlan d = direct_plan(T.n, nt);
+  if (d.splits > 1 && !scratch) d = {d.tpl, 1, T.n};
+  const dim3 grid((nt + 64 * d.tpl - 1) / (64 * d.tpl), d.splits);
+  float4* p = d.splits > 1 ? (float4*)scratch : nullptr;
+  auto* k = d.tpl == 2 ? direct_kernel<2> : direct_kernel<1>;
+  k<<<grid, 64, 0, s>>>(T, targets, nt, eps * eps, d.range, p, acc, pot);
   if (p)
     direct_combine_kernel<<<(nt + kThreads / kDLanes - 1) / (kThreads / kDLanes), kThreads, 0, s>>>(
-        T, targets, nt, eps * eps, splits, p, acc, pot);
+        T, targets, nt, eps * eps, d.splits, p, acc, pot);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
