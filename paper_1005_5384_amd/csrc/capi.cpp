@@ -48,7 +48,8 @@ int fail(int code, const std::string& msg) {
 
 // Set by the environment variable OCTGRAV_FAIL_ALLOC=1 (test-only fault
 // injection): every device allocation of the library fails; by
-// OCTGRAV_ALLOC_LIMIT=<bytes>: a tree's allocations of more than this.
+// OCTGRAV_ALLOC_LIMIT=<bytes>: a tree's allocations of more than this (and its
+// build's, device_malloc).
 bool alloc_fault(size_t bytes = 0) {
   const char* v = std::getenv("OCTGRAV_FAIL_ALLOC");
   if (v && v[0] == '1') return true;
@@ -105,14 +106,20 @@ void set_ctl(WalkBufs& b, void* base) {
 
 }  // namespace
 
-// Network of the learned criterion: FP32 master parameters, Adam moments,
-// the last gradient, the packed BF16 inference image and training scratch.
-// Page-locked copy of a step's results.
+int octgrav::device_malloc(void** p, size_t bytes) {
+  const char* m = std::getenv("OCTGRAV_ALLOC_LIMIT");
+  if (m && (long long)bytes > std::atoll(m)) return hipErrorOutOfMemory;
+  return hipMalloc(p, bytes);
+}
+
+// Page-locked copy of a training step's results.
 struct MlpHost {
   double loss;
   float v[kMlpParams];
 };
 
+// Network of the learned criterion: FP32 master parameters, Adam moments,
+// the last gradient, the packed BF16 inference image and training scratch.
 struct octgrav_mlp {
   hipStream_t stream = nullptr;
   MlpHost *host = nullptr, *host_dev = nullptr;  // and its device address

@@ -206,6 +206,8 @@ struct DevAlloc {
   virtual void expect(size_t) {}
   virtual ~DevAlloc() = default;
 };
+// hipMalloc, with the tests' limit on its size (capi.cpp); a hipError_t.
+int device_malloc(void** p, size_t bytes);
 // Device buffers cut from a few large allocations that are freed together: a
 // tree set up with one hipMalloc and hipFree per array spent 3 of 4 ms on
 // about 75 of them (250k points; a hipFree takes 15 to 400 us).

@@ -1306,11 +1306,17 @@ int exclusive_sum(const T* in, T* out, int64_t n, Scratch& S, hipStream_t s) {
 void* Arena::take(size_t bytes) {
   bytes = (std::max<size_t>(bytes, 1) + 255) & ~size_t(255);
   if (bytes > left) {
-    const size_t want = std::max(bytes, next);
+    // A chunk for all that is expected or, where the device has no room for it in
+    // one piece, for this array alone.
+    size_t want = std::max(bytes, next);
     void* q = nullptr;
-    if (hipMalloc(&q, want) != hipSuccess) {
+    if (device_malloc(&q, want) != hipSuccess) {
       (void)hipGetLastError();
-      return nullptr;
+      want = bytes;
+      if (want >= next || device_malloc(&q, want) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
     }
     chunks.push_back(q);
     at = static_cast<char*>(q);
@@ -1374,9 +1380,10 @@ int build_device_tree(const float* pos_in, const float* mass_in, bool inputs_on_
     pools->outer.rewind();
     pools->cells.rewind();
   }
-  // About what the arrays below add up to (the sort's and the scans' scratch
-  // included); what a build needs beyond that is allocated on its own.
-  Scratch S(pools ? &pools->outer : nullptr, (size_t)n * 96 + (1 << 20));
+  // What the arrays below add up to (the sort's and the scans' scratch included:
+  // 72 to 76 bytes per particle, 16 of them the inputs); what a build needs beyond
+  // that is allocated on its own.
+  Scratch S(pools ? &pools->outer : nullptr, (size_t)n * (inputs_on_device ? 60 : 76) + (1 << 20));
   Scratch CS(pools ? &pools->cells : nullptr, (size_t)n * 48 + (1 << 13));
   auto fail = [&](const char* what) {
     err = what;

@@ -52,3 +52,25 @@ def test_line_of_the_one_block_build(n_leaf, n_group, past):
     H, D = _same_tree(pos, m * np.random.default_rng(n).uniform(0.5, 2, n).astype(np.float32), n_leaf, n_group)
     a, b = H.forces(0.6, 0.01), D.forces(0.6, 0.01)
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("n", [3000, 60000, (1 << 20) + 5])
+@pytest.mark.parametrize("device", [True, False])
+def test_memory_in_pieces(n, device, monkeypatch):
+    """The device has room for every array of a tree, but not for several of them in one piece."""
+    import torch
+    pos, m = W.plummer(n, 4)
+    ref = og.Tree(pos, m, 16, 64, device_build=device)
+    a = ref.forces(0.75, 0.01)
+    # the largest arrays: 16 bytes per particle, 80 per cell (for cells the arrays hold in the one-block build);
+    # the library sort's scratch above 2^20 particles takes 16 more
+    cells = 2 * n + 64 if n < 7168 else ref.stats["n_cells"]
+    most = max((16 if n <= 1 << 20 else 32) * n, 80 * cells) + 4096
+    assert most < 60 * n or n < 7168
+    monkeypatch.setenv("OCTGRAV_ALLOC_LIMIT", str(most))
+    T = og.Tree(pos, m, 16, 64, device_build=device)
+    b = T.forces(0.75, 0.01)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    monkeypatch.setenv("OCTGRAV_ALLOC_LIMIT", str(4 * n))
+    with pytest.raises(og.OctgravError, match="alloc|hipMalloc"):
+        og.Tree(pos, m, 16, 64, device_build=device)
