@@ -74,3 +74,47 @@ def test_memory_in_pieces(n, device, monkeypatch):
     monkeypatch.setenv("OCTGRAV_ALLOC_LIMIT", str(4 * n))
     with pytest.raises(og.OctgravError, match="alloc|hipMalloc"):
         og.Tree(pos, m, 16, 64, device_build=device)
+
+
+# A simulation's handle is rebuilt in place, on either side of the line between the builds' paths: the tree of
+# each step gives a fresh handle's forces.
+@pytest.mark.parametrize("n,n_leaf", [(7168, 16), (7169, 16), (7168, 64), (1870, 1), (1871, 1), (1000, 3), (7169, 1)])
+def test_rebuilt_in_place(n, n_leaf):
+    pos, vel, m = W.plummer_with_velocities(n, 5)
+    S = og.Sim(pos, vel, m, n_leaf, 64)
+    for _ in range(3):
+        S.run(0.6, 0.02, 1.0 / 64, 3)
+        p, _, acc = S.state()
+        a, _ = og.Tree(p, m, n_leaf, 64).forces(0.6, 0.02)  # the host's build
+        assert np.array_equal(a.cpu().numpy(), acc)
+
+
+@pytest.mark.parametrize("n", [1023, 1025, 5000, 7168])
+def test_order_of_ties_in_one_block(n):
+    """Few distinct positions: the order within each is the input's."""
+    rng = np.random.default_rng(n)
+    pos = (rng.integers(-1, 2, (n, 3)) * 0.5).astype(np.float32)
+    _same_tree(pos, rng.uniform(0.5, 2.0, n).astype(np.float32), 16, 64)
+
+
+@pytest.mark.parametrize("n", [20000, 300000])
+def test_misleading_sample_in_a_rebuilt_handle(n):
+    """A step moves the particles to where the sort's sample tells nothing of most of them, so that a bucket is
+    too large and the library sorts instead: in a handle whose arrays hold the step before.  The next step
+    moves them back."""
+    rng = np.random.default_rng(n)
+    s = 2048 if n <= 1 << 16 else 4096 if n <= 1 << 18 else 8192  # the sample's size
+    pos = rng.uniform(-1, 1, (n, 3)).astype(np.float32)
+    to = rng.normal(0.9, 1e-3, (n, 3)).astype(np.float32)
+    to[np.arange(s) * n // s] = rng.uniform(-1, 0, (s, 3)).astype(np.float32)
+    m = np.full(n, 1e-12, np.float32)  # forces that move nothing
+    vel = to - pos
+    S = og.Sim(pos, vel, m, 16, 64)
+    S.run(0.7, 0.05, 0.0, 2)
+    for dt in (1.0, 0.0, -1.0, 1.0, 0.0):
+        S.run(0.7, 0.05, dt, 1)
+        p, _, acc = S.state()
+        if dt == 0.0:
+            assert np.abs(p - to).max() < 1e-5
+        a, _ = og.Tree(p, m, 16, 64).forces(0.7, 0.05)
+        assert np.array_equal(a.cpu().numpy(), acc)
