@@ -54,7 +54,8 @@ extern "C" {
  * OCTGRAV_TWO_PASS    count walk, offsets, write walk and evaluation kernels (the paper's
  *                     structure), pipelined over batches of groups on two streams;
  * OCTGRAV_FUSED_BLOCK one 256-thread block per group walks and evaluates (lists stay in LDS);
- * OCTGRAV_FUSED_WAVE  one 64-lane wave per group walks and evaluates (the default). */
+ * OCTGRAV_FUSED_WAVE  one 64-lane wave per group, or a few that share its walk where the
+ *                     groups are few, walks and evaluates (the default). */
 #define OCTGRAV_TWO_PASS 4u
 #define OCTGRAV_FUSED_BLOCK 8u
 #define OCTGRAV_FUSED_WAVE 16u
@@ -156,10 +157,12 @@ int octgrav_forces_ex(octgrav_tree* t, float theta, float eps, float* acc, float
  * octgrav_mac_stats report this call, as after octgrav_forces.
  *   Sizes: the tree must need at most 128 MiB of scratch (about
  *   16 B x groups + 8 B x max(groups, work items) + one fallback frontier
- *   queue of 8 B x (2 x its widest level + 64) rounded up to a power of two;
- *   the 2^24-particle galaxy mix needs 21.4 MiB + 8 MiB), else OCTGRAV_EINVAL before
- *   any launch.  Fewer fallback queues than octgrav_forces uses may fit
- *   (only the rare walks that outgrow the LDS queues use them).
+ *   queue of 4 B x (2 x its widest level + 64) rounded up to a power of two;
+ *   the 2^24-particle galaxy mix needs 21.4 MiB + 4 MiB), else OCTGRAV_EINVAL before
+ *   any launch.  Where they fit beside that, 32 B x work items hold the
+ *   diagnostics' partial sums (otherwise they are summed over the particles).
+ *   Fewer fallback queues than octgrav_forces uses may fit (only the rare walks
+ *   that outgrow the LDS queues use them).
  *   Sharing: every call on one GPU uses that GPU's one array; it keeps the
  *   last call's contents and each call clears what it needs.  Calls that
  *   overlap in time on one GPU (handles on different streams, or threads)

@@ -158,8 +158,8 @@ struct octgrav_mlp {
     allocs.push_back(*p);
     return OCTGRAV_OK;
   }
-  // Training scratch for batches of up to b samples (activations, gradients
-  // and the partial gradient sums of launch_mlp_loss_grad).
+  // Training scratch for batches of up to b samples (the blocks' partial sums of
+  // launch_mlp_loss_grad).
   int reserve(int64_t b) {
     if (b <= scratch_b) return OCTGRAV_OK;
     if (scratch) {
@@ -744,11 +744,12 @@ enum class Path { TwoPass, FusedBlock, FusedWave };
 
 // Path of a call: an explicit flag, else the fused wave walk, the fastest
 // measured at every angle (ms, fused wave / fused block, at theta 0.3, 0.35,
-// 0.4, 0.5: 2^20 Plummer 8.95 / 11.0, 6.19 / 7.60, 4.30 / 5.46, 2.59 / 3.19;
-// 4M clumps 34.5 / 43.4, 23.5 / 30.0, 16.8 / 21.6, 10.2 / 12.6; the two-pass
-// path trails both).  The wave walk's queue entries of up to eight children
-// keep its 512-entry LDS frontiers from overflowing down to theta 0.3, so it
-// runs 16 walks per CU where the block walk runs four.
+// 0.4, 0.5: 2^20 Plummer 7.90 / 11.0, 5.40 / 7.55, 3.74 / 5.35, 2.26 / 3.11;
+// 4M clumps 31.5 / 43.6, 21.4 / 30.2, 15.0 / 21.5, 9.1 / 12.5; the two-pass
+// path at 0.3 and 0.5 11.7 and 3.28, 44.8 and 11.7).  The wave walk's queue
+// entries of up to eight children keep its 512-entry LDS frontiers from
+// overflowing down to theta 0.3, so it runs 20 walks per CU where the block walk
+// runs four.
 static Path choose_path(uint32_t flags) {
   if (flags & OCTGRAV_TWO_PASS) return Path::TwoPass;
   if (flags & OCTGRAV_FUSED_BLOCK) return Path::FusedBlock;

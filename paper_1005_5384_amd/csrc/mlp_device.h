@@ -28,7 +28,7 @@
 
 #include <cstdint>
 
-#include "octgrav_internal.h"
+#include "walk_types.h"
 
 namespace octgrav {
 

@@ -7,8 +7,8 @@
 //
 // Subdivision: which cells start at a particle follows from the sorted keys
 // around it (level_range), so all levels are numbered by one scan and written
-// by one kernel.  Boxes and moments: one thread per
-// cell, deepest level first.  Then the FP32 images, the walk records, the
+// by one kernel.  Boxes and moments: one thread per leaf, then eight lanes per
+// inner cell, deepest level first.  Then the FP32 images, the walk records, the
 // learned criterion's cell features, the groups (scattered to their first
 // particle and compacted, which orders them by first particle) and the work
 // chunks.

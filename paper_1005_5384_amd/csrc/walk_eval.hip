@@ -707,9 +707,11 @@ void walk_eval_persistent_kernel(
 // its width, and a level of a small tree is one or two steps.  Every wave
 // counts what its window appends and, after a barrier, writes it behind that of the
 // waves before it, so the lists keep the order of the one-wave walk.  The tiles
-// are its tiles too, so that the compensated sums round to the same results:
-// of cells one per wave whenever all have one, and what there is at the end; of each
-// 64 leaves in turns.  The first wave adds the partial sums in wave order.  At 1000 bodies an item takes 13 us, of which 4.4 are seven steps
+// are its tiles too: of cells one per wave whenever all have one, and what there
+// is at the end; of each 64 leaves in turns.  The first wave adds the partial
+// sums in wave order, another order than the one-wave walk's, so the results agree
+// with its to rounding: compensated ones nearly always bit for bit, plain ones
+// not.  At 1000 bodies an item takes 13 us, of which 4.4 are seven steps
 // and 4 its sources; with every wave walking alone and evaluating every NW-th
 // tile, calls took 54 us for 5003 bodies (now 47), 75 for 16384 (67).
 // (Remainders shared evenly by the waves were 1 to 2 us faster, but are other
