@@ -12,6 +12,7 @@
 #include <new>
 #include <memory>
 #include <mutex>
+#include <stdexcept>
 #include <string>
 #include <vector>
 
@@ -1213,14 +1214,14 @@ int octgrav_direct(octgrav_tree* t, float eps, const int32_t* targets, int64_t n
   if (!acc) return fail(OCTGRAV_EINVAL, "acc must be non-NULL");
   if (!targets) nt = t->h.n;
   if (nt < 0) return fail(OCTGRAV_EINVAL, "nt must be >= 0");
-  if (targets && nt > 0) {  // indices are checked on the host before any kernel reads them
-    std::vector<int32_t> tg(nt);
-    if (hipMemcpy(tg.data(), targets, nt * 4, hipMemcpyDeviceToHost) != hipSuccess)
-      return fail(OCTGRAV_EINVAL, "targets is not readable device memory");
-    for (int32_t v : tg)
-      if (v < 0 || v >= t->h.n) return fail(OCTGRAV_EINVAL, "target index out of range");
-  }
   try {
+    if (targets && nt > 0) {  // indices are checked on the host before any kernel reads them
+      std::vector<int32_t> tg(nt);
+      if (hipMemcpy(tg.data(), targets, nt * 4, hipMemcpyDeviceToHost) != hipSuccess)
+        return fail(OCTGRAV_EINVAL, "targets is not readable device memory");
+      for (int32_t v : tg)
+        if (v < 0 || v >= t->h.n) return fail(OCTGRAV_EINVAL, "target index out of range");
+    }
     // The scratch is the handle's: calls from several threads take turns.
     std::lock_guard<std::mutex> lock(t->direct_mu);
     if (launch_direct(t->dt, targets, nt, eps, acc, pot, t->direct_scratch(nt), t->stream))
@@ -1228,6 +1229,10 @@ int octgrav_direct(octgrav_tree* t, float eps, const int32_t* targets, int64_t n
     if (hipStreamSynchronize(t->stream) != hipSuccess)
       return fail(OCTGRAV_EHIP, std::string("device error: ") + hipGetErrorString(hipGetLastError()));
     return OCTGRAV_OK;
+  } catch (const std::bad_alloc&) {
+    return fail(OCTGRAV_ENOMEM, "host allocation failed");
+  } catch (const std::length_error&) {
+    return fail(OCTGRAV_EINVAL, "nt is too large");
   } catch (const std::exception& e) {
     return fail(OCTGRAV_EHIP, e.what());
   }

@@ -43,3 +43,16 @@ def test_without_scratch(n, monkeypatch):
     for u, v in zip(a, b):
         d = (u.double() - v.double()).abs().max()
         assert d <= 8 * 2.0 ** -24 * max(v.abs().max(), 1.0)
+
+
+def test_absurd_number_of_targets_is_an_error():
+    import ctypes
+    import torch
+    pos, m = W.plummer(100, 7)
+    T = og.Tree(pos, m, 16, 64)
+    out = torch.zeros(300, device="cuda")
+    idx = torch.zeros(1, dtype=torch.int32, device="cuda")
+    rc = og.lib().octgrav_direct(T._h, 0.01, ctypes.c_void_p(idx.data_ptr()), 1 << 61,
+                                 ctypes.c_void_p(out.data_ptr()), None)
+    assert rc == og.EINVAL and "nt" in og.last_error()
+    assert (T.direct(0.01)[0] != 0).any()
