@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kST) void cells_kernel(Cells C, const uint64_t* __r
   }
   __syncthreads();
   if (t <= kLevels) {
-    CellSum begin = 0;  // the level's first cell
+    StartCount<SCANNED> begin = 0;  // the level's first cell
     if constexpr (SCANNED) begin = sums[(int64_t)t * nb];
     else
       for (int L = 0; L < t; ++L) begin += all[L];
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kST) void cells_kernel(Cells C, const uint64_t* __r
     if (t < kLevels) {
       int at;
       if constexpr (SCANNED) at = cell_number(sums[(int64_t)t * nb + blk]);
-      else at = (int)begin + before[t];
+      else at = begin + before[t];
       for (int v = 0; v < kSW; ++v) {
         const int k = rows[t][v];
         rows[t][v] = at;
